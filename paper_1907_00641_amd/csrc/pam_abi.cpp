@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <initializer_list>
 #include <string>
 #include <vector>
@@ -77,10 +78,12 @@ struct TimingRec {
     hipEvent_t start, stop;
 };
 
-// Device buffer that only grows.
+// Device buffer that only grows: an allocation of its own, or a part of its
+// group's allocation.
 struct DevBuf {
     void *ptr = nullptr;
     size_t bytes = 0;
+    bool part = false;
 };
 
 }  // namespace
@@ -94,23 +97,29 @@ struct pam_lattice_s {
     Elev E{};
     bool built = false;
 
-    Ctl *ctl = nullptr;       // device control block
-    Ctl *ctl_host = nullptr;  // pinned host copy
-    DevBuf tkeys, tids, vkeys, nbr, vert, lat[4];
-    DevBuf aug[3];          // augmented-channel lattices of the embedding gradient
+    Ctl *ctl = nullptr;             // device control block
+    HostResult *host_result = nullptr;  // pinned host memory the compaction publishes its outcome in
+    uint32_t attempt = 0;               // number of the last build attempt
+    BuildResult result{};               // its outcome
+    // groups of buffers (ensure_group), each with its shared allocation
+    DevBuf table_own, tkeys, tids, bkeys, bcount;  // vertex table; bucket table (distinct vertex-0 keys): keys;
+                                                   // point counts, then starts
+    DevBuf points_own, place, perm, pts, svert, tiles;  // per point: bucket slot and place within the bucket; the
+                                                        // simplex-sorted order and its tile view
+    DevBuf vertex_own, vkeys, nbr;
+    DevBuf lat_own, lat[4];
+    DevBuf aug_own, aug[3];  // augmented-channel lattices of the embedding gradient
     DevBuf part;            // per-block quotient ranges of the range pass
     DevBuf gstart;          // group starts of a batched build (G + 1 int64)
     int32_t groups = 1;
     int32_t gbits = 0;
-    DevBuf ntiles;          // tiles of consecutive points: key dedup of the insert
-    DevBuf bucket, scan;    // points per vertex 0, then bucket starts; scan scratch
-    DevBuf pos0;            // per point: position within its bucket
-    DevBuf perm, pts, svert, tiles;  // the simplex-sorted order and its tile view
     DevBuf hA;              // backward splat's <g_p, A[m_pk]> per sorted point and vertex (raw mode)
-    uint64_t cap = 0;         // hash-table capacity of the last build
-    uint64_t clean_cap = 0;   // table emptied and control counters zeroed for this capacity (0: not known)
+    uint64_t cap = 0;         // vertex-table capacity of the last build
+    uint64_t bcap = 0;        // bucket-table capacity of the last build
+    uint64_t clean_bcap = 0;  // bucket table emptied and control counters zeroed for this capacity (0: not known)
     int64_t M = 0;
     int64_t prev_M = -1;
+    int64_t prev_buckets = -1;
 
     int64_t cap_request = 0;
     bool allow_regrow = true;
@@ -169,6 +178,65 @@ pam_status_t ensure(DevBuf &b, size_t bytes, const char *what)
         return hip_fail(e, what);
     }
     b.bytes = alloc;
+    return PAM_OK;
+}
+
+// Buffers that are sized together.  An allocation of 2 MB and more costs the
+// host up to 0.3 ms, smaller ones a few us (a new handle of 614 400 points:
+// eight large buffers, 1.3 ms), so the large buffers of a group share one
+// allocation and small ones have their own.  Contents are lost when a buffer
+// of the group grows; `moved` tells.
+constexpr size_t kLargeBuffer = (size_t)1 << 20;
+
+struct Want {
+    DevBuf *buf;
+    size_t bytes;
+};
+
+pam_status_t ensure_group(DevBuf &own, std::initializer_list<Want> wants, const char *what, bool *moved = nullptr)
+{
+    auto size = [](const Want &w) { return (std::max(w.bytes, w.buf->bytes) + 255) & ~(size_t)255; };
+    bool grow = false;
+    size_t total = 0;
+    for (const Want &w : wants) {
+        grow = grow || w.bytes > w.buf->bytes;
+        total += size(w) > kLargeBuffer ? size(w) : 0;
+    }
+    if (!grow)
+        return PAM_OK;
+    if (moved)
+        *moved = true;
+    pam_status_t st = PAM_OK;
+    bool large = false;  // a large buffer grows: the shared allocation is replaced
+    for (const Want &w : wants)
+        large = large || (w.bytes > w.buf->bytes && size(w) > kLargeBuffer);
+    if (large) {
+        size_t at = 0;
+        for (const Want &w : wants) {
+            if (size(w) <= kLargeBuffer)
+                continue;
+            if (!w.buf->part && w.buf->ptr)
+                PAM_HIP(hipFree(w.buf->ptr), what);
+            w.buf->ptr = nullptr;
+        }
+        if ((st = ensure(own, total, what)) == PAM_OK) {
+            for (const Want &w : wants) {
+                const size_t bytes = size(w);
+                if (bytes <= kLargeBuffer)
+                    continue;
+                *w.buf = {(char *)own.ptr + at, bytes, true};
+                at += bytes;
+            }
+        } else {
+            for (const Want &w : wants)
+                if (!w.buf->ptr)
+                    *w.buf = DevBuf{};
+            return st;
+        }
+    }
+    for (const Want &w : wants)
+        if (w.bytes > w.buf->bytes && (st = ensure(*w.buf, w.bytes, what)) != PAM_OK)
+            return st;
     return PAM_OK;
 }
 
@@ -276,6 +344,19 @@ pam_status_t check_sticky_error()
     return PAM_OK;
 }
 
+pam_status_t ensure_lattice_buffers(pam_lattice_s *h, int64_t elems)
+{
+    const size_t bytes = (size_t)std::max<int64_t>(elems, 1) * sizeof(float);
+    bool moved = false;
+    pam_status_t st = ensure_group(
+        h->lat_own, {{&h->lat[0], bytes}, {&h->lat[1], bytes}, {&h->lat[2], bytes}, {&h->lat[3], bytes}},
+        "lattice buffers", &moved);
+    if (moved)
+        for (int64_t &z : h->zeroed)
+            z = 0;  // a new allocation holds no known zeros
+    return st;
+}
+
 Groups64 groups_of(const pam_lattice_s *h)
 {
     Groups64 g;
@@ -284,47 +365,149 @@ Groups64 groups_of(const pam_lattice_s *h)
     return g;
 }
 
-// One insertion attempt at capacity h->cap.  Returns the device flags.
-// allow_fixed: the keys may be packed with the fixed layout (no range pass)
-// when the table is known empty at this capacity; a key that does not fit
-// it sets kFlagLayoutMiss and the caller retries without.
-pam_status_t insert_pass(pam_lattice_s *h, bool allow_fixed, uint32_t *flags_out)
+// Vertices the buffers of keys and neighbours hold.
+uint32_t vertex_capacity(const pam_lattice_s *h)
+{
+    const size_t k = h->vkeys.bytes / sizeof(uint64_t), b = h->nbr.bytes / ((size_t)(h->d + 1) * 2 * sizeof(int32_t));
+    return (uint32_t)std::min<size_t>(std::min(k, b), 0x7fffffffu);
+}
+
+// Waits until the compaction of the last attempt has published its outcome:
+// the three words are read until they carry the attempt's number; after
+// kSpinSeconds, or when the attempt did not come that far (a device error),
+// the whole stream is waited for.
+constexpr double kSpinSeconds = 0.2;
+
+pam_status_t await_result(pam_lattice_s *h)
+{
+    auto arrived = [&] {
+        const uint64_t f = __atomic_load_n(&h->host_result->flags, __ATOMIC_ACQUIRE);
+        const uint64_t c = __atomic_load_n(&h->host_result->count, __ATOMIC_ACQUIRE);
+        const uint64_t b = __atomic_load_n(&h->host_result->nbucket, __ATOMIC_ACQUIRE);
+        h->result = {(uint32_t)f, (uint32_t)c, (uint32_t)b, 0u};
+        return (f >> 32) == h->attempt && (c >> 32) == h->attempt && (b >> 32) == h->attempt;
+    };
+    const auto began = std::chrono::steady_clock::now();
+    for (;;) {
+        for (int i = 0; i < 256; ++i) {
+            if (arrived())
+                return PAM_OK;
+            __builtin_ia32_pause();
+        }
+        if (std::chrono::duration<double>(std::chrono::steady_clock::now() - began).count() > kSpinSeconds)
+            break;
+    }
+    PAM_HIP(hipStreamSynchronize(h->stream), "build synchronise");
+    if (!arrived())
+        return fail(PAM_ERR_DEVICE, "the build's outcome was not published");
+    return PAM_OK;
+}
+
+// The build's last two launches.  The host waits for the first alone, which
+// publishes the outcome, so that the second runs while the caller goes on.
+pam_status_t compact_and_resolve(pam_lattice_s *h, int64_t M_estimate)
+{
+    hipStream_t s = h->stream;
+    const uint32_t vcap = vertex_capacity(h);
+    PAM_LAUNCH(h, kKCompact,
+               launch_compact((const uint64_t *)h->tkeys.ptr, (int32_t *)h->tids.ptr, (uint64_t *)h->vkeys.ptr, vcap,
+                              h->cap, h->ctl, h->host_result, ++h->attempt, s),
+               "compact");
+    // the resolve also clears the splat targets of the next forward and
+    // backward calls (buffers 0 and 2) for the last row stride used
+    h->zeroed[0] = h->zeroed[2] = 0;
+    const int64_t zcap = (int64_t)(std::min(h->lat[0].bytes, h->lat[2].bytes) / sizeof(float));
+    PAM_LAUNCH(h, kKResolve,
+               launch_resolve(h->d, h->feat, h->n, h->E, groups_of(h), h->ctl, (const int32_t *)h->perm.ptr,
+                              (const uint64_t *)h->tkeys.ptr, (const int32_t *)h->tids.ptr, h->cap,
+                              (uint8_t *)h->tiles.ptr, (int32_t *)h->svert.ptr, (const uint64_t *)h->vkeys.ptr, vcap,
+                              M_estimate, (int32_t *)h->nbr.ptr, (float *)h->lat[0].ptr, (float *)h->lat[2].ptr,
+                              h->last_ld, zcap, (uint64_t *)h->bkeys.ptr, (int32_t *)h->bcount.ptr, h->bcap, s),
+               "resolve");
+    pam_status_t st = await_result(h);
+    if (st != PAM_OK)
+        return st;
+    const int64_t M = h->result.count;
+    if (h->result.flags == 0 && M <= (int64_t)vcap) {
+        h->clean_bcap = h->bcap;  // the resolve empties the bucket table for the next build
+        if (M * h->last_ld <= zcap)
+            h->zeroed[0] = h->zeroed[2] = M * h->last_ld;
+    }
+    return PAM_OK;
+}
+
+// One build attempt at capacities h->cap and h->bcap; its outcome is in
+// h->result.  allow_fixed: the keys may be packed with the fixed layout (no
+// range pass) when the bucket table is known empty at this capacity; a key
+// that does not fit it sets kFlagLayoutMiss and the caller retries without.
+// A kernel that finds the flags of an earlier one set does nothing.
+pam_status_t build_pass(pam_lattice_s *h, bool allow_fixed)
 {
     hipStream_t s = h->stream;
     pam_status_t st;
-    const void *tk = h->tkeys.ptr;
-    if ((st = ensure(h->tkeys, h->cap * sizeof(uint64_t), "hash table keys")) != PAM_OK)
-        return st;
-    if ((st = ensure(h->tids, h->cap * sizeof(int32_t), "hash table ids")) != PAM_OK)
+    const TileRec rec(h->d);
+    const int64_t n = h->n, ntiles = (n + rec.T - 1) / rec.T;
+    bool moved = false;
+    if ((st = ensure_group(h->table_own,
+                           {{&h->tkeys, h->cap * sizeof(uint64_t)},
+                            {&h->tids, h->cap * sizeof(int32_t)},
+                            {&h->bkeys, h->bcap * sizeof(uint64_t)},
+                            {&h->bcount, h->bcap * sizeof(int32_t)}},
+                           "hash tables", &moved)) != PAM_OK ||
+        (st = ensure_group(h->points_own,
+                           {{&h->place, (size_t)n * sizeof(int2)},
+                            {&h->perm, (size_t)n * sizeof(int32_t)},
+                            {&h->pts, (size_t)n * point_bytes(h->d)},
+                            {&h->svert, (size_t)n * (h->d + 1) * sizeof(int32_t)},
+                            {&h->tiles, (size_t)ntiles * rec.bytes}},
+                           "sorted points")) != PAM_OK)
         return st;
     KeyLayout fixed{};
-    const bool fast = allow_fixed && h->clean_cap == h->cap && h->tkeys.ptr == tk &&
-                      fixed_layout(h->d, h->gbits, &fixed);
-    h->clean_cap = 0;  // the insert fills the table
+    const bool fast = allow_fixed && !moved && h->clean_bcap == h->bcap && fixed_layout(h->d, h->gbits, &fixed);
+    h->clean_bcap = 0;  // the insert fills the table
     if (!fast) {
         if ((st = ensure(h->part, (size_t)kRangePartInts * sizeof(int32_t), "range partials")) != PAM_OK)
             return st;
         PAM_LAUNCH(h, kKRange,
-                   launch_range(h->d, h->feat, h->n, h->E, (int32_t *)h->part.ptr, (uint64_t *)h->tkeys.ptr, h->cap,
-                                s),
+                   launch_range(h->d, h->feat, n, h->E, (int32_t *)h->part.ptr, (uint64_t *)h->bkeys.ptr,
+                                (int32_t *)h->bcount.ptr, h->bcap, s),
                    "range");
-        PAM_LAUNCH(h, kKLayout, launch_layout(h->d, h->n, h->gbits, h->ctl, (const int32_t *)h->part.ptr, s),
-                   "layout");
+        PAM_LAUNCH(h, kKLayout, launch_layout(h->d, n, h->gbits, h->ctl, (const int32_t *)h->part.ptr, s), "layout");
     }
-    const TileRec rec(h->d);
-    const int64_t ntiles = (h->n + rec.T - 1) / rec.T;
-    if ((st = ensure(h->ntiles, (size_t)ntiles * rec.bytes, "per-tile key dedup")) != PAM_OK)
-        return st;
     PAM_LAUNCH(h, kKInsert,
-               launch_insert_tiles(h->d, h->feat, h->n, h->E, groups_of(h), h->ctl, fast ? &fixed : nullptr,
-                                   (uint64_t *)h->tkeys.ptr, h->cap, (uint8_t *)h->ntiles.ptr, s),
+               launch_insert(h->d, h->feat, n, h->E, groups_of(h), h->ctl, fast ? &fixed : nullptr,
+                             (uint64_t *)h->bkeys.ptr, (int32_t *)h->bcount.ptr, h->bcap, (int2 *)h->place.ptr,
+                             (uint64_t *)h->tkeys.ptr, h->cap, s),
                "insert");
-    PAM_HIP(hipMemcpyAsync(h->ctl_host, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s), "readback");
-    PAM_HIP(hipStreamSynchronize(s), "build synchronise");
-    *flags_out = h->ctl_host->flags;
-    // load factor above one half: regrow as for a full table
-    if ((uint64_t)h->ctl_host->count > h->cap / 2)
-        *flags_out |= kFlagTableFull;
+    PAM_LAUNCH(h, kKScan, launch_starts((int32_t *)h->bcount.ptr, h->bcap, h->ctl, s), "scan");
+    PAM_LAUNCH(h, kKScatter,
+               launch_scatter((const int2 *)h->place.ptr, (const int32_t *)h->bcount.ptr, n, h->ctl,
+                              (int32_t *)h->perm.ptr, s),
+               "scatter");
+    PAM_LAUNCH(h, kKTiles,
+               launch_sorted_tiles(h->d, h->feat, n, h->E, groups_of(h), h->ctl, (const int32_t *)h->perm.ptr,
+                                   (uint8_t *)h->pts.ptr, (uint64_t *)h->tkeys.ptr, h->cap, (uint8_t *)h->tiles.ptr,
+                                   s),
+               "tiles");
+    if ((st = compact_and_resolve(h, h->prev_M > 0 ? h->prev_M + h->prev_M / 4 : 1)) != PAM_OK)
+        return st;
+    const int64_t M = h->result.count;
+    if (h->result.flags == 0 && M > (int64_t)vertex_capacity(h)) {
+        // first build, or a lattice that outgrew the buffers: the resolve did
+        // nothing; a quarter more than needed, so that a lattice that grows a
+        // little from build to build seldom comes here
+        const size_t room = (size_t)std::min<int64_t>(M + M / 4, 0x7fffffff);
+        if ((st = ensure_group(h->vertex_own,
+                               {{&h->vkeys, room * sizeof(uint64_t)},
+                                {&h->nbr, room * (h->d + 1) * 2 * sizeof(int32_t)}},
+                               "vertex keys and neighbours")) != PAM_OK)
+            return st;
+        if (h->last_ld > 0 && (st = ensure_lattice_buffers(h, M * h->last_ld)) != PAM_OK)
+            return st;
+        PAM_LAUNCH(h, kKFill, launch_fill_f32((float *)&h->ctl->nvert, 0.0f, 1, s), "id counter clear");
+        if ((st = compact_and_resolve(h, M)) != PAM_OK)
+            return st;
+    }
     return PAM_OK;
 }
 
@@ -351,8 +534,6 @@ const char *pam_last_error(void) { return g_last_error.c_str(); }
 int32_t pam_kernel_count(void) { return kKNumKinds; }
 
 const char *pam_kernel_name(int32_t kind) { return kernel_name(kind); }
-
-static pam_status_t ensure_lattice_buffers(pam_lattice_s *h, int64_t elems);
 
 static pam_status_t build_impl(const float *feat, int64_t n, int32_t d, const int64_t *group_start, int32_t groups,
                                void *stream, pam_lattice_t *lat)
@@ -391,7 +572,7 @@ static pam_status_t build_impl(const float *feat, int64_t n, int32_t d, const in
         }
         hipError_t e = hipMalloc((void **)&h->ctl, sizeof(Ctl));
         if (e == hipSuccess)
-            e = hipHostMalloc((void **)&h->ctl_host, sizeof(Ctl), hipHostMallocDefault);
+            e = hipHostMalloc((void **)&h->host_result, sizeof(HostResult), hipHostMallocCoherent);
         if (e != hipSuccess) {
             pam_status_t st = hip_fail(e, "control block");
             if (h->ctl)
@@ -399,6 +580,7 @@ static pam_status_t build_impl(const float *feat, int64_t n, int32_t d, const in
             delete h;
             return st;
         }
+        *h->host_result = HostResult{0, 0, 0};
         created = true;
     }
     DeviceGuard guard(h->device);
@@ -427,8 +609,6 @@ static pam_status_t build_impl(const float *feat, int64_t n, int32_t d, const in
     }
 
     pam_status_t st;
-    if ((st = ensure(h->vert, (size_t)n * (d + 1) * sizeof(int32_t), "per-point vertex ids")) != PAM_OK)
-        return st;
     if (groups > 1) {
         if ((st = ensure(h->gstart, (size_t)(groups + 1) * sizeof(int64_t), "group starts")) != PAM_OK)
             return st;
@@ -447,11 +627,19 @@ static pam_status_t build_impl(const float *feat, int64_t n, int32_t d, const in
         h->cap = next_pow2((uint64_t)guess);
     }
 
+    // the bucket table keeps its capacity while its load stays between 1/16
+    // and 1/2 (a capacity that changes costs the next build a range pass)
+    if (h->prev_buckets >= 0) {
+        if ((int64_t)h->bcap < 2 * h->prev_buckets || (int64_t)h->bcap > std::max<int64_t>(16 * h->prev_buckets, 1024))
+            h->bcap = std::min<uint64_t>(next_pow2(std::max<int64_t>(4 * h->prev_buckets, 1024)), (uint64_t)1 << 31);
+    } else
+        h->bcap = next_pow2((uint64_t)std::min<int64_t>(std::max<int64_t>(n / 4, 1024), (int64_t)1 << 22));
+
     bool allow_fixed = true;
     for (;;) {
-        uint32_t flags = 0;
-        if ((st = insert_pass(h, allow_fixed, &flags)) != PAM_OK)
+        if ((st = build_pass(h, allow_fixed)) != PAM_OK)
             return st;
+        const uint32_t flags = h->result.flags;
         if (flags & kFlagBadFeature)
             return fail(PAM_ERR_KEY_RANGE, "a feature is not finite or its elevation exceeds 2^24");
         if (flags & kFlagKeyRange)
@@ -460,65 +648,25 @@ static pam_status_t build_impl(const float *feat, int64_t n, int32_t d, const in
             allow_fixed = false;
             continue;
         }
-        if (!(flags & kFlagTableFull))
+        if (!flags)
             break;
-        if (!h->allow_regrow)
-            return fail(PAM_ERR_CAPACITY, "hash table full (regrowth disabled)");
-        if (h->cap >= ((uint64_t)1 << 34))
-            return fail(PAM_ERR_CAPACITY, "hash table cannot grow further");
-        h->cap *= 4;
+        if (flags & kFlagBucketsFull) {
+            if (h->bcap >= ((uint64_t)1 << 31))
+                return fail(PAM_ERR_CAPACITY, "bucket table cannot grow further");
+            h->bcap = std::min<uint64_t>(h->bcap * 4, (uint64_t)1 << 31);
+        }
+        if (flags & kFlagTableFull) {
+            if (!h->allow_regrow)
+                return fail(PAM_ERR_CAPACITY, "hash table full (regrowth disabled)");
+            if (h->cap >= ((uint64_t)1 << 34))
+                return fail(PAM_ERR_CAPACITY, "hash table cannot grow further");
+            h->cap *= 4;
+        }
     }
-
-    const int64_t M = h->ctl_host->count;
-    hipStream_t s = h->stream;
-    const TileRec rec(d);
-    const int64_t ntiles = (n + rec.T - 1) / rec.T;
-    const size_t M1 = (size_t)std::max<int64_t>(M, 1);
-    if ((st = ensure(h->vkeys, M1 * sizeof(uint64_t), "vertex keys")) != PAM_OK ||
-        (st = ensure(h->nbr, M1 * (d + 1) * 2 * sizeof(int32_t), "neighbour table")) != PAM_OK ||
-        (st = ensure(h->bucket, M1 * sizeof(int32_t), "vertex-0 buckets")) != PAM_OK ||
-        (st = ensure(h->scan, (size_t)scan_scratch_ints(M) * sizeof(int32_t), "scan scratch")) != PAM_OK ||
-        (st = ensure(h->pos0, (size_t)n * sizeof(int32_t), "bucket positions")) != PAM_OK ||
-        (st = ensure(h->perm, (size_t)n * sizeof(int32_t), "sorted order")) != PAM_OK ||
-        (st = ensure(h->pts, (size_t)n * point_bytes(d), "sorted point records")) != PAM_OK ||
-        (st = ensure(h->svert, (size_t)n * (d + 1) * sizeof(int32_t), "sorted vertex ids")) != PAM_OK ||
-        (st = ensure(h->tiles, (size_t)ntiles * rec.bytes, "per-tile lattice view")) != PAM_OK)
-        return st;
-    PAM_LAUNCH(h, kKCompact,
-               launch_compact((const uint64_t *)h->tkeys.ptr, (int32_t *)h->tids.ptr,
-                              (uint64_t *)h->vkeys.ptr, (int32_t *)h->bucket.ptr, h->cap, h->ctl, s),
-               "compact");
-    PAM_LAUNCH(h, kKResolve,
-               launch_resolve(d, feat, n, h->E, groups_of(h), h->ctl, (const uint64_t *)h->tkeys.ptr,
-                              (const int32_t *)h->tids.ptr,
-                              h->cap, (uint8_t *)h->ntiles.ptr, (int32_t *)h->vert.ptr,
-                              (int32_t *)h->bucket.ptr, (int32_t *)h->pos0.ptr, (const uint64_t *)h->vkeys.ptr, M,
-                              (int32_t *)h->nbr.ptr, s),
-               "resolve");
-    PAM_LAUNCH(h, kKScan, launch_exclusive_scan((int32_t *)h->bucket.ptr, M, (int32_t *)h->scan.ptr, s), "scan");
-    PAM_LAUNCH(h, kKScatter,
-               launch_scatter(d, feat, n, h->E, (const uint8_t *)h->ntiles.ptr, (const int32_t *)h->vert.ptr,
-                              (const int32_t *)h->bucket.ptr, (const int32_t *)h->pos0.ptr, (int32_t *)h->perm.ptr,
-                              (uint8_t *)h->pts.ptr, (int32_t *)h->svert.ptr, s),
-               "scatter");
-    // the tiles launch also clears the splat targets of the next forward
-    // and backward calls (buffers 0 and 2) for the last row stride used
-    int64_t zelems = 0;
-    h->zeroed[0] = h->zeroed[2] = 0;
-    if (h->last_ld > 0) {
-        zelems = M * h->last_ld;
-        if ((st = ensure_lattice_buffers(h, zelems)) != PAM_OK)
-            return st;
-    }
-    PAM_LAUNCH(h, kKTiles,
-               launch_sorted_tiles(d, (const int32_t *)h->svert.ptr, n, (uint8_t *)h->tiles.ptr,
-                                   (float *)h->lat[0].ptr, (float *)h->lat[2].ptr, zelems, (uint64_t *)h->tkeys.ptr,
-                                   h->cap, h->ctl, s),
-               "tiles");
-    h->zeroed[0] = h->zeroed[2] = zelems;
-    h->clean_cap = h->cap;  // the tiles launch emptied the table for the next build
+    const int64_t M = h->result.count;
     h->M = M;
     h->prev_M = M;
+    h->prev_buckets = h->result.nbucket;
     h->built = true;
     log_line(1, "build n=%lld d=%d groups=%d M=%lld table=%llu", (long long)n, d, h->groups, (long long)M,
              (unsigned long long)h->cap);
@@ -550,19 +698,6 @@ static pam_status_t check_filter_args(pam_lattice_s *h, const float *val, int32_
     if ((flags & PAM_EGRAD_AUGMENTED) && (flags & PAM_NORMALIZE))
         return fail(PAM_ERR_INVALID_ARGUMENT, "PAM_EGRAD_AUGMENTED needs raw mode (no PAM_NORMALIZE)");
     (void)val;  // the callers check the arrays against their row counts
-    return PAM_OK;
-}
-
-static pam_status_t ensure_lattice_buffers(pam_lattice_s *h, int64_t elems)
-{
-    for (int b = 0; b < 4; ++b) {
-        void *before = h->lat[b].ptr;
-        pam_status_t st = ensure(h->lat[b], (size_t)std::max<int64_t>(elems, 1) * sizeof(float), "lattice buffer");
-        if (h->lat[b].ptr != before)
-            h->zeroed[b] = 0;  // a new allocation holds no known zeros
-        if (st != PAM_OK)
-            return st;
-    }
     return PAM_OK;
 }
 
@@ -807,10 +942,10 @@ static pam_status_t filter_bwd(pam_lattice_s *h, int64_t src_n, int64_t tgt_0, c
     q.side = 0;
     q.ld = (int32_t)(((int64_t)h->d * c + 3) & ~(int64_t)3);
     const int64_t qelems = h->M * q.ld;
-    for (int b = 0; b < 3; ++b)
-        if ((st = ensure(h->aug[b], (size_t)std::max<int64_t>(qelems, 1) * sizeof(float), "augmented lattice")) !=
-            PAM_OK)
-            return st;
+    const size_t qbytes = (size_t)std::max<int64_t>(qelems, 1) * sizeof(float);
+    if ((st = ensure_group(h->aug_own, {{&h->aug[0], qbytes}, {&h->aug[1], qbytes}, {&h->aug[2], qbytes}},
+                           "augmented lattices")) != PAM_OK)
+        return st;
     PAM_LAUNCH(h, kKFill, launch_fill_f32((float *)h->aug[0].ptr, 0.0f, qelems, h->stream), "lattice clear");
     PAM_LAUNCH(h, kKSplatAug,
                launch_splat(h->d, q, (const uint8_t *)h->tiles.ptr, val, nullptr, kSplatModeAug,
@@ -1016,6 +1151,7 @@ pam_status_t pam_lattice_export(pam_lattice_t lat, int32_t *keys, int32_t *vert,
         int32_t *tv = (int32_t *)tmp;
         float *tb = (float *)((char *)tmp + ib);
         hipError_t e = launch_export_points(d, (const uint8_t *)h->pts.ptr, (const int32_t *)h->svert.ptr,
+                                            (const uint8_t *)h->tiles.ptr,
                                             (const int32_t *)h->perm.ptr, n, tv, tb, s);
         if (e == hipSuccess && vert)
             e = hipMemcpyAsync(vert, tv, ib, hipMemcpyDeviceToHost, s);
@@ -1117,18 +1253,19 @@ void pam_lattice_destroy(pam_lattice_t lat)
         drain_timing(lat);
         for (hipEvent_t e : lat->event_pool)
             (void)hipEventDestroy(e);
-        DevBuf *bufs[] = {&lat->tkeys, &lat->tids,   &lat->vkeys,  &lat->nbr,    &lat->vert,
-                          &lat->ntiles, &lat->bucket, &lat->scan,   &lat->pos0,   &lat->perm,
-                          &lat->pts,    &lat->svert,  &lat->tiles,  &lat->lat[0], &lat->lat[1],
-                          &lat->lat[2], &lat->lat[3], &lat->part, &lat->gstart, &lat->aug[0],
-                          &lat->aug[1], &lat->aug[2], &lat->hA};
+        DevBuf *bufs[] = {&lat->tkeys,     &lat->tids,       &lat->bkeys,      &lat->bcount, &lat->place,
+                          &lat->perm,      &lat->pts,        &lat->svert,      &lat->tiles,  &lat->vkeys,
+                          &lat->nbr,       &lat->lat[0],     &lat->lat[1],     &lat->lat[2], &lat->lat[3],
+                          &lat->table_own, &lat->points_own, &lat->vertex_own, &lat->lat_own, &lat->part,
+                          &lat->gstart,    &lat->aug[0],     &lat->aug[1],     &lat->aug[2], &lat->aug_own,
+                          &lat->hA};
         for (DevBuf *b : bufs)
-            if (b->ptr)
+            if (b->ptr && !b->part)
                 (void)hipFree(b->ptr);
         if (lat->ctl)
             (void)hipFree(lat->ctl);
-        if (lat->ctl_host)
-            (void)hipHostFree(lat->ctl_host);
+        if (lat->host_result)
+            (void)hipHostFree(lat->host_result);
     }
     delete lat;
 }

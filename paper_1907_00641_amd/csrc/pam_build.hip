@@ -5,17 +5,23 @@
 //   range      per point: rounded remainder-0 quotients -> per-coordinate
 //              min/max (sizes the packed key)
 //   layout     one thread: bit layout of the 63-bit packed key
-//   insert     per tile of consecutive points: the tile's distinct vertex
-//              keys into an open-addressing hash table
+//   insert     per tile of consecutive points: the distinct vertex-0 keys
+//              into a hash table of buckets, and each point's place within
+//              its bucket
+//   scan       per bucket: its start in the order sorted by vertex 0
+//   scatter    per point: its index written to its place in that order
+//   tiles      per tile of the sorted order: simplices, weights and vertex
+//              keys of its points; distinct keys as rows, inserted into the
+//              vertex hash table; contributions sorted by row, segments,
+//              work order
 //   compact    per table slot: dense vertex ids
-//   resolve    per point: the d+1 vertex ids; points counted per vertex 0
-//   scan       exclusive prefix sum of those counts
-//   scatter    per point: barycentric weights, ranks and ids written to the
-//              point's place in the order sorted by vertex 0
-//   tiles      per tile of the sorted order: distinct vertices as rows,
-//              contributions sorted by row, segments, work order
-//   neighbours per vertex and direction: ids of key -/+ u_j (extra blocks
-//              of the resolve launch)
+//   resolve    per tile row: its vertex id; per vertex and direction the
+//              neighbour table, ids of key -/+ u_j (further blocks)
+// Only a point's vertex 0 is needed to sort the points, and a tile of the
+// sorted order has far fewer distinct vertices than one of consecutive
+// points (128^3 volume, d = 5: about 65 against 290; 2 x 160x160x96, d = 8:
+// about 330 against 940), so the d+1 keys of a point are deduplicated and
+// inserted once, in the sorted order.
 #include "pam_device.h"
 
 #include <algorithm>
@@ -26,16 +32,18 @@ namespace pam {
 // part[c * kRangeBlocks + block] and part[(D + c) * kRangeBlocks + block],
 // and whether one of them is not finite or too large, to
 // part[2D * kRangeBlocks + block]; k_layout reduces the blocks.  The grid
-// also clears the hash table for the insert.
+// also empties the bucket table for the insert.
 constexpr int kRangeUnroll = 4;
 
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_range(const float *__restrict__ feat, int64_t n, Elev E,
-                                                  int32_t *__restrict__ part, uint64_t *__restrict__ tkeys,
-                                                  uint64_t cap)
+                                                  int32_t *__restrict__ part, uint64_t *__restrict__ bkeys,
+                                                  int32_t *__restrict__ bcount, uint64_t bcap)
 {
-    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < cap; i += (uint64_t)gridDim.x * kBlock)
-        tkeys[i] = kEmptyKey;
+    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < bcap; i += (uint64_t)gridDim.x * kBlock) {
+        bkeys[i] = kEmptyKey;
+        bcount[i] = 0;
+    }
     __shared__ int smin[kBlock / 64][D];
     __shared__ int smax[kBlock / 64][D];
     int qmin[D], qmax[D];
@@ -151,7 +159,8 @@ __global__ __launch_bounds__(kLayoutThreads) void k_layout(Ctl *ctl, const int32
     ctl->flags = bad ? kFlagBadFeature : 0u;
     ctl->count = 0;
     ctl->nvert = 0;
-    ctl->pad = 0;
+    ctl->nbucket = 0;
+    ctl->nsorted = 0;
     for (int c = 0; c < d; ++c) {
         int lo = INT_MAX, hi = INT_MIN;
         for (int w = 0; w < NW; ++w) {
@@ -202,13 +211,16 @@ __global__ void k_fill_f32(float *p, float value, int64_t count)
 // final key.  Most keys of a tile are already in the table (the tiles
 // around it share them), and the plain load finds those in the caches,
 // where a compare-and-swap would go to the L2 every time.  Counts new keys
-// in `added`; sets `full` if the whole table was probed.  Returns the key's
-// slot (all ones when the table is full).
+// in `added`; sets `full` after kMaxProbe slots (or the whole table), a run
+// that linear probing does not reach at the loads the build accepts (up to
+// one half), so that a table far too small is given up at once.  Returns the
+// key's slot (all ones when the table is full).
+constexpr uint64_t kMaxProbe = 512;
 __device__ __forceinline__ uint64_t table_insert(uint64_t *tkeys, uint64_t mask, uint64_t key, uint32_t &added,
                                                  bool &full)
 {
     uint64_t h = mix64(key) & mask;
-    for (uint64_t probe = 0; probe <= mask; ++probe) {
+    for (uint64_t probe = 0; probe <= mask && probe < kMaxProbe; ++probe) {
         const uint64_t cur = tkeys[h];
         if (cur == key)
             return h;
@@ -231,24 +243,45 @@ __device__ __forceinline__ uint64_t table_insert(uint64_t *tkeys, uint64_t mask,
 // Dense ids for the occupied slots: each block counts its PER * kBlock
 // slots, scans the counts, and takes its id range with one update of a
 // single counter (updates of one address serialise, so large tables take
-// more slots per block).  Also clears the per-vertex bucket counters.
+// more slots per block).  The first thread publishes the build's outcome:
+// to the control block for the resolve (whose further blocks zero the
+// counters) and to the host (pinned memory), which waits for nothing more,
+// so that the caller goes on while the compaction and the resolve run.  Ids
+// from vcap on are not stored: the host then grows its buffers and launches
+// again.
 constexpr uint64_t kCompactWideCap = 1ull << 20;  // tables from this size take 16 slots per thread, else 4
 
 template <int PER>
 __global__ __launch_bounds__(kBlock) void k_compact(const uint64_t *__restrict__ tkeys, int32_t *tids,
-                                                    uint64_t *vkeys, int32_t *__restrict__ bucket, uint64_t cap,
-                                                    Ctl *ctl)
+                                                    uint64_t *vkeys, uint32_t vcap, uint64_t cap, Ctl *ctl,
+                                                    HostResult *result, uint32_t attempt)
 {
     constexpr int kCompactPer = PER;
     __shared__ int cs[kBlock];
     __shared__ int wsum[kBlock / 64 + 1];
     __shared__ uint32_t base_s;
+    const uint32_t count = ctl->count;
+    uint32_t flags = ctl->flags;
+    if ((uint64_t)count > cap / 2)
+        flags |= kFlagTableFull;  // load factor above one half: regrow as for a full table
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const BuildResult r = {flags, count, ctl->nbucket, 0u};
+        ctl->result = r;
+        const uint64_t tag = (uint64_t)attempt << 32;
+        __hip_atomic_store(&result->flags, tag | r.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&result->count, tag | r.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&result->nbucket, tag | r.nbucket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (flags)
+        return;
     const uint64_t b0 = (uint64_t)blockIdx.x * kBlock * kCompactPer + threadIdx.x;
+    uint64_t key[kCompactPer];
     int c = 0;
 #pragma unroll
     for (int j = 0; j < kCompactPer; ++j) {
         const uint64_t s = b0 + (uint64_t)j * kBlock;
-        c += (s < cap && tkeys[s] != kEmptyKey) ? 1 : 0;
+        key[j] = s < cap ? tkeys[s] : kEmptyKey;
+        c += key[j] != kEmptyKey ? 1 : 0;
     }
     cs[threadIdx.x] = c;
     __syncthreads();
@@ -260,14 +293,11 @@ __global__ __launch_bounds__(kBlock) void k_compact(const uint64_t *__restrict__
 #pragma unroll
     for (int j = 0; j < kCompactPer; ++j) {
         const uint64_t s = b0 + (uint64_t)j * kBlock;
-        if (s < cap) {
-            const uint64_t key = tkeys[s];
-            if (key != kEmptyKey) {
-                tids[s] = (int32_t)id;
-                vkeys[id] = key;
-                bucket[id] = 0;  // vertex-0 counts of k_resolve start at zero
-                ++id;
-            }
+        if (key[j] != kEmptyKey) {
+            tids[s] = (int32_t)id;
+            if (id < vcap)
+                vkeys[id] = key[j];
+            ++id;
         }
     }
 }
@@ -297,49 +327,56 @@ __device__ __forceinline__ void unpack_key(uint64_t key, int d, const KeyLayout 
     }
 }
 
-// Pack explicit coordinates (all congruent mod d+1); false if outside the
-// layout's range (such a vertex cannot be in the table).
-__device__ __forceinline__ bool pack_coords(const int *coord, int d, const KeyLayout &lay,
-                                            uint64_t *out)
-{
-    int k = ((coord[0] % (d + 1)) + (d + 1)) % (d + 1);
-    uint64_t key = (uint64_t)k;
-    for (int c = 0; c < d; ++c) {
-        int t = (coord[c] - k) / (d + 1);
-        int64_t off = (int64_t)t - lay.lo[c];
-        if (off < 0 || off >= (1ll << lay.bits[c]))
-            return false;
-        key |= (uint64_t)off << lay.shift[c];
-    }
-    *out = key;
-    return true;
-}
-
-// One entry of the neighbour table, item e = j * M + m: the ids of key_m
-// -/+ u_j (-1 if absent).  nbr is direction-major:
+// One entry of the neighbour table: the ids of key_m -/+ u_j (-1 if
+// absent), u_j = (d+1) e_j - 1.  nbr is direction-major:
 // nbr[(j * M + m) * 2 + 0] = id(key_m - u_j), nbr[(j * M + m) * 2 + 1] = id(key_m + u_j).
-__device__ __forceinline__ void neighbour_item(int d, const uint64_t *__restrict__ vkeys, int64_t M,
-                                               const KeyLayout &lay, const uint64_t *__restrict__ tkeys,
-                                               const int32_t *__restrict__ tids, uint64_t mask,
-                                               int32_t *__restrict__ nbr, int64_t e)
+// On the packed key (remainder k, quotients t_c): adding u_j lowers every
+// coordinate by one and raises coordinate j by d+1, so k becomes k - 1 with
+// t_j + 1, or, from k = 0, k becomes d with every other t_c - 1; subtracting
+// u_j is the reverse.  A quotient that would leave its field has no vertex.
+template <int D>
+__device__ __forceinline__ void neighbour_item(const uint64_t *__restrict__ vkeys, uint32_t M, const KeyLayout &lay,
+                                               const uint64_t *__restrict__ tkeys, const int32_t *__restrict__ tids,
+                                               uint64_t mask, int32_t *__restrict__ nbr, uint32_t e)
 {
-    int64_t m = e % M;
-    int j = (int)(e / M);
-    int base[kMaxD], nb[kMaxD];
+    const int j = (int)(e / M);
+    const uint32_t m = e - (uint32_t)j * M;
     const uint64_t key_m = vkeys[m];
-    const uint64_t gfield = lay.gbits ? key_m & (((1ull << lay.gbits) - 1) << lay.gshift) : 0;
-    unpack_key(key_m, d, lay, base);
-    // both keys first, then both probes side by side: their first slots,
-    // then their ids, are requested together
-    uint64_t key[2] = {0, 0};
-    bool ok[2];
-    for (int sgn = 0; sgn < 2; ++sgn) {
-        int step = sgn ? 1 : -1;
-        for (int c = 0; c < d; ++c)
-            nb[c] = base[c] + step * ((c == j) ? d : -1);
-        ok[sgn] = pack_coords(nb, d, lay, &key[sgn]);
-        key[sgn] |= gfield;
+    const int k = (int)(key_m & ((1ull << lay.kbits) - 1));
+    uint64_t one_j = 0, others = 0;  // 1 in field j; 1 in every other field
+    bool j_min = false, j_max = false, o_min = false, o_max = false;  // a field at its lowest / highest value
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+        const uint64_t top = (1ull << lay.bits[c]) - 1;
+        const uint64_t off = (key_m >> lay.shift[c]) & top;
+        if (c == j) {
+            one_j = 1ull << lay.shift[c];
+            j_min = off == 0;
+            j_max = off == top;
+        } else {
+            others |= 1ull << lay.shift[c];
+            o_min |= off == 0;
+            o_max |= off == top;
+        }
     }
+    uint64_t key[2];
+    bool ok[2];
+    if (k < D) {  // - u_j
+        key[0] = key_m + 1 - one_j;
+        ok[0] = !j_min;
+    } else {
+        key[0] = key_m - D + others;
+        ok[0] = !o_max;
+    }
+    if (k > 0) {  // + u_j
+        key[1] = key_m - 1 + one_j;
+        ok[1] = !j_max;
+    } else {
+        key[1] = key_m + D - others;
+        ok[1] = !o_min;
+    }
+    // both probes side by side: their first slots, then their ids, are
+    // requested together
     uint64_t h[2], cur[2];
     for (int sgn = 0; sgn < 2; ++sgn) {
         h[sgn] = mix64(key[sgn]) & mask;
@@ -361,7 +398,7 @@ __device__ __forceinline__ void neighbour_item(int d, const uint64_t *__restrict
     }
     const int32_t id0 = slot[0] >= 0 ? tids[slot[0]] : -1;
     const int32_t id1 = slot[1] >= 0 ? tids[slot[1]] : -1;
-    reinterpret_cast<int2 *>(nbr)[j * M + m] = make_int2(id0, id1);
+    reinterpret_cast<int2 *>(nbr)[e] = make_int2(id0, id1);
 }
 
 __global__ void k_vertex_groups(const uint64_t *__restrict__ vkeys, int64_t M, const Ctl *ctl, int32_t *vgroup)
@@ -386,85 +423,89 @@ __global__ void k_unpack_keys(int d, const uint64_t *__restrict__ vkeys, int64_t
 }
 
 // Per sorted position s: the point's vertex ids and barycentric weights as
-// the filter kernels read them (the sorted records), written back at the
-// point's original index perm[s].
+// the filter kernels read them (the sorted records and the tile's rows),
+// written back at the point's original index perm[s].
 __global__ void k_export_points(int d, const uint8_t *__restrict__ pts, const int32_t *__restrict__ svert,
-                                const int32_t *__restrict__ perm, int64_t n, int32_t *vert, float *bary)
+                                const uint8_t *__restrict__ tiles, const int32_t *__restrict__ perm, int64_t n,
+                                int32_t *vert, float *bary)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n)
         return;
     const int64_t i = perm[s];
     const float *w = reinterpret_cast<const float *>(pts + s * point_bytes(d));
+    const TileRec rec(d);
+    const int64_t tile = s / rec.T;
+    const int p = (int)(s - tile * rec.T);
+    const uint8_t *R = tiles + (size_t)tile * rec.bytes;
+    const bool overflow = (reinterpret_cast<const uint32_t *>(R)[1] & kTileOverflow) != 0;
+    const int32_t *rowid = reinterpret_cast<const int32_t *>(R + rec.rowid);
+    const uint16_t *lrow = reinterpret_cast<const uint16_t *>(R + rec.lrow);
     for (int k = 0; k <= d; ++k) {
         bary[i * (d + 1) + k] = w[k];
-        vert[i * (d + 1) + k] = svert[s * (d + 1) + k];
+        vert[i * (d + 1) + k] = overflow ? svert[s * (d + 1) + k] : rowid[lrow[p * (d + 1) + k]];
     }
 }
 
-
-// The lattice's vertex set, built a tile of consecutive points at a time:
-// the d+1 vertex keys of every point are deduplicated in an LDS hash
-// (64-bit compare-and-swap), and only the tile's distinct keys are inserted
-// into the global table.  The tile's record keeps the distinct keys and each
-// point's local row, so that k_resolve attaches global ids with one table
-// lookup per distinct key.
-// LDS hash of a tile: 2048 slots while a tile has at most 3072
-// contributions (d <= 5 at 512 points), else 4096.
-__host__ __device__ constexpr int tile_hash_bits(int d) { return tile_points(d) * (d + 1) <= 3072 ? 11 : 12; }
-constexpr int kTileProbe = 64;
+// The points' buckets, a tile of consecutive points at a time: a point's
+// bucket is its vertex 0.  The tile's vertex-0 keys are deduplicated in an
+// LDS hash (64-bit compare-and-swap; it holds twice the tile's points, so it
+// never fills), the tile's points are counted per distinct key, and each
+// distinct key takes its slot of the bucket table and, with one global
+// atomic, its range of the bucket (same-address atomics per point would
+// serialise).  Neighbouring points often share their vertex 0: only the
+// first lane of a run of equal keys in a wave probes the LDS table.
+// Per point: the bucket's slot and the point's place in the bucket.
+// The grid's blocks past the last tile empty the vertex hash table (cap
+// slots), which the tiles launch fills.
+constexpr int kInsertPoints = 512;  // points (= threads) per tile
+constexpr int kInsertHash = 2 * kInsertPoints;
 
 template <int D>
-__global__ __launch_bounds__(tile_points(D)) void k_insert_tiles(const float *__restrict__ feat, int64_t n, Elev E,
-                                                                 Groups64 grp, Ctl *ctl, KeyLayout fixed,
-                                                                 int use_fixed, uint64_t *tkeys, uint64_t mask,
-                                                                 uint8_t *__restrict__ tiles)
+__global__ __launch_bounds__(kInsertPoints) void k_insert(const float *__restrict__ feat, int64_t n, Elev E,
+                                                          Groups64 grp, Ctl *ctl, KeyLayout fixed, int use_fixed,
+                                                          uint64_t *bkeys, uint64_t bmask, int32_t *bcount,
+                                                          int2 *__restrict__ place, uint64_t *__restrict__ tkeys,
+                                                          uint64_t cap)
 {
-    constexpr int T = tile_points(D);
-    constexpr int kTileHashBits = tile_hash_bits(D);
-    constexpr int kTileHash = 1 << kTileHashBits;
-    __shared__ uint64_t hkey[kTileHash];
-    __shared__ int16_t hrow[kTileHash];
-    __shared__ uint64_t rkey[kTileHash];  // distinct keys, row order
-    __shared__ int nrows_s, overflow_s, full_s, miss_s;
+    constexpr int T = kInsertPoints;
+    constexpr int H = kInsertHash;
+    __shared__ uint64_t hkey[H];
+    __shared__ int hcnt[H];   // points of the key, then its base in the bucket
+    __shared__ int hslot[H];  // its slot of the bucket table
+    __shared__ int miss_s, full_s;
     __shared__ uint32_t added_s;
+    const int t = threadIdx.x;
+    const int64_t ntiles = (n + T - 1) / T;
+    if ((int64_t)blockIdx.x >= ntiles) {  // block-uniform
+        const uint64_t e = (uint64_t)((int64_t)blockIdx.x - ntiles) * T + t;  // two slots each
+        if (2 * e < cap)  // cap is a power of two >= 64: whole pieces
+            reinterpret_cast<ulonglong2 *>(tkeys)[e] = make_ulonglong2(kEmptyKey, kEmptyKey);
+        return;
+    }
     if (!use_fixed && (ctl->flags & (kFlagKeyRange | kFlagBadFeature)))
         return;
     const KeyLayout lay = use_fixed ? fixed : ctl->lay;
-    if (use_fixed && blockIdx.x == 0 && threadIdx.x == 0)
+    if (use_fixed && blockIdx.x == 0 && t == 0)
         ctl->lay = fixed;  // for the later kernels of the build (identical in every block)
-    const TileRec rec(D);
-    const int t = threadIdx.x;
-    const int64_t tile = insert_tile((n + T - 1) / T);
-    const int64_t base = tile * T;
+    const int64_t base = insert_tile(ntiles) * T;
     const int nt = (int)min((int64_t)T, n - base);
-    const int nc = nt * (D + 1);
-    uint8_t *R = tiles + (size_t)tile * rec.bytes;
-    uint32_t *hdr = reinterpret_cast<uint32_t *>(R);
-    uint64_t *rowkey = reinterpret_cast<uint64_t *>(R + rec.rowkey);
-    uint16_t *lrow = reinterpret_cast<uint16_t *>(R + rec.lrow);
-    for (int e = t; e < kTileHash; e += T)
+    for (int e = t; e < H; e += T) {
         hkey[e] = kEmptyKey;
+        hcnt[e] = 0;
+    }
     if (t == 0) {
-        nrows_s = 0;
-        overflow_s = 0;
-        added_s = 0;
-        full_s = 0;
         miss_s = 0;
+        full_s = 0;
+        added_s = 0;
     }
     __syncthreads();
-    // Neighbouring points often share vertices: only the first lane of a
-    // run of equal keys in a wave probes the LDS table, the others take its
-    // slot.  The loop over k is wave-uniform (cross-lane operations).
     const int lane = t & 63;
     const bool valid = t < nt;
-    uint64_t key[D + 1];
-    int slot[D + 1];
-    Simplex<D> s;
-    uint64_t gfield = 0;
+    uint64_t key = kEmptyKey;
     if (valid) {
+        Simplex<D> s;
         const bool ok = embed<D>(feat + (base + t) * D, E, s);
-        gfield = group_field(grp, lay, base + t);
         if (use_fixed) {
             // every vertex quotient of the point is q_c or q_c - 1: both must
             // fit the fixed layout's field (else the build takes the range pass)
@@ -477,36 +518,24 @@ __global__ __launch_bounds__(tile_points(D)) void k_insert_tiles(const float *__
             if (!fits)
                 miss_s = 1;
         }
+        key = pack_vertex<D>(s, 0, lay, group_field(grp, lay, base + t));
     }
-#pragma unroll
-    for (int k = 0; k <= D; ++k) {
-        key[k] = valid ? pack_vertex<D>(s, k, lay, gfield) : kEmptyKey;
-        const LaneRun run = lane_run(key[k], valid);
-        int found = -1;
-        if (valid && run.lead == lane) {
-            uint32_t h = (uint32_t)(mix64(key[k]) >> (64 - kTileHashBits));
-            for (int probe = 0; probe < kTileProbe; ++probe) {
-                const uint64_t prev = atomicCAS((unsigned long long *)&hkey[h], (unsigned long long)kEmptyKey,
-                                                (unsigned long long)key[k]);
-                if (prev == kEmptyKey) {
-                    const int r = atomicAdd(&nrows_s, 1);
-                    hrow[h] = r;
-                    rkey[r] = key[k];
-                    found = (int)h;
-                    break;
-                }
-                if (prev == key[k]) {
-                    found = (int)h;
-                    break;
-                }
-                h = (h + 1) & (kTileHash - 1);
-            }
+    const LaneRun run = lane_run(key, valid);
+    int found = 0, lpos = 0;
+    if (valid && run.lead == lane) {
+        uint32_t h = (uint32_t)(mix64(key) >> 32) & (H - 1);
+        for (;;) {  // at most T of the H slots are ever taken: ends at the key or an empty slot
+            const uint64_t prev = atomicCAS((unsigned long long *)&hkey[h], (unsigned long long)kEmptyKey,
+                                            (unsigned long long)key);
+            if (prev == kEmptyKey || prev == key)
+                break;
+            h = (h + 1) & (H - 1);
         }
-        found = __shfl(found, run.lead);
-        slot[k] = found;
-        if (valid && found < 0)
-            overflow_s = 1;
+        found = (int)h;
+        lpos = atomicAdd(&hcnt[h], run.len);
     }
+    found = __shfl(found, run.lead);
+    lpos = __shfl(lpos, run.lead) + (lane - run.lead);
     __syncthreads();
     if (miss_s) {  // block-uniform: the keys are not valid in this layout
         if (t == 0)
@@ -515,27 +544,13 @@ __global__ __launch_bounds__(tile_points(D)) void k_insert_tiles(const float *__
     }
     uint32_t added = 0;
     bool full = false;
-    if (overflow_s) {
-        // no room to deduplicate: every key of the tile goes to the table
-        if (t < nt) {
-#pragma unroll
-            for (int k = 0; k <= D; ++k)
-                table_insert(tkeys, mask, key[k], added, full);
-        }
-    } else {
-        // each distinct key's slot goes to the tile record (its rowid field,
-        // unused by tiles of consecutive points) so that k_resolve reads the
-        // key's id without probing; -1 when the slot does not fit an int32
-        int32_t *rslot = reinterpret_cast<int32_t *>(R + rec.rowid);
-        for (int r = t; r < nrows_s; r += T) {
-            const uint64_t h = table_insert(tkeys, mask, rkey[r], added, full);
-            rowkey[r] = rkey[r];
-            rslot[r] = h <= 0x7fffffffull ? (int32_t)h : -1;
-        }
-        if (t < nt) {
-#pragma unroll
-            for (int k = 0; k <= D; ++k)
-                lrow[t * (D + 1) + k] = (uint16_t)hrow[slot[k]];
+    for (int e = t; e < H; e += T) {
+        if (hkey[e] != kEmptyKey) {
+            const uint64_t slot = table_insert(bkeys, bmask, hkey[e], added, full);
+            if (!full) {
+                hslot[e] = (int)slot;  // the bucket table has at most 2^31 slots
+                hcnt[e] = atomicAdd(&bcount[slot], hcnt[e]);
+            }
         }
     }
     if (added)
@@ -544,388 +559,116 @@ __global__ __launch_bounds__(tile_points(D)) void k_insert_tiles(const float *__
         full_s = 1;
     __syncthreads();
     if (t == 0) {
-        // the count's result is not needed here (the host compares the
-        // final count with the load limit), so the add does not return
+        // no result is needed here, so the adds do not return
         if (added_s)
-            atomicAdd(&ctl->count, added_s);
+            atomicAdd(&ctl->nbucket, added_s);
         if (full_s)
-            atomicOr(&ctl->flags, kFlagTableFull);
-        hdr[0] = overflow_s ? 0u : (uint32_t)nrows_s;
-        hdr[1] = overflow_s ? kTileOverflow : 0u;
-        hdr[2] = (uint32_t)nc;
-        hdr[3] = 0;
+            atomicOr(&ctl->flags, kFlagBucketsFull);
     }
+    if (valid && !full_s)
+        place[base + t] = make_int2(hslot[found], hcnt[found] + lpos);
 }
 
-// Per tile of consecutive points: the global id of each distinct key of the
-// tile, one table lookup each, written over the key's slot in the tile's
-// record (tiles that overflowed their LDS table look up every point's keys
-// and write the points' ids in natural order instead), and each point's
-// position among the points that share its vertex 0.
-// The grid's blocks past the last tile fill the neighbour table (one item
-// per thread), which needs only the compacted vertex keys and the table.
-template <int D>
-__global__ __launch_bounds__(tile_points(D)) void k_resolve(const float *__restrict__ feat, int64_t n, Elev E,
-                                                            Groups64 grp, const Ctl *ctl,
-                                                            const uint64_t *__restrict__ tkeys,
-                                                            const int32_t *__restrict__ tids, uint64_t mask,
-                                                            uint8_t *__restrict__ tiles,
-                                                            int32_t *__restrict__ vert, int32_t *__restrict__ bucket,
-                                                            int32_t *__restrict__ pos0,
-                                                            const uint64_t *__restrict__ vkeys, int64_t M,
-                                                            int32_t *__restrict__ nbr)
+// Bucket counts to bucket starts in the sorted order, in place: each block
+// scans its PER * kBlock slots and takes its range of the order with one
+// update of a single counter.  The order of the buckets is arbitrary (it is
+// the order of a hash), so no scan across blocks is needed.
+template <int PER>
+__global__ __launch_bounds__(kBlock) void k_starts(int32_t *__restrict__ bcount, uint64_t bcap, Ctl *ctl)
 {
-    constexpr int T = tile_points(D);
-    constexpr int NC = T * (D + 1);
-    constexpr int J = (1 << tile_hash_bits(D)) / T;  // rows per thread at most (a tile's rows fit the insert's LDS table)
-    __shared__ int rid[NC];
-    __shared__ int cnt0[NC];  // per row: the tile's points with it as vertex 0, then their bucket base
-    const int64_t ntiles = (n + T - 1) / T;
-    if ((int64_t)blockIdx.x >= ntiles) {  // block-uniform
-        const int64_t e = ((int64_t)blockIdx.x - ntiles) * T + threadIdx.x;
-        if (e < M * (D + 1))
-            neighbour_item(D, vkeys, M, ctl->lay, tkeys, tids, mask, nbr, e);
-        return;
-    }
-    const TileRec rec(D);
-    const int t = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * T;
-    const int nt = (int)min((int64_t)T, n - base);
-    uint8_t *R = tiles + (size_t)blockIdx.x * rec.bytes;
-    const uint32_t *hdr = reinterpret_cast<const uint32_t *>(R);
-    const uint64_t *rowkey = reinterpret_cast<const uint64_t *>(R + rec.rowkey);
-    const uint16_t *lrow = reinterpret_cast<const uint16_t *>(R + rec.lrow);
-    const bool overflow = (hdr[1] & kTileOverflow) != 0;
-    const int nrows = (int)hdr[0];
-    if (!overflow) {
-        // the insert's slot of each distinct key (or -1) becomes the key's id,
-        // in place: the scatter reads the points' ids from this record
-        // (a thread's rows are requested together: slots, then ids)
-        int32_t *rslot = reinterpret_cast<int32_t *>(R + rec.rowid);
-        int32_t hs[J], ids[J];
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-            hs[j] = t + j * T < nrows ? rslot[t + j * T] : -1;
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-            ids[j] = hs[j] >= 0 ? tids[hs[j]] : -1;
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int r = t + j * T;
-            if (r < nrows) {
-                const int32_t id = hs[j] >= 0 ? ids[j] : probe_id(tkeys, tids, mask, rowkey[r]);
-                rid[r] = id;
-                rslot[r] = id;
-                cnt0[r] = 0;
-            }
-        }
-    }
-    __syncthreads();
-    // Bucket positions: the tile's points are counted per vertex-0 row in
-    // LDS (one atomic per run of equal rows in a wave), then each row takes
-    // its range of its bucket with one global atomic.
-    const int lane = t & 63;
-    const bool counted = !overflow && t < nt;
-    const int r0 = counted ? (int)lrow[t * (D + 1)] : 0;
-    const LaneRun run = lane_run((uint64_t)(uint32_t)r0, counted);
-    int lpos = 0;
-    if (counted && run.lead == lane)
-        lpos = atomicAdd(&cnt0[r0], run.len);
-    lpos = __shfl(lpos, run.lead) + (lane - run.lead);
-    __syncthreads();
-    if (!overflow) {
-        int got[J];
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int r = t + j * T;
-            const int c = r < nrows ? cnt0[r] : 0;
-            got[j] = c > 0 ? atomicAdd(&bucket[max(rid[r], 0)], c) : 0;
-        }
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int r = t + j * T;
-            if (r < nrows && cnt0[r] > 0)
-                cnt0[r] = got[j];
-        }
-    }
-    __syncthreads();
-    if (t >= nt)
-        return;
-    const int64_t i = base + t;
-    if (overflow) {
-        // no per-tile rows: every key is looked up, and the ids go to the
-        // natural-order array the scatter reads for such tiles
-        const KeyLayout lay = ctl->lay;
-        Simplex<D> s;
-        embed<D>(feat + i * D, E, s);
-        int ids[D + 1];
-#pragma unroll
-        for (int k = 0; k <= D; ++k) {
-            ids[k] = probe_id(tkeys, tids, mask, pack_vertex<D>(s, k, lay, group_field(grp, lay, i)));
-            vert[i * (D + 1) + k] = ids[k];
-        }
-        pos0[i] = atomicAdd(&bucket[max(ids[0], 0)], 1);
-    } else {
-        pos0[i] = cnt0[r0] + lpos;
-    }
-}
-
-// Exclusive prefix sum of an int array of any length: per-block scans of
-// kBlock * kScanPer elements, a scan of the block totals (one block, in
-// chunks with a running carry), and a final add.
-constexpr int kScanPer = 8;  // elements per thread
-constexpr int kScanChunk = 4096;
-constexpr int64_t kScanOneBlock = 24576;  // up to here one block scans the array
-
-// One block: exclusive scan of x[0..count), count <= kScanOneBlock.  Each
-// thread holds kScanOneBlock / 1024 consecutive elements in registers (read
-// and written as int4), the threads' sums are scanned across the wave with
-// shuffles and across the block's 16 waves in LDS.
-__global__ __launch_bounds__(1024) void k_scan_lds(int32_t *__restrict__ x, int count)
-{
-    constexpr int PER = (int)(kScanOneBlock / 1024);
-    static_assert(PER % 4 == 0 && PER * 1024 == kScanOneBlock, "int4 pieces per thread");
-    constexpr int NW = 1024 / 64;
-    __shared__ int wsum[NW];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int b0 = t * PER;
-    int v[PER];
-#pragma unroll
-    for (int q = 0; q < PER / 4; ++q) {
-        const int e = b0 + 4 * q;
-        int4 z = make_int4(0, 0, 0, 0);
-        if (e + 3 < count) {
-            z = *reinterpret_cast<const int4 *>(x + e);
-        } else {
-            z.x = e < count ? x[e] : 0;
-            z.y = e + 1 < count ? x[e + 1] : 0;
-            z.z = e + 2 < count ? x[e + 2] : 0;
-        }
-        v[4 * q] = z.x;
-        v[4 * q + 1] = z.y;
-        v[4 * q + 2] = z.z;
-        v[4 * q + 3] = z.w;
-    }
-    int s = 0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i)
-        s += v[i];
-    int incl = s;  // inclusive scan of the thread sums over the wave
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(incl, off);
-        if (lane >= off)
-            incl += y;
-    }
-    if (lane == 63)
-        wsum[w] = incl;
-    __syncthreads();
-    if (t == 0) {
-        int run = 0;
-        for (int i = 0; i < NW; ++i) {
-            const int u = wsum[i];
-            wsum[i] = run;
-            run += u;
-        }
-    }
-    __syncthreads();
-    int run = wsum[w] + incl - s;  // exclusive prefix of this thread's first element
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int u = v[i];
-        v[i] = run;
-        run += u;
-    }
-#pragma unroll
-    for (int q = 0; q < PER / 4; ++q) {
-        const int e = b0 + 4 * q;
-        if (e + 3 < count) {
-            *reinterpret_cast<int4 *>(x + e) = make_int4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-        } else {
-            if (e < count)
-                x[e] = v[4 * q];
-            if (e + 1 < count)
-                x[e + 1] = v[4 * q + 1];
-            if (e + 2 < count)
-                x[e + 2] = v[4 * q + 2];
-        }
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_scan_blocks(int32_t *__restrict__ x, int64_t count,
-                                                        int32_t *__restrict__ sums)
-{
-    __shared__ int cs[kBlock * kScanPer];
+    __shared__ int cs[kBlock];
     __shared__ int wsum[kBlock / 64 + 1];
-    const int64_t b0 = (int64_t)blockIdx.x * kBlock * kScanPer;
-    for (int e = threadIdx.x; e < kBlock * kScanPer; e += kBlock)
-        cs[e] = (b0 + e < count) ? x[b0 + e] : 0;
+    __shared__ uint32_t base_s;
+    if (ctl->flags)
+        return;
+    const uint64_t b0 = (uint64_t)blockIdx.x * kBlock * PER + threadIdx.x;
+    int v[PER], c = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint64_t s = b0 + (uint64_t)j * kBlock;
+        v[j] = s < bcap ? bcount[s] : 0;
+        c += v[j];
+    }
+    cs[threadIdx.x] = c;
     __syncthreads();
-    const int total = block_exclusive_scan(cs, kBlock * kScanPer, wsum);
-    for (int e = threadIdx.x; e < kBlock * kScanPer; e += kBlock)
-        if (b0 + e < count)
-            x[b0 + e] = cs[e];
+    const int total = block_exclusive_scan(cs, kBlock, wsum);
     if (threadIdx.x == 0)
-        sums[blockIdx.x] = total;
-}
-
-// One block: in-place exclusive scan of sums[0..nblocks) in chunks with a
-// running carry (the block totals of k_scan_blocks, or a short array).
-__global__ __launch_bounds__(1024) void k_scan_sums(int32_t *__restrict__ sums, int64_t nblocks)
-{
-    __shared__ int cs[kScanChunk];
-    __shared__ int wsum[1024 / 64 + 1];
-    int carry = 0;
-    for (int64_t c0 = 0; c0 < nblocks; c0 += kScanChunk) {
-        for (int e = threadIdx.x; e < kScanChunk; e += 1024)
-            cs[e] = (c0 + e < nblocks) ? sums[c0 + e] : 0;
-        __syncthreads();
-        const int total = block_exclusive_scan(cs, kScanChunk, wsum);
-        for (int e = threadIdx.x; e < kScanChunk; e += 1024)
-            if (c0 + e < nblocks)
-                sums[c0 + e] = cs[e] + carry;
-        carry += total;
-        __syncthreads();
+        base_s = total ? atomicAdd(&ctl->nsorted, (uint32_t)total) : 0u;
+    __syncthreads();
+    int start = (int)base_s + cs[threadIdx.x];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint64_t s = b0 + (uint64_t)j * kBlock;
+        if (s < bcap)
+            bcount[s] = start;
+        start += v[j];
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_add(int32_t *__restrict__ x, int64_t count,
-                                                     const int32_t *__restrict__ sums)
+// Every point's index to its place in the simplex-sorted order: points are
+// grouped by their vertex 0 (bucket starts from k_starts), within a group in
+// the order in which they took their places.
+__global__ __launch_bounds__(kBlock) void k_scatter(const int2 *__restrict__ place,
+                                                    const int32_t *__restrict__ start, int64_t n,
+                                                    const Ctl *ctl, int32_t *__restrict__ perm)
 {
-    const int64_t b0 = (int64_t)blockIdx.x * kBlock * kScanPer;
-    const int add = sums[blockIdx.x];
-    for (int e = threadIdx.x; e < kBlock * kScanPer; e += kBlock)
-        if (b0 + e < count)
-            x[b0 + e] += add;
-}
-
-// Every point to its place in the simplex-sorted order: points are grouped
-// by their vertex 0 (bucket starts from the scan), within a group in the
-// order in which they took their positions.  The point's record there holds
-// its barycentric weights and ranks (recomputed from its features), next to
-// its d+1 vertex ids and its original index.  A vertex id that is missing
-// (never after a successful build) becomes vertex 0 with weight 0.
-template <int D>
-__global__ __launch_bounds__(kBlock) void k_scatter(const float *__restrict__ feat, int64_t n, Elev E,
-                                                    const uint8_t *__restrict__ ntiles,
-                                                    const int32_t *__restrict__ vert,
-                                                    const int32_t *__restrict__ start,
-                                                    const int32_t *__restrict__ pos0, int32_t *__restrict__ perm,
-                                                    uint8_t *__restrict__ psort, int32_t *__restrict__ svert)
-{
-    constexpr int PW = point_bytes(D) / 4;
-    constexpr int T = tile_points(D);
-    static_assert(T % kBlock == 0, "a block's points lie in one tile");
+    if (ctl->flags)
+        return;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n)
         return;
-    // the point's ids: its local rows in its tile of consecutive points and
-    // the tile's row ids (written by the resolve), or the natural-order ids
-    // of a tile that overflowed its LDS table
-    const TileRec rec(D);
-    const int64_t tile = i / T;
-    const int p = (int)(i - tile * T);
-    const uint8_t *R = ntiles + (size_t)tile * rec.bytes;
-    const bool overflow = (reinterpret_cast<const uint32_t *>(R)[1] & kTileOverflow) != 0;
-    int ids[D + 1];
-    if (!overflow) {
-        const uint16_t *lrow = reinterpret_cast<const uint16_t *>(R + rec.lrow) + p * (D + 1);
-        const int32_t *rid = reinterpret_cast<const int32_t *>(R + rec.rowid);
-        int lr[D + 1];
-#pragma unroll
-        for (int k = 0; k <= D; ++k)
-            lr[k] = lrow[k];
-#pragma unroll
-        for (int k = 0; k <= D; ++k)
-            ids[k] = rid[lr[k]];
-    } else {
-#pragma unroll
-        for (int k = 0; k <= D; ++k)
-            ids[k] = vert[i * (D + 1) + k];
-    }
-    const int64_t dst = (int64_t)start[max(ids[0], 0)] + pos0[i];
-    Simplex<D> s;
-    embed<D>(feat + i * D, E, s);
-    float b[D + 1];
-    barycentric<D>(s, feat + i * D, E, b);
-    uint32_t w[PW];
-#pragma unroll
-    for (int u = 0; u < PW; ++u)
-        w[u] = 0u;
-#pragma unroll
-    for (int k = 0; k <= D; ++k)
-        w[k] = __float_as_uint(ids[k] >= 0 ? b[k] : 0.0f);
-#pragma unroll
-    for (int c = 0; c <= D; ++c)
-        w[D + 1 + c / 4] |= (uint32_t)(s.rank[c] & 0xff) << (8 * (c % 4));
-    uint4 *prec = reinterpret_cast<uint4 *>(psort + dst * (PW * 4));
-#pragma unroll
-    for (int u = 0; u < PW / 4; ++u)
-        prec[u] = make_uint4(w[4 * u], w[4 * u + 1], w[4 * u + 2], w[4 * u + 3]);
-    if constexpr ((D + 1) % 2 == 0) {
-#pragma unroll
-        for (int k = 0; k <= D; k += 2)
-            reinterpret_cast<int2 *>(svert + dst * (D + 1))[k / 2] = make_int2(max(ids[k], 0), max(ids[k + 1], 0));
-    } else {
-#pragma unroll
-        for (int k = 0; k <= D; ++k)
-            svert[dst * (D + 1) + k] = max(ids[k], 0);
-    }
-    perm[dst] = (int32_t)i;
+    const int2 sp = place[i];
+    perm[start[sp.x] + sp.y] = (int32_t)i;
 }
 
-// Per tile of the sorted order: the tile's distinct vertex ids become dense
-// rows (LDS hash, integer compare-and-swap); the tile's (point, vertex)
-// contributions are counting-sorted by (window, row) (integer LDS atomics
-// give each its position within its pair); each pair's contributions are
-// cut into segments of at most kSegLen, and the segments are
-// counting-sorted window by window and by length, longest first, the order
-// in which the splat hands them out.
-// The grid's blocks past the last tile clear the first `zelems` floats of
-// z0 and z1 (a multiple of 4; the lattice buffers the next filter calls
-// splat into), so that those calls need no clearing launch of their own,
-// and, with tkeys, empty the hash table's cap slots and zero the control
-// block's flags and counters for the next build's insert.
+// LDS hash of a tile: 2048 slots while a tile has at most 3072
+// contributions (d <= 5 at 512 points), else 4096.
+__host__ __device__ constexpr int tile_hash_bits(int d) { return tile_points(d) * (d + 1) <= 3072 ? 11 : 12; }
+constexpr int kTileProbe = 64;
+
+// Per tile of the sorted order (one thread per point): the point's simplex,
+// barycentric weights and vertex keys from its features; the record of
+// weights and ranks the filter kernels read; the tile's distinct vertex
+// keys become dense rows (LDS hash, 64-bit compare-and-swap) and are
+// inserted into the vertex hash table, their slots kept in the tile record
+// for the resolve; the tile's (point, vertex) contributions are
+// counting-sorted by (window, row) (integer LDS atomics give each its
+// position within its pair); each pair's contributions are cut into
+// segments of at most kSegLen, and the segments are counting-sorted window
+// by window and by length, longest first, the order in which the splat
+// hands them out.  Sorted points share vertices in long runs: only the
+// first lane of a run of equal keys in a wave probes the LDS table and
+// later counts the whole run, the others take its results.
 template <int D>
-__global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const int32_t *__restrict__ svert, int64_t n,
-                                                                 uint8_t *__restrict__ tiles, float *__restrict__ z0,
-                                                                 float *__restrict__ z1, int64_t zelems,
-                                                                 uint64_t *__restrict__ tkeys, uint64_t cap, Ctl *ctl)
+__global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__restrict__ feat, int64_t n, Elev E,
+                                                                 Groups64 grp, Ctl *ctl,
+                                                                 const int32_t *__restrict__ perm,
+                                                                 uint8_t *__restrict__ psort, uint64_t *tkeys,
+                                                                 uint64_t mask, uint8_t *__restrict__ tiles)
 {
     constexpr int T = tile_points(D);
     constexpr int NC = T * (D + 1);
+    constexpr int PW = point_bytes(D) / 4;
     static_assert(NC < (1 << 13), "segment start and row must fit their 13-bit fields");
-    const int64_t ntiles = (n + T - 1) / T;
-    if ((int64_t)blockIdx.x >= ntiles) {  // block-uniform
-        const int64_t e = ((int64_t)blockIdx.x - ntiles) * T + threadIdx.x;  // 16-byte piece
-        if (4 * e < zelems) {
-            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-            reinterpret_cast<float4 *>(z0)[e] = z;
-            reinterpret_cast<float4 *>(z1)[e] = z;
-        }
-        if (tkeys) {
-            if ((uint64_t)(2 * e) < cap)  // cap is a power of two >= 64: whole pieces
-                reinterpret_cast<ulonglong2 *>(tkeys)[e] = make_ulonglong2(kEmptyKey, kEmptyKey);
-            if (e == 0) {
-                ctl->flags = 0;
-                ctl->count = 0;
-                ctl->nvert = 0;
-            }
-        }
-        return;
-    }
     constexpr int kTileHashBits = tile_hash_bits(D);
     constexpr int kTileHash = 1 << kTileHashBits;
-    __shared__ int hkey[kTileHash];
+    __shared__ uint64_t hkey[kTileHash];
     __shared__ int16_t hrow[kTileHash];
     constexpr int kWin = splat_windows(D);  // point windows per tile
     constexpr int kWinPts = T / kWin;
     static_assert(kWin == 1 || kWinPts >= 64, "a wave must not span two windows");
-    __shared__ int cnt[kTileHash + 1];  // per (window, row): count, then first entry
-    __shared__ int nsg[kTileHash + 1];  // per (window, row): segment count, then first segment
+    // the distinct keys in row order, dead once they are inserted; then per
+    // (window, row): count, then first entry (cnt), and segment count, then
+    // first segment (nsg)
+    __shared__ uint64_t rkey[kTileHash + 1];
+    int *cnt = reinterpret_cast<int *>(rkey), *nsg = cnt + kTileHash + 1;
     __shared__ int hist[kWin * (kSegLen + 1)];
     __shared__ int wsum[2 * (T / 64 + 1)];
-    __shared__ int nrows_s, overflow_s;
+    __shared__ int nrows_s, overflow_s, full_s;
+    __shared__ uint32_t added_s;
+    if (ctl->flags & ~kFlagTableFull)  // set by other blocks of this launch: TableFull only
+        return;
+    const KeyLayout lay = ctl->lay;
     const TileRec rec(D);
     const int t = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * T;
@@ -934,50 +677,71 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const int32_t *
     uint8_t *R = tiles + (size_t)blockIdx.x * rec.bytes;
     uint32_t *hdr = reinterpret_cast<uint32_t *>(R);
     int32_t *rowid = reinterpret_cast<int32_t *>(R + rec.rowid);
+    uint64_t *rowkey = reinterpret_cast<uint64_t *>(R + rec.rowkey);
     uint16_t *sfirst = reinterpret_cast<uint16_t *>(R + rec.sfirst);
     uint32_t *seg = reinterpret_cast<uint32_t *>(R + rec.seg);
     uint16_t *order = reinterpret_cast<uint16_t *>(R + rec.order);
     uint16_t *list = reinterpret_cast<uint16_t *>(R + rec.list);
     uint16_t *lrow = reinterpret_cast<uint16_t *>(R + rec.lrow);
     uint16_t *pent = reinterpret_cast<uint16_t *>(R + rec.pent);
+    const bool valid = t < nt;
+    const int64_t i = valid ? perm[base + t] : 0;
     for (int e = t; e < kTileHash; e += T)
-        hkey[e] = -1;
-    for (int e = t; e <= kTileHash; e += T) {
-        cnt[e] = 0;
-        nsg[e] = 0;
-    }
+        hkey[e] = kEmptyKey;
     for (int e = t; e < kWin * (kSegLen + 1); e += T)
         hist[e] = 0;
     if (t == 0) {
         nrows_s = 0;
         overflow_s = 0;
+        full_s = 0;
+        added_s = 0;
+    }
+    Simplex<D> s;
+    uint64_t gfield = 0;
+    if (valid) {
+        embed<D>(feat + i * D, E, s);
+        gfield = group_field(grp, lay, i);
+        float b[D + 1];
+        barycentric<D>(s, feat + i * D, E, b);
+        uint32_t w[PW];
+#pragma unroll
+        for (int u = 0; u < PW; ++u)
+            w[u] = 0u;
+#pragma unroll
+        for (int k = 0; k <= D; ++k)
+            w[k] = __float_as_uint(b[k]);
+#pragma unroll
+        for (int c = 0; c <= D; ++c)
+            w[D + 1 + c / 4] |= (uint32_t)(s.rank[c] & 0xff) << (8 * (c % 4));
+        uint4 *prec = reinterpret_cast<uint4 *>(psort + (base + t) * (PW * 4));
+#pragma unroll
+        for (int u = 0; u < PW / 4; ++u)
+            prec[u] = make_uint4(w[4 * u], w[4 * u + 1], w[4 * u + 2], w[4 * u + 3]);
     }
     __syncthreads();
-    // Sorted points share vertices in long runs: only the first lane of a
-    // run of equal ids in a wave probes the LDS table (and later counts the
-    // whole run), the others take its results.  The loops over k are
-    // wave-uniform (cross-lane operations).
+    // The loops over k are wave-uniform (cross-lane operations).
     const int lane = t & 63;
-    const bool valid = t < nt;
     int slot[D + 1];
     LaneRun run[D + 1];
+    uint64_t key = 0;
 #pragma unroll
     for (int k = 0; k <= D; ++k) {
-        const int m = valid ? svert[(base + t) * (D + 1) + k] : 0;  // >= 0
-        run[k] = lane_run((uint64_t)(uint32_t)m, valid);
+        key = valid ? pack_vertex<D>(s, k, lay, gfield) : kEmptyKey;
+        run[k] = lane_run(key, valid);
         int found = -1;
         if (valid && run[k].lead == lane) {
-            uint32_t h = ((uint32_t)m * 2654435761u) >> (32 - kTileHashBits);
+            uint32_t h = (uint32_t)(mix64(key) >> (64 - kTileHashBits));
             for (int probe = 0; probe < kTileProbe; ++probe) {
-                const int prev = atomicCAS(&hkey[h], -1, m);
-                if (prev == -1) {
+                const uint64_t prev = atomicCAS((unsigned long long *)&hkey[h], (unsigned long long)kEmptyKey,
+                                                (unsigned long long)key);
+                if (prev == kEmptyKey) {
                     const int r = atomicAdd(&nrows_s, 1);
                     hrow[h] = r;
-                    rowid[r] = m;
+                    rkey[r] = key;
                     found = (int)h;
                     break;
                 }
-                if (prev == m) {
+                if (prev == key) {
                     found = (int)h;
                     break;
                 }
@@ -992,9 +756,45 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const int32_t *
     __syncthreads();
     // a tile whose (window, row) pairs do not fit the counters or the record
     // takes the overflow path too
-    if (kWin > 1 && t == 0 && !(nrows_s * kWin <= kTileHash && nrows_s * kWin <= NC))
-        overflow_s = 1;
-    __syncthreads();
+    if (kWin > 1) {
+        if (t == 0 && !(nrows_s * kWin <= kTileHash && nrows_s * kWin <= NC))
+            overflow_s = 1;
+        __syncthreads();
+    }
+    const int nrows = nrows_s;
+    uint32_t added = 0;
+    bool full = false;
+    if (overflow_s) {
+        // no room to deduplicate: every key of the tile goes to the table,
+        // and the resolve looks the points' ids up one by one
+        if (valid) {
+#pragma unroll
+            for (int k = 0; k <= D; ++k)
+                table_insert(tkeys, mask, pack_vertex<D>(s, k, lay, gfield), added, full);
+        }
+    } else {
+        // each distinct key's slot, for the resolve; -1 when it does not fit
+        // an int32 (the resolve then looks the key up)
+        for (int r = t; r < nrows; r += T) {
+            const uint64_t kr = rkey[r];
+            const uint64_t h = table_insert(tkeys, mask, kr, added, full);
+            rowkey[r] = kr;
+            rowid[r] = h <= 0x7fffffffull ? (int32_t)h : -1;
+        }
+    }
+    if (added)
+        atomicAdd(&added_s, added);
+    if (full)
+        full_s = 1;
+    __syncthreads();  // rkey is dead from here: its LDS takes the counters
+    if (t == 0) {
+        // the count's result is not needed here (the compaction compares the
+        // final count with the load limit), so the add does not return
+        if (added_s)
+            atomicAdd(&ctl->count, added_s);
+        if (full_s)
+            atomicOr(&ctl->flags, kFlagTableFull);
+    }
     if (overflow_s) {
         if (t == 0) {
             hdr[0] = 0;
@@ -1007,9 +807,11 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const int32_t *
     // Contributions are counting-sorted by (point window, row): a row's
     // contributions from one window of consecutive points form their own
     // segments, and window w's entries and segments are contiguous.
-    const int nrows = nrows_s;
     const int nwin = kWin;
     const int nq = nrows * nwin;
+    for (int e = t; e < nq; e += T)
+        cnt[e] = 0;
+    __syncthreads();
     const int win = nwin > 1 ? t / kWinPts : 0;
     int q[D + 1], pos[D + 1];
 #pragma unroll
@@ -1050,10 +852,10 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const int32_t *
         constexpr int NB = kWin * (kSegLen + 1), NBL = (NB + 63) / 64;
         int v[NBL], sum = 0;
 #pragma unroll
-        for (int i = 0; i < NBL; ++i) {
-            const int b = t * NBL + i;
-            v[i] = b < NB ? hist[b] : 0;
-            sum += v[i];
+        for (int u = 0; u < NBL; ++u) {
+            const int b = t * NBL + u;
+            v[u] = b < NB ? hist[b] : 0;
+            sum += v[u];
         }
         int incl = sum;
 #pragma unroll
@@ -1062,13 +864,13 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const int32_t *
             if (t >= off)
                 incl += y;
         }
-        int run = incl - sum;
+        int first = incl - sum;
 #pragma unroll
-        for (int i = 0; i < NBL; ++i) {
-            const int b = t * NBL + i;
+        for (int u = 0; u < NBL; ++u) {
+            const int b = t * NBL + u;
             if (b < NB)
-                hist[b] = run;
-            run += v[i];
+                hist[b] = first;
+            first += v[u];
         }
     }
     if (t == 0) {
@@ -1091,6 +893,118 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const int32_t *
     }
 }
 
+// The build's last launch, with three kinds of blocks:
+// * tiles, resolve_waves(D) waves each (one up to d = 8, whose tiles have at
+//   most a few hundred rows; four above, where a tile has thousands and one
+//   wave's trips became the launch's tail: 40x36x28 points, d = 12, launch
+//   181 us with one wave per tile): the slot of each row's key becomes its
+//   vertex id (kResolveRows rows per lane requested together: slots, then
+//   ids); a tile that overflowed its LDS table looks up its points' keys one
+//   by one and writes their ids to svert;
+// * the neighbour table, one item per thread and trip;
+// * clears: the first M * zld floats of z0 and z1 (the lattice buffers the
+//   next filter calls splat into, zcap floats each, so that those calls
+//   need no clearing launch of their own), the bucket table, and the
+//   control block's counters, for the next build's insert.
+// Reads the outcome the compaction published; does nothing when the build
+// failed or its vertices do not fit vcap (the buffers of vkeys and nbr).
+constexpr int kResolveRows = 4;
+__host__ __device__ constexpr int resolve_waves(int d) { return d <= 8 ? 1 : 4; }
+
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_resolve(const float *__restrict__ feat, int64_t n, Elev E, Groups64 grp,
+                                                    Ctl *ctl, const int32_t *__restrict__ perm,
+                                                    const uint64_t *__restrict__ tkeys,
+                                                    const int32_t *__restrict__ tids, uint64_t mask,
+                                                    uint8_t *__restrict__ tiles, int32_t *__restrict__ svert,
+                                                    const uint64_t *__restrict__ vkeys, uint32_t vcap,
+                                                    int32_t *__restrict__ nbr, unsigned tile_blocks,
+                                                    unsigned nbr_blocks, float *__restrict__ z0,
+                                                    float *__restrict__ z1, int32_t zld, int64_t zcap,
+                                                    uint64_t *__restrict__ bkeys, int32_t *__restrict__ bcount,
+                                                    uint64_t bcap)
+{
+    constexpr int T = tile_points(D);
+    const uint32_t M = ctl->result.count;
+    if (ctl->result.flags || M > vcap)
+        return;
+    const KeyLayout lay = ctl->lay;
+    if (blockIdx.x < tile_blocks) {
+        const TileRec rec(D);
+        const int lane = threadIdx.x & 63;
+        constexpr int W = resolve_waves(D);
+        const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+        const int64_t tile = wave / W;
+        const int part = (int)(wave % W) * 64 + lane;
+        if (tile * T >= n)
+            return;
+        uint8_t *R = tiles + (size_t)tile * rec.bytes;
+        const uint32_t *hdr = reinterpret_cast<const uint32_t *>(R);
+        if (hdr[1] & kTileOverflow) {
+            const int64_t base = tile * T;
+            const int nt = (int)min((int64_t)T, n - base);
+            for (int p = part; p < nt; p += 64 * W) {
+                const int64_t i = perm[base + p];
+                Simplex<D> s;
+                embed<D>(feat + i * D, E, s);
+                const uint64_t gfield = group_field(grp, lay, i);
+                for (int k = 0; k <= D; ++k)
+                    svert[(base + p) * (D + 1) + k] =
+                        max(probe_id(tkeys, tids, mask, pack_vertex<D>(s, k, lay, gfield)), 0);
+            }
+            return;
+        }
+        int32_t *rowid = reinterpret_cast<int32_t *>(R + rec.rowid);
+        const uint64_t *rowkey = reinterpret_cast<const uint64_t *>(R + rec.rowkey);
+        const int nrows = (int)hdr[0];
+        constexpr int J = kResolveRows;
+        for (int r0 = part; r0 < nrows; r0 += 64 * W * J) {
+            int32_t hs[J], ids[J];
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+                hs[j] = r0 + j * 64 * W < nrows ? rowid[r0 + j * 64 * W] : 0;
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+                ids[j] = hs[j] >= 0 ? tids[hs[j]] : 0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int r = r0 + j * 64 * W;
+                if (r < nrows)
+                    rowid[r] = hs[j] >= 0 ? ids[j] : max(probe_id(tkeys, tids, mask, rowkey[r]), 0);
+            }
+        }
+        return;
+    }
+    const unsigned b = blockIdx.x - tile_blocks;
+    if (b < nbr_blocks) {
+        const uint64_t items = (uint64_t)M * (D + 1);  // < 2^31
+        for (uint64_t e = (uint64_t)b * kBlock + threadIdx.x; e < items; e += (uint64_t)nbr_blocks * kBlock)
+            neighbour_item<D>(vkeys, M, lay, tkeys, tids, mask, nbr, (uint32_t)e);
+        return;
+    }
+    const uint64_t first = (uint64_t)(b - nbr_blocks) * kBlock + threadIdx.x;
+    const uint64_t stride = (uint64_t)(gridDim.x - tile_blocks - nbr_blocks) * kBlock;
+    const int64_t zelems = (int64_t)M * zld;  // a multiple of 4
+    if (zelems <= zcap) {
+        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (uint64_t e = first; (int64_t)(4 * e) < zelems; e += stride) {
+            reinterpret_cast<float4 *>(z0)[e] = z;
+            reinterpret_cast<float4 *>(z1)[e] = z;
+        }
+    }
+    for (uint64_t e = first; 2 * e < bcap; e += stride) {  // bcap is a power of two >= 64
+        reinterpret_cast<ulonglong2 *>(bkeys)[e] = make_ulonglong2(kEmptyKey, kEmptyKey);
+        reinterpret_cast<int2 *>(bcount)[e] = make_int2(0, 0);
+    }
+    if (first == 0) {
+        ctl->flags = 0;
+        ctl->count = 0;
+        ctl->nvert = 0;
+        ctl->nbucket = 0;
+        ctl->nsorted = 0;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
@@ -1103,11 +1017,11 @@ static unsigned range_blocks(int64_t n)
 
 size_t tile_record_bytes_build(int d) { return TileRec(d).bytes; }
 
-hipError_t launch_range(int d, const float *feat, int64_t n, const Elev &E, int32_t *part, uint64_t *tkeys,
-                        uint64_t cap, hipStream_t s)
+hipError_t launch_range(int d, const float *feat, int64_t n, const Elev &E, int32_t *part, uint64_t *bkeys,
+                        int32_t *bcount, uint64_t bcap, hipStream_t s)
 {
     PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_range<D>, dim3(range_blocks(n)), dim3(kBlock), 0, s, feat, n, E, part,
-                                         tkeys, cap));
+                                         bkeys, bcount, bcap));
     return hipGetLastError();
 }
 
@@ -1128,17 +1042,20 @@ hipError_t launch_fill_f32(float *p, float value, int64_t count, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_insert_tiles(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
-                               const KeyLayout *fixed, uint64_t *tkeys, uint64_t cap, uint8_t *tiles,
-                               hipStream_t s)
+hipError_t launch_insert(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
+                         const KeyLayout *fixed, uint64_t *bkeys, int32_t *bcount, uint64_t bcap, int2 *place,
+                         uint64_t *tkeys, uint64_t cap, hipStream_t s)
 {
     if (n <= 0)
         return hipSuccess;
-    const unsigned grid = (unsigned)((n + tile_points(d) - 1) / tile_points(d));
+    if (bcap < 64 || (bcap & (bcap - 1)) != 0 || bcap > ((uint64_t)1 << 31) || cap < 64 || (cap & (cap - 1)) != 0)
+        return hipErrorInvalidValue;
+    const uint64_t T = kInsertPoints;
+    const uint64_t grid = ((uint64_t)n + T - 1) / T + (cap / 2 + T - 1) / T;
     const KeyLayout lay = fixed ? *fixed : KeyLayout{};
     const int use_fixed = fixed ? 1 : 0;
-    PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_insert_tiles<D>, dim3(grid), dim3(tile_points(d)), 0, s, feat, n, E, grp,
-                                         ctl, lay, use_fixed, tkeys, cap - 1, tiles));
+    PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_insert<D>, dim3((unsigned)grid), dim3(kInsertPoints), 0, s, feat, n, E,
+                                         grp, ctl, lay, use_fixed, bkeys, bcap - 1, bcount, place, tkeys, cap));
     return hipGetLastError();
 }
 
@@ -1168,91 +1085,90 @@ bool fixed_layout(int d, int gbits, KeyLayout *lay)
     return true;
 }
 
-hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, const Ctl *ctl,
-                          const uint64_t *tkeys, const int32_t *tids, uint64_t cap, uint8_t *tiles,
-                          int32_t *vert, int32_t *bucket, int32_t *pos0, const uint64_t *vkeys, int64_t M,
-                          int32_t *nbr, hipStream_t s)
+hipError_t launch_starts(int32_t *bcount, uint64_t bcap, Ctl *ctl, hipStream_t s)
 {
-    if (n <= 0)
-        return hipSuccess;
-    const int T = tile_points(d);
-    const int64_t grid = (n + T - 1) / T + (M * (d + 1) + T - 1) / T;
-    PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_resolve<D>, dim3((unsigned)grid), dim3(T), 0, s, feat, n, E, grp, ctl,
-                                         tkeys, tids, cap - 1, tiles, vert, bucket, pos0, vkeys, M, nbr));
-    return hipGetLastError();
-}
-
-int64_t scan_scratch_ints(int64_t count)
-{
-    const int64_t per = (int64_t)kBlock * kScanPer;
-    return count <= 0 ? 1 : (count + per - 1) / per;
-}
-
-hipError_t launch_exclusive_scan(int32_t *x, int64_t count, int32_t *sums, hipStream_t s)
-{
-    if (count <= 0)
-        return hipSuccess;
-    if (count <= kScanOneBlock) {
-        hipLaunchKernelGGL(k_scan_lds, dim3(1), dim3(1024), 0, s, x, (int)count);
-        return hipGetLastError();
+    if (bcap >= kCompactWideCap) {  // as in launch_compact
+        const uint64_t per_block = (uint64_t)kBlock * 16;
+        hipLaunchKernelGGL(k_starts<16>, dim3((unsigned)((bcap + per_block - 1) / per_block)), dim3(kBlock), 0, s,
+                           bcount, bcap, ctl);
+    } else {
+        const uint64_t per_block = (uint64_t)kBlock * 4;
+        hipLaunchKernelGGL(k_starts<4>, dim3((unsigned)((bcap + per_block - 1) / per_block)), dim3(kBlock), 0, s,
+                           bcount, bcap, ctl);
     }
-    const int64_t nb = scan_scratch_ints(count);
-    hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(kBlock), 0, s, x, count, sums);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, sums, nb);
-    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(kBlock), 0, s, x, count, sums);
     return hipGetLastError();
 }
 
-hipError_t launch_scatter(int d, const float *feat, int64_t n, const Elev &E, const uint8_t *ntiles,
-                          const int32_t *vert, const int32_t *start, const int32_t *pos0, int32_t *perm,
-                          uint8_t *psort, int32_t *svert, hipStream_t s)
+hipError_t launch_scatter(const int2 *place, const int32_t *start, int64_t n, const Ctl *ctl, int32_t *perm,
+                          hipStream_t s)
 {
     if (n <= 0)
         return hipSuccess;
-    PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_scatter<D>, dim3(blocks_for(n)), dim3(kBlock), 0, s, feat, n, E, ntiles,
-                                         vert, start, pos0, perm, psort, svert));
+    hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n)), dim3(kBlock), 0, s, place, start, n, ctl, perm);
     return hipGetLastError();
 }
 
-hipError_t launch_sorted_tiles(int d, const int32_t *svert, int64_t n, uint8_t *tiles, float *z0, float *z1,
-                               int64_t zelems, uint64_t *tkeys, uint64_t cap, Ctl *ctl, hipStream_t s)
+hipError_t launch_sorted_tiles(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
+                               const int32_t *perm, uint8_t *psort, uint64_t *tkeys, uint64_t cap, uint8_t *tiles,
+                               hipStream_t s)
 {
     if (n <= 0)
         return hipSuccess;
-    if (zelems % 4 != 0 || (zelems > 0 && (!z0 || !z1)))
-        return hipErrorInvalidValue;
-    if (tkeys && (cap < 2 || (cap & (cap - 1)) != 0 || !ctl))
+    if (cap < 64 || (cap & (cap - 1)) != 0)
         return hipErrorInvalidValue;
     const int T = tile_points(d);
-    const int64_t pieces = std::max<int64_t>(zelems / 4, tkeys ? (int64_t)(cap / 2) : 0);
-    const int64_t grid = (n + T - 1) / T + std::max<int64_t>((pieces + T - 1) / T, tkeys ? 1 : 0);
-    PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_sorted_tiles<D>, dim3((unsigned)grid), dim3(T), 0, s, svert, n, tiles, z0,
-                                         z1, zelems, tkeys, cap, ctl));
+    PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_sorted_tiles<D>, dim3((unsigned)((n + T - 1) / T)), dim3(T), 0, s, feat, n,
+                                         E, grp, ctl, perm, psort, tkeys, cap - 1, tiles));
     return hipGetLastError();
 }
 
-hipError_t launch_compact(const uint64_t *tkeys, int32_t *tids, uint64_t *vkeys, int32_t *bucket, uint64_t cap,
-                          Ctl *ctl, hipStream_t s)
+hipError_t launch_compact(const uint64_t *tkeys, int32_t *tids, uint64_t *vkeys, uint32_t vcap, uint64_t cap,
+                          Ctl *ctl, HostResult *result, uint32_t attempt, hipStream_t s)
 {
     if (cap >= kCompactWideCap) {
         const uint64_t per_block = (uint64_t)kBlock * 16;
         hipLaunchKernelGGL(k_compact<16>, dim3((unsigned)((cap + per_block - 1) / per_block)), dim3(kBlock), 0, s,
-                           tkeys, tids, vkeys, bucket, cap, ctl);
+                           tkeys, tids, vkeys, vcap, cap, ctl, result, attempt);
     } else {
         const uint64_t per_block = (uint64_t)kBlock * 4;
         hipLaunchKernelGGL(k_compact<4>, dim3((unsigned)((cap + per_block - 1) / per_block)), dim3(kBlock), 0, s,
-                           tkeys, tids, vkeys, bucket, cap, ctl);
+                           tkeys, tids, vkeys, vcap, cap, ctl, result, attempt);
     }
     return hipGetLastError();
 }
 
-
-hipError_t launch_export_points(int d, const uint8_t *pts, const int32_t *svert, const int32_t *perm, int64_t n,
-                                int32_t *vert, float *bary, hipStream_t s)
+hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
+                          const int32_t *perm, const uint64_t *tkeys, const int32_t *tids, uint64_t cap,
+                          uint8_t *tiles, int32_t *svert, const uint64_t *vkeys, uint32_t vcap, int64_t M_estimate,
+                          int32_t *nbr, float *z0, float *z1, int32_t zld, int64_t zcap, uint64_t *bkeys,
+                          int32_t *bcount, uint64_t bcap, hipStream_t s)
 {
     if (n <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL(k_export_points, dim3(blocks_for(n)), dim3(kBlock), 0, s, d, pts, svert, perm, n, vert, bary);
+    if (zld % 4 != 0 || (zcap > 0 && (!z0 || !z1)) || (bcap & (bcap - 1)) != 0)
+        return hipErrorInvalidValue;
+    const int64_t ntiles = (n + tile_points(d) - 1) / tile_points(d);
+    const int64_t tile_blocks = (ntiles * resolve_waves(d) + kBlock / 64 - 1) / (kBlock / 64);
+    // the item and clear loops stride over whatever their extents turn out
+    // to be; the estimate only sizes the launch
+    const int64_t items = std::max<int64_t>(M_estimate, 1) * (d + 1);
+    const int64_t nbr_blocks = (items + kBlock - 1) / kBlock;
+    const int64_t pieces = std::max<int64_t>(M_estimate * zld / 4, (int64_t)(bcap / 2));
+    const int64_t clear_blocks = std::min<int64_t>((pieces + kBlock - 1) / kBlock, 4096);
+    PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_resolve<D>, dim3((unsigned)(tile_blocks + nbr_blocks + clear_blocks)),
+                                         dim3(kBlock), 0, s, feat, n, E, grp, ctl, perm, tkeys, tids, cap - 1, tiles,
+                                         svert, vkeys, vcap, nbr, (unsigned)tile_blocks, (unsigned)nbr_blocks, z0, z1,
+                                         zld, zcap, bkeys, bcount, bcap));
+    return hipGetLastError();
+}
+
+hipError_t launch_export_points(int d, const uint8_t *pts, const int32_t *svert, const uint8_t *tiles,
+                                const int32_t *perm, int64_t n, int32_t *vert, float *bary, hipStream_t s)
+{
+    if (n <= 0)
+        return hipSuccess;
+    hipLaunchKernelGGL(k_export_points, dim3(blocks_for(n)), dim3(kBlock), 0, s, d, pts, svert, tiles, perm, n, vert,
+                       bary);
     return hipGetLastError();
 }
 
@@ -1272,7 +1188,5 @@ hipError_t launch_unpack_keys(int d, const uint64_t *vkeys, int64_t M, const Ctl
     hipLaunchKernelGGL(k_unpack_keys, dim3(blocks_for(M)), dim3(kBlock), 0, s, d, vkeys, M, ctl, keys);
     return hipGetLastError();
 }
-
-
 
 }  // namespace pam

@@ -230,9 +230,7 @@ namespace pam {
 // XCDs in turn (block b to XCD b mod 8), each with its own L2.  Here each
 // XCD takes a contiguous range of tiles instead, so that the table lines
 // neighbouring tiles share stay in one L2 (the insert's probes load a slot
-// before swapping it).  A bijection of [0, ntiles).  The other per-tile
-// launches keep the launch order: for the resolve it sets the order of
-// points within a vertex-0 bucket, which the splat's gathers follow.
+// before swapping it).  A bijection of [0, ntiles).
 #ifndef PAM_XCD_INSERT
 #define PAM_XCD_INSERT 1
 #endif
@@ -257,16 +255,14 @@ __host__ __device__ constexpr int tile_points(int d)
                                : (PAM_TILE_POINTS < PAM_TILE_POINTS_HIGH_D ? PAM_TILE_POINTS : PAM_TILE_POINTS_HIGH_D);
 }
 
-// Per-tile view of the lattice.  The build writes one set of records for
-// tiles of consecutive points (rowkey, lrow: the key dedup of the insert)
-// and one for tiles of the simplex-sorted order (every field but rowkey),
-// which the filter kernels read.  A sorted tile is cut into nwin windows of
-// consecutive points.
+// Per-tile view of the lattice, for the tiles of the simplex-sorted order.
+// A tile is cut into nwin windows of consecutive points.
 // With nc = (points in the tile) * (d+1):
 //   hdr    : nrows; flags (bit 0: the tile's vertices did not fit the LDS
 //            dedup table, then only the per-point ids are valid) | nwin << 8;
 //            nc; nseg
 //   rowid  : nrows global vertex ids, one per distinct vertex of the tile
+//            (slots of the vertex table until the resolve)
 //   rowkey : nrows packed keys of those vertices (uint64)
 //   sfirst : nwin * nrows + 1 first segment of each (window, row) pair,
 //            window-major (uint16); the window-w segments of row r are

@@ -453,6 +453,7 @@ __device__ __forceinline__ void norm_bwd_prologue(const FilterArgs &a, const Til
     constexpr int GL = SCH / VEC;
     const int l = threadIdx.x & (GL - 1), q = threadIdx.x / GL, ng = blockDim.x / GL;
     const int C = a.c, ld = a.ld, nrows = (int)tv.hdr[0];
+    const bool ovf = (tv.hdr[1] & kTileOverflow) != 0;
     auto chunk = [&](auto staged_flag, int cc) {
         constexpr bool S = decltype(staged_flag)::value;
         // uniform trip count for the whole block; the group reduction below
@@ -464,7 +465,12 @@ __device__ __forceinline__ void norm_bwd_prologue(const FilterArgs &a, const Til
             int m[D + 1];
 #pragma unroll
             for (int k = 0; k <= D; ++k)
-                m[k] = S ? (int)tv.lrow[pc * (D + 1) + k] : a.svert[(base + pc) * (D + 1) + k];
+                m[k] = S || !ovf ? (int)tv.lrow[pc * (D + 1) + k] : a.svert[(base + pc) * (D + 1) + k];
+            if (!S && !ovf) {
+#pragma unroll
+                for (int k = 0; k <= D; ++k)
+                    m[k] = tv.rowid[m[k]];
+            }
             const bool on = valid && l * VEC < min(SCH, C - cc);
             const Vec<VEC> gv = load_vec<VEC>(g + (int64_t)sperm[pc] * C + cc + l * VEC, on);
             float dot = 0.0f;
@@ -1187,29 +1193,51 @@ __global__ __launch_bounds__(kBlock) void k_blur2(const float *__restrict__ in, 
 // the row; staged rows are zero beyond C.
 // ---------------------------------------------------------------------------
 
-// Phase A of the slice kernels: weights, original index, tile-local rows
-// (when the tile's rows are staged) and ranks (when asked) of each point.
+// Phase A of the slice kernels: weights, original index, ranks (when
+// asked) and rows of each point's vertices: tile-local (slr) when the tile's
+// rows are staged, else global vertex ids (sid, in LDS the staged rows do
+// not use then), from the tile's row ids or, for a tile that overflowed the
+// build's LDS table, from the points' own ids.
 template <int D>
 __device__ __forceinline__ void stage_slice_points(const FilterArgs &a, const TileView &tv, bool staged, int64_t base,
                                                    int nt, float (*sb)[D + 1], uint16_t (*slr)[D + 1],
-                                                   signed char (*srank)[D + 1], int *sperm, int side = kRowNatural)
+                                                   int32_t (*sid)[D + 1], signed char (*srank)[D + 1], int *sperm,
+                                                   int side = kRowNatural)
 {
     stage_points<D>(a, base, nt, sb, nullptr, srank, sperm, side);
     const int t = threadIdx.x;
-    if (staged && t < nt) {
+    if (t >= nt)
+        return;
+    if (tv.hdr[1] & kTileOverflow) {  // block-uniform
 #pragma unroll
         for (int k = 0; k <= D; ++k)
-            slr[t][k] = tv.lrow[t * (D + 1) + k];
+            sid[t][k] = a.svert[(base + t) * (D + 1) + k];
+        return;
+    }
+    int r[D + 1];
+#pragma unroll
+    for (int k = 0; k <= D; ++k)
+        r[k] = tv.lrow[t * (D + 1) + k];
+    if (staged) {
+#pragma unroll
+        for (int k = 0; k <= D; ++k)
+            slr[t][k] = (uint16_t)r[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k <= D; ++k)
+            r[k] = tv.rowid[r[k]];
+#pragma unroll
+        for (int k = 0; k <= D; ++k)
+            sid[t][k] = r[k];
     }
 }
 
-// Row index of vertex k of tile point p: tile-local when staged, else the
-// global vertex id.
-template <int D, bool STAGED>
-__device__ __forceinline__ int point_row(const FilterArgs &a, const uint16_t (*slr)[D + 1], int64_t base, int p,
-                                         int k)
+// Floats of LDS for the staged rows of `nrows` rows at pitch kRowPitch, or
+// for the global vertex ids of a tile that stages none.
+template <int D>
+__host__ __device__ constexpr int stage_floats(int nrows)
 {
-    return STAGED ? (int)slr[p][k] : a.svert[(base + p) * (D + 1) + k];
+    return nrows * kRowPitch > tile_points(D) * (D + 1) ? nrows * kRowPitch : tile_points(D) * (D + 1);
 }
 
 // Staged rows of the slices, one pass of CH channels: pitch CH + 4 floats
@@ -1279,7 +1307,7 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice(FilterArgs a, const uint8_
                                                       const float *__restrict__ A, float *__restrict__ out)
 {
     constexpr int T = Tile<D>::T;
-    constexpr int kFloats = kSliceRows * kRowPitch;
+    constexpr int kFloats = stage_floats<D>(kSliceRows);
     constexpr int RS = kFloats / (CH + 4);  // rows the LDS holds
     __shared__ float sb[T][D + 1];
     __shared__ uint16_t slr[T][D + 1];
@@ -1292,7 +1320,8 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice(FilterArgs a, const uint8_
     const bool full = !ovf && nrows <= RS;
     const int64_t base = (int64_t)blockIdx.x * T;
     const int nt = (int)min((int64_t)T, a.n - base);
-    stage_slice_points<D>(a, tv, full, base, nt, sb, slr, nullptr, sperm, kRowTarget);
+    int32_t(*sid)[D + 1] = reinterpret_cast<int32_t(*)[D + 1]>(rows);
+    stage_slice_points<D>(a, tv, full, base, nt, sb, slr, sid, nullptr, sperm, kRowTarget);
     const Groups gr(CH / VEC, Tile<D>::NW);
     auto rounds = [&](auto mode_flag, int cc) {
         constexpr int MODE = decltype(mode_flag)::value;
@@ -1304,7 +1333,7 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice(FilterArgs a, const uint8_
 #pragma unroll
             for (int k = 0; k <= D; ++k) {
                 ml[k] = MODE != kStageNone ? (int)slr[p][k] : 0;
-                mg[k] = MODE != kStageFull ? a.svert[(base + p) * (D + 1) + k] : 0;
+                mg[k] = MODE != kStageFull ? sid[p][k] : 0;
             }
             float sc = a.E.raw_scale;
             if (a.normalize) {
@@ -1683,7 +1712,7 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice_bwd(FilterArgs a, const ui
     __shared__ uint16_t slr[T][D + 1];
     __shared__ signed char srank[T][D + 1];
     __shared__ int sperm[T];
-    __shared__ __attribute__((aligned(16))) float rowsT[kSliceBwdRows * kRowPitch];
+    __shared__ __attribute__((aligned(16))) float rowsT[stage_floats<D>(kSliceBwdRows)];
     __shared__ __attribute__((aligned(16))) float rowsA[kSliceBwdRows * kRowPitch];
     const TileView tv = tile_view<D>(tiles);
     const int nrows = (int)tv.hdr[0];
@@ -1694,7 +1723,8 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice_bwd(FilterArgs a, const ui
     const int nt = (int)min((int64_t)T, a.n - base);
     const float sc = NORM ? 1.0f : a.E.raw_scale;
     const bool want_f = grad_feat != nullptr;
-    stage_slice_points<D>(a, tv, full, base, nt, sb, slr, want_f ? srank : nullptr, sperm);
+    int32_t(*sid)[D + 1] = reinterpret_cast<int32_t(*)[D + 1]>(rowsT);
+    stage_slice_points<D>(a, tv, full, base, nt, sb, slr, sid, want_f ? srank : nullptr, sperm);
     if (full) {
         stage_rows_p<CH>(rowsT, At, tv.rowid, nrows, ld, C, 0, NORM);
         if (want_f && !HAIN)
@@ -1755,7 +1785,7 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice_bwd(FilterArgs a, const ui
 #pragma unroll
             for (int k = 0; k <= D; ++k) {
                 ml[k] = MODE != kStageNone ? (int)slr[pc][k] : 0;
-                mg[k] = MODE != kStageFull ? a.svert[(base + pc) * (D + 1) + k] : 0;
+                mg[k] = MODE != kStageFull ? sid[pc][k] : 0;
             }
             const int64_t ip = sperm[pc];
             const int rv = ASYM ? side_row(a, ip, kRowSource) : (int)ip;  // row of v and dv, or -1

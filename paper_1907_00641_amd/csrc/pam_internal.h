@@ -18,10 +18,11 @@ constexpr int kMaxD = PAM_MAX_D;
 constexpr uint64_t kEmptyKey = ~0ull;  // hash slot sentinel; packed keys use <= 63 bits
 
 // device-side status bits (Ctl::flags)
-constexpr uint32_t kFlagTableFull = 1u;  // insertion probed the whole table (the host adds: load > cap / 2)
+constexpr uint32_t kFlagTableFull = 1u;  // vertex table full (the compaction adds: load > cap / 2)
 constexpr uint32_t kFlagKeyRange = 2u;   // keys need more than 63 bits
 constexpr uint32_t kFlagBadFeature = 4u; // non-finite feature or |x| > 2^24
 constexpr uint32_t kFlagLayoutMiss = 8u; // a key does not fit the fixed layout of the fast insert
+constexpr uint32_t kFlagBucketsFull = 16u; // bucket table full
 
 // fp32 entries of the embedding matrix E = alpha * Q, (d+1) x d.  Every
 // entry above the diagonal band of column j equals pos[j]; the single
@@ -59,15 +60,32 @@ struct Groups64 {
     int32_t G;
 };
 
+// Outcome of a build attempt, published by the compaction in the control
+// block, and for the host in pinned coherent memory: there each value is
+// the low half of a 64-bit word whose high half is the attempt's number, so
+// that the host can wait for a word to carry it.
+struct BuildResult {
+    uint32_t flags;    // kFlag* bits
+    uint32_t count;    // vertices
+    uint32_t nbucket;  // buckets (distinct vertex-0 keys)
+    uint32_t pad;
+};
+struct HostResult {
+    uint64_t flags, count, nbucket;
+};
+
 // Small device-resident control block of a lattice handle.
 struct Ctl {
     int32_t qmin[kMaxD];  // range of the rounded remainder-0 quotients
     int32_t qmax[kMaxD];
     KeyLayout lay;
-    uint32_t flags;  // kFlag* bits
-    uint32_t count;  // keys inserted into the hash table
-    uint32_t nvert;  // ids handed out by compaction
+    uint32_t flags;    // kFlag* bits
+    uint32_t count;    // keys inserted into the vertex table
+    uint32_t nvert;    // ids handed out by compaction
+    uint32_t nbucket;  // keys inserted into the bucket table
+    uint32_t nsorted;  // places of the sorted order handed out to buckets
     uint32_t pad;
+    BuildResult result;
 };
 
 enum KernelKind : int32_t {
@@ -96,7 +114,7 @@ const char *kernel_name(int32_t kind);
 // simplex-sorted point order
 struct FilterArgs {
     const uint8_t *pts;    // per sorted point: barycentric weights and ranks
-    const int32_t *svert;  // per sorted point: its d+1 vertex ids
+    const int32_t *svert;  // per sorted point: its d+1 vertex ids (tiles that overflowed their LDS table only)
     const int32_t *perm;   // per sorted point: its index in the caller's arrays
     int64_t n;
     int32_t c;       // value channels
@@ -123,49 +141,52 @@ size_t tile_record_bytes_filter(int d);
 
 // ---- launchers (pam_build.hip, pam_filter.hip); all return the hipError_t of the launch
 // the range pass writes per-block partials: kRangeBlocks * (2d + 1) ints
-// (at most kRangePartInts); it also clears the hash table (cap slots)
+// (at most kRangePartInts); it also empties the bucket table (bcap slots)
 constexpr int kRangeBlocks = 2048;
 constexpr int64_t kRangePartInts = (int64_t)kRangeBlocks * (2 * kMaxD + 1);
 // measurement utility (pam_probe.hip)
 hipError_t launch_copy_rows(const float *src, float *dst, const int32_t *perm, int64_t n, int32_t row_floats,
                             int32_t mode, hipStream_t s);
-hipError_t launch_range(int d, const float *feat, int64_t n, const Elev &E, int32_t *part, uint64_t *tkeys,
-                        uint64_t cap, hipStream_t s);
+hipError_t launch_range(int d, const float *feat, int64_t n, const Elev &E, int32_t *part, uint64_t *bkeys,
+                        int32_t *bcount, uint64_t bcap, hipStream_t s);
 hipError_t launch_layout(int d, int64_t n, int gbits, Ctl *ctl, const int32_t *part, hipStream_t s);
 hipError_t launch_fill_f32(float *p, float value, int64_t count, hipStream_t s);
 // fixed: null to take the key layout the range pass computed (ctl->lay);
 // else a fixed layout (fixed_layout) that the insert checks every key
 // against (kFlagLayoutMiss) and writes to ctl->lay; it also flags
-// non-finite features.  The fixed layout needs a table cleared and the
-// control block's flags and counters zeroed (the previous build's tiles
-// launch leaves them so).
-hipError_t launch_insert_tiles(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
-                               const KeyLayout *fixed, uint64_t *tkeys, uint64_t cap, uint8_t *tiles,
-                               hipStream_t s);
+// non-finite features.  The fixed layout needs the bucket table empty and
+// the control block's flags and counters zeroed (the previous build's
+// resolve leaves them so).  place: per point its bucket's slot and its place
+// in the bucket.  Also empties the vertex table (cap slots).
+hipError_t launch_insert(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
+                         const KeyLayout *fixed, uint64_t *bkeys, int32_t *bcount, uint64_t bcap, int2 *place,
+                         uint64_t *tkeys, uint64_t cap, hipStream_t s);
 // A key layout that needs no range pass: every stored coordinate's quotient
 // in [-2^(b-1), 2^(b-1)) with b bits, b = (63 - bits of k - gbits) / d;
 // false when b < 6 (then the range pass always runs).
 bool fixed_layout(int d, int gbits, KeyLayout *lay);
-// also zeroes bucket[0..M)
-hipError_t launch_compact(const uint64_t *tkeys, int32_t *tids, uint64_t *vkeys, int32_t *bucket, uint64_t cap,
-                          Ctl *ctl, hipStream_t s);
-hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, const Ctl *ctl,
-                          const uint64_t *tkeys, const int32_t *tids, uint64_t cap, uint8_t *tiles,
-                          int32_t *vert, int32_t *bucket, int32_t *pos0, const uint64_t *vkeys, int64_t M,
-                          int32_t *nbr, hipStream_t s);
-// ints of scratch launch_exclusive_scan needs for `count` elements
-int64_t scan_scratch_ints(int64_t count);
-hipError_t launch_exclusive_scan(int32_t *x, int64_t count, int32_t *sums, hipStream_t s);
-// ids from the tiles of consecutive points (ntiles, as the resolve left
-// them), or from vert (natural order) for tiles that overflowed
-hipError_t launch_scatter(int d, const float *feat, int64_t n, const Elev &E, const uint8_t *ntiles,
-                          const int32_t *vert, const int32_t *start, const int32_t *pos0, int32_t *perm,
-                          uint8_t *psort, int32_t *svert, hipStream_t s);
-// also clears the first zelems floats (a multiple of 4) of z0 and z1, and,
-// with tkeys, the next build's hash table (cap slots) and the flags and
-// counters of ctl
-hipError_t launch_sorted_tiles(int d, const int32_t *svert, int64_t n, uint8_t *tiles, float *z0, float *z1,
-                               int64_t zelems, uint64_t *tkeys, uint64_t cap, Ctl *ctl, hipStream_t s);
+// bucket counts to starts in the sorted order, in place
+hipError_t launch_starts(int32_t *bcount, uint64_t bcap, Ctl *ctl, hipStream_t s);
+hipError_t launch_scatter(const int2 *place, const int32_t *start, int64_t n, const Ctl *ctl, int32_t *perm,
+                          hipStream_t s);
+// the sorted tiles' records (rows as slots of the vertex table, filled here)
+// and the points' records
+hipError_t launch_sorted_tiles(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
+                               const int32_t *perm, uint8_t *psort, uint64_t *tkeys, uint64_t cap, uint8_t *tiles,
+                               hipStream_t s);
+// dense ids; publishes the outcome to ctl->result and *result (pinned host
+// memory), as attempt number `attempt`; vkeys holds vcap keys
+hipError_t launch_compact(const uint64_t *tkeys, int32_t *tids, uint64_t *vkeys, uint32_t vcap, uint64_t cap,
+                          Ctl *ctl, HostResult *result, uint32_t attempt, hipStream_t s);
+// the tiles' rows as vertex ids, the neighbour table (vcap vertices at most;
+// else nothing is done), and the clears for the calls that follow: M * zld
+// floats of z0 and z1 when they hold them (zcap), the bucket table, ctl's
+// flags and counters.  M_estimate sizes the launch only.
+hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
+                          const int32_t *perm, const uint64_t *tkeys, const int32_t *tids, uint64_t cap,
+                          uint8_t *tiles, int32_t *svert, const uint64_t *vkeys, uint32_t vcap, int64_t M_estimate,
+                          int32_t *nbr, float *z0, float *z1, int32_t zld, int64_t zcap, uint64_t *bkeys,
+                          int32_t *bcount, uint64_t bcap, hipStream_t s);
 // x onto L.  mode: kSplatModePlain (forward, or backward raw),
 // kSplatModeNormBwd (x / z and the weight column b * gamma, with A the
 // forward lattice), kSplatModeAug (d*C channels f_q x_c, a.ld wide).
@@ -194,8 +215,8 @@ hipError_t launch_slice_aug(int d, const FilterArgs &a, const uint8_t *tiles, co
                             const float *A, const float *At, const float *L1, const float *L2, int32_t ldq,
                             float *grad_feat, hipStream_t s);
 // per-point vertex ids and weights from the sorted records, in the caller's order
-hipError_t launch_export_points(int d, const uint8_t *pts, const int32_t *svert, const int32_t *perm, int64_t n,
-                                int32_t *vert, float *bary, hipStream_t s);
+hipError_t launch_export_points(int d, const uint8_t *pts, const int32_t *svert, const uint8_t *tiles,
+                                const int32_t *perm, int64_t n, int32_t *vert, float *bary, hipStream_t s);
 hipError_t launch_unpack_keys(int d, const uint64_t *vkeys, int64_t M, const Ctl *ctl,
                               int32_t *keys, hipStream_t s);
 hipError_t launch_vertex_groups(const uint64_t *vkeys, int64_t M, const Ctl *ctl, int32_t *vgroup, hipStream_t s);

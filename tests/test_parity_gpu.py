@@ -243,6 +243,41 @@ def test_capacity_hint_regrow_and_refusal(O):
     lat.destroy()
 
 
+def test_rebuild_grows_every_table(O):
+    """Rebuilds of one handle across a lattice of few buckets and one where
+    every point has its own bucket and vertices: the bucket table (sized from
+    the last build's buckets), the vertex table, and the buffers of vertex
+    keys and neighbours (sized from the last build's vertices, whose
+    overflow the device finds) all grow, then serve the small lattice again."""
+    import torch
+
+    import paper_1907_00641_amd as P
+
+    log("[edge] every table grows on a rebuild")
+    d, n = 4, 2500
+    rng = np.random.default_rng(42)
+    small = rng.uniform(0.0, 1.5, size=(n, d)).astype(np.float32)
+    wide = rng.uniform(0.0, 1.0, size=(n, d))
+    wide[:, 0] += 25.0 * np.arange(n)
+    wide = wide.astype(np.float32)
+    v = rng.standard_normal((n, 8)).astype(np.float32)
+    g = rng.standard_normal((n, 8)).astype(np.float32)
+    vt, gt = torch.from_numpy(v).cuda(), torch.from_numpy(g).cuda()
+    lat = None
+    for f in (small, small, wide, small):
+        olat = O.lattice(f)
+        lat = P.pam_lattice_build(torch.from_numpy(f).cuda(), lat=lat)
+        out = P.pam_filter_fwd(lat, vt)
+        dv, df = P.pam_filter_bwd(lat, vt, gt)
+        keys, vert, bary, nbr = P.pam_lattice_export(lat)
+        M, _ = P.pam_lattice_stats(lat)
+        assert_lattice_equal({"M": M, "keys": keys, "vert": vert, "nbr": nbr}, olat)
+        assert_bary_close({"bary": bary}, olat)
+        check_filter({"out": out.cpu().numpy(), "dv": dv.cpu().numpy(), "df": df.cpu().numpy()},
+                     O, olat, v, g, 0)
+    lat.destroy()
+
+
 def test_large_table_small_lattice(O):
     """A 2^21-slot table under a lattice of a few thousand vertices: the
     compaction of tables from 2^20 slots (16 slots per thread, most blocks
