@@ -621,7 +621,7 @@ static pam_status_t build_impl(const float *feat, int64_t n, int32_t d, const in
         h->cap = next_pow2(std::max<int64_t>(h->cap_request, 64));
         h->cap_request = 0;
     } else if (h->prev_M >= 0) {
-        h->cap = next_pow2(std::max<int64_t>(4 * h->prev_M, 1024));
+        h->cap = next_pow2(std::max<int64_t>(3 * h->prev_M, 1024));
     } else {
         int64_t guess = std::min<int64_t>(std::max<int64_t>(n * (d + 1) / 4, 1024), (int64_t)1 << 24);
         h->cap = next_pow2((uint64_t)guess);

@@ -624,21 +624,31 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const int2 *__restrict__ pla
 // LDS hash of a tile: 2048 slots while a tile has at most 3072
 // contributions (d <= 5 at 512 points), else 4096.
 __host__ __device__ constexpr int tile_hash_bits(int d) { return tile_points(d) * (d + 1) <= 3072 ? 11 : 12; }
-constexpr int kTileProbe = 64;
+constexpr int kTileProbe = 512;
 
-// Per tile of the sorted order (one thread per point): the point's simplex,
-// barycentric weights and vertex keys from its features; the record of
-// weights and ranks the filter kernels read; the tile's distinct vertex
-// keys become dense rows (LDS hash, 64-bit compare-and-swap) and are
-// inserted into the vertex hash table, their slots kept in the tile record
-// for the resolve; the tile's (point, vertex) contributions are
-// counting-sorted by (window, row) (integer LDS atomics give each its
-// position within its pair); each pair's contributions are cut into
-// segments of at most kSegLen, and the segments are counting-sorted window
-// by window and by length, longest first, the order in which the splat
-// hands them out.  Sorted points share vertices in long runs: only the
-// first lane of a run of equal keys in a wave probes the LDS table and
-// later counts the whole run, the others take its results.
+// Per tile of the sorted order (one thread per point): the point's simplex
+// and barycentric weights from its features; the record of weights and ranks
+// the filter kernels read; the tile's distinct vertices become dense rows
+// (LDS hash) whose keys are inserted into the vertex hash table, their slots
+// kept in the tile record for the resolve; the tile's (point, vertex)
+// contributions are counting-sorted by (window, row) (integer LDS atomics
+// give each its position within its pair); each pair's contributions are cut
+// into segments of at most kSegLen, and the segments are counting-sorted
+// window by window and by length, longest first, the order in which the
+// splat hands them out.
+//
+// A point's vertices are told apart within the tile by the bucket the point
+// belongs to (its vertex 0; a bucket's points are consecutive) and the set of
+// coordinates that vertex k has stepped down: a local key of 32 bits, where
+// the packed keys take 64 and a shift per coordinate.  Only the distinct
+// local keys are turned into packed keys (a vertex that two buckets share
+// becomes two rows with one id; buckets are in the order of a hash, so that
+// is rare).  The launch is bound by its vector instructions: with 64-bit keys
+// it took 1090 per wave and 94 us at 128^3, d = 5.
+//
+// Sorted points share vertices in runs: only the first lane of a run of
+// equal keys in a wave probes the LDS table and later counts the whole run,
+// the others take its results.
 template <int D>
 __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__restrict__ feat, int64_t n, Elev E,
                                                                  Groups64 grp, Ctl *ctl,
@@ -646,31 +656,42 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
                                                                  uint8_t *__restrict__ psort, uint64_t *tkeys,
                                                                  uint64_t mask, uint8_t *__restrict__ tiles)
 {
-    constexpr int T = tile_points(D);
+    constexpr int T = tile_points(D), NW = T / 64;
     constexpr int NC = T * (D + 1);
     constexpr int PW = point_bytes(D) / 4;
     static_assert(NC < (1 << 13), "segment start and row must fit their 13-bit fields");
     constexpr int kTileHashBits = tile_hash_bits(D);
     constexpr int kTileHash = 1 << kTileHashBits;
-    __shared__ uint64_t hkey[kTileHash];
-    __shared__ int16_t hrow[kTileHash];
     constexpr int kWin = splat_windows(D);  // point windows per tile
     constexpr int kWinPts = T / kWin;
     static_assert(kWin == 1 || kWinPts >= 64, "a wave must not span two windows");
-    // the distinct keys in row order, dead once they are inserted; then per
-    // (window, row): count, then first entry (cnt), and segment count, then
-    // first segment (nsg)
-    __shared__ uint64_t rkey[kTileHash + 1];
-    int *cnt = reinterpret_cast<int *>(rkey), *nsg = cnt + kTileHash + 1;
+    // two uses of one piece of LDS: the hash (local keys, their rows) and the
+    // buckets' keys, until every contribution has its row; then the weights
+    // and the sorted entries, on their way to coalesced stores
+    constexpr int kHashBytes = kTileHash * 4 + kTileHash * 2 + T * 8;
+    constexpr int kEntryBytes = NC * 4 + NC * 2;
+    __shared__ __attribute__((aligned(16))) uint8_t pool[kHashBytes > kEntryBytes ? kHashBytes : kEntryBytes];
+    uint64_t *bkey = reinterpret_cast<uint64_t *>(pool);
+    uint32_t *hkey = reinterpret_cast<uint32_t *>(pool + T * 8);
+    uint16_t *hrow = reinterpret_cast<uint16_t *>(pool + T * 8 + kTileHash * 4);
+    float *sw = reinterpret_cast<float *>(pool);
+    uint16_t *slist = reinterpret_cast<uint16_t *>(pool + NC * 4);
+    // per (window, row): count, then first entry (cnt), and segment count,
+    // then first segment (nsg); before that the local keys in row order
+    __shared__ int cnt[kTileHash + 1];
+    __shared__ int nsg[kTileHash + 1];
+    uint32_t *rkey = reinterpret_cast<uint32_t *>(cnt);
     __shared__ int hist[kWin * (kSegLen + 1)];
     __shared__ int wsum[2 * (T / 64 + 1)];
+    __shared__ uint64_t last_s[NW];
+    __shared__ int starts_s[NW];
     __shared__ int nrows_s, overflow_s, full_s;
     __shared__ uint32_t added_s;
     if (ctl->flags & ~kFlagTableFull)  // set by other blocks of this launch: TableFull only
         return;
     const KeyLayout lay = ctl->lay;
     const TileRec rec(D);
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int64_t base = (int64_t)blockIdx.x * T;
     const int nt = (int)min((int64_t)T, n - base);
     const int nc = nt * (D + 1);
@@ -681,13 +702,13 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     uint16_t *sfirst = reinterpret_cast<uint16_t *>(R + rec.sfirst);
     uint32_t *seg = reinterpret_cast<uint32_t *>(R + rec.seg);
     uint16_t *order = reinterpret_cast<uint16_t *>(R + rec.order);
-    uint16_t *list = reinterpret_cast<uint16_t *>(R + rec.list);
     uint16_t *lrow = reinterpret_cast<uint16_t *>(R + rec.lrow);
-    uint16_t *pent = reinterpret_cast<uint16_t *>(R + rec.pent);
+    uint32_t *wseg = reinterpret_cast<uint32_t *>(R + rec.wseg);
+    int2 *entry = reinterpret_cast<int2 *>(R + rec.entry);
     const bool valid = t < nt;
     const int64_t i = valid ? perm[base + t] : 0;
     for (int e = t; e < kTileHash; e += T)
-        hkey[e] = kEmptyKey;
+        hkey[e] = ~0u;
     for (int e = t; e < kWin * (kSegLen + 1); e += T)
         hist[e] = 0;
     if (t == 0) {
@@ -697,11 +718,11 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
         added_s = 0;
     }
     Simplex<D> s;
-    uint64_t gfield = 0;
+    float b[D + 1];
+    uint64_t key0 = kEmptyKey;
     if (valid) {
         embed<D>(feat + i * D, E, s);
-        gfield = group_field(grp, lay, i);
-        float b[D + 1];
+        key0 = pack_vertex<D>(s, 0, lay, group_field(grp, lay, i));
         barycentric<D>(s, feat + i * D, E, b);
         uint32_t w[PW];
 #pragma unroll
@@ -718,30 +739,64 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
         for (int u = 0; u < PW / 4; ++u)
             prec[u] = make_uint4(w[4 * u], w[4 * u + 1], w[4 * u + 2], w[4 * u + 3]);
     }
+    // the point's bucket within the tile: how many of the tile's points up to
+    // it have another vertex 0 than the point before them
+    if (lane == 63)
+        last_s[wave] = key0;
     __syncthreads();
+    const uint32_t plo = __shfl_up((uint32_t)key0, 1), phi = __shfl_up((uint32_t)(key0 >> 32), 1);
+    const uint64_t prev = lane > 0 ? ((uint64_t)phi << 32) | plo : (wave > 0 ? last_s[wave - 1] : kEmptyKey);
+    const bool first = valid && key0 != prev;  // the tile's first point has no point before it
+    const uint64_t firsts = __ballot(first);
+    if (lane == 0)
+        starts_s[wave] = __popcll(firsts);
+    __syncthreads();
+    int bl = __popcll(firsts & (lane == 63 ? ~0ull : ((2ull << lane) - 1))) - 1;
+    for (int w = 0; w < wave; ++w)
+        bl += starts_s[w];
+    if (first)
+        bkey[bl] = key0;
+    // the coordinate of each rank, 4 bits each (d = 16: 5)
+    constexpr int CB = D < 16 ? 4 : 5;
+    uint64_t by_rank[2] = {0, 0};  // ranks 0 .. 11 and 12 .. 16
+    if (valid) {
+#pragma unroll
+        for (int c = 0; c <= D; ++c) {
+            if constexpr (D < 12) {
+                by_rank[0] |= (uint64_t)c << (CB * s.rank[c]);
+            } else {
+                const bool high = s.rank[c] >= 12;
+                const uint64_t v = (uint64_t)c << (CB * (high ? s.rank[c] - 12 : s.rank[c]));
+                by_rank[0] |= high ? 0 : v;
+                by_rank[1] |= high ? v : 0;
+            }
+        }
+    }
     // The loops over k are wave-uniform (cross-lane operations).
-    const int lane = t & 63;
     int slot[D + 1];
     LaneRun run[D + 1];
-    uint64_t key = 0;
+    uint32_t lkey = (uint32_t)bl << (D + 1);  // vertex k steps down the coordinates of rank > d - k
 #pragma unroll
     for (int k = 0; k <= D; ++k) {
-        key = valid ? pack_vertex<D>(s, k, lay, gfield) : kEmptyKey;
-        run[k] = lane_run(key, valid);
+        if (k > 0) {
+            const int r = D + 1 - k;  // 1 .. D
+            const uint32_t c = (uint32_t)(by_rank[r >= 12] >> (CB * (r >= 12 ? r - 12 : r))) & ((1u << CB) - 1);
+            lkey |= 1u << c;
+        }
+        run[k] = lane_run32(lkey, valid);
         int found = -1;
         if (valid && run[k].lead == lane) {
-            uint32_t h = (uint32_t)(mix64(key) >> (64 - kTileHashBits));
+            uint32_t h = (lkey * 2654435761u) >> (32 - kTileHashBits);
             for (int probe = 0; probe < kTileProbe; ++probe) {
-                const uint64_t prev = atomicCAS((unsigned long long *)&hkey[h], (unsigned long long)kEmptyKey,
-                                                (unsigned long long)key);
-                if (prev == kEmptyKey) {
+                const uint32_t was = atomicCAS(&hkey[h], ~0u, lkey);
+                if (was == ~0u) {
                     const int r = atomicAdd(&nrows_s, 1);
-                    hrow[h] = r;
-                    rkey[r] = key;
+                    hrow[h] = (uint16_t)r;
+                    rkey[r] = lkey;
                     found = (int)h;
                     break;
                 }
-                if (prev == key) {
+                if (was == lkey) {
                     found = (int)h;
                     break;
                 }
@@ -768,6 +823,7 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
         // no room to deduplicate: every key of the tile goes to the table,
         // and the resolve looks the points' ids up one by one
         if (valid) {
+            const uint64_t gfield = group_field(grp, lay, i);
 #pragma unroll
             for (int k = 0; k <= D; ++k)
                 table_insert(tkeys, mask, pack_vertex<D>(s, k, lay, gfield), added, full);
@@ -776,7 +832,13 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
         // each distinct key's slot, for the resolve; -1 when it does not fit
         // an int32 (the resolve then looks the key up)
         for (int r = t; r < nrows; r += T) {
-            const uint64_t kr = rkey[r];
+            const uint32_t lk = rkey[r];
+            // vertex k: the bucket's vertex 0 plus k, minus 1 in the field of
+            // every stepped-down coordinate (coordinate d has no field)
+            uint64_t kr = bkey[lk >> (D + 1)] + (uint32_t)__popc(lk & ((2u << D) - 1));
+#pragma unroll
+            for (int c = 0; c < D; ++c)
+                kr -= (uint64_t)((lk >> c) & 1) << lay.shift[c];
             const uint64_t h = table_insert(tkeys, mask, kr, added, full);
             rowkey[r] = kr;
             rowid[r] = h <= 0x7fffffffull ? (int32_t)h : -1;
@@ -816,29 +878,39 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     int q[D + 1], pos[D + 1];
 #pragma unroll
     for (int k = 0; k <= D; ++k) {
-        const int row = valid ? hrow[slot[k]] : 0;
-        q[k] = win * nrows + row;
-        int b = 0;
+        q[k] = win * nrows + (valid ? (int)hrow[slot[k]] : 0);
+        int first_pos = 0;
         if (valid && run[k].lead == lane)
-            b = atomicAdd(&cnt[q[k]], run[k].len);
-        pos[k] = __shfl(b, run[k].lead) + (lane - run[k].lead);
-        if (valid)
-            lrow[t * (D + 1) + k] = (uint16_t)row;
+            first_pos = atomicAdd(&cnt[q[k]], run[k].len);
+        pos[k] = __shfl(first_pos, run[k].lead) + (lane - run[k].lead);
     }
-    __syncthreads();
+    if (valid) {
+        if constexpr ((D + 1) % 2 == 0) {
+            uint32_t *lr = reinterpret_cast<uint32_t *>(lrow + t * (D + 1));
+#pragma unroll
+            for (int k = 0; k <= D; k += 2)
+                lr[k / 2] = (uint32_t)(q[k] - win * nrows) | ((uint32_t)(q[k + 1] - win * nrows) << 16);
+        } else {
+#pragma unroll
+            for (int k = 0; k <= D; ++k)
+                lrow[t * (D + 1) + k] = (uint16_t)(q[k] - win * nrows);
+        }
+    }
+    __syncthreads();  // hkey, hrow and bkey are dead from here: their LDS takes the entries
     // cnt[q]: first entry of pair q; nsg[q]: its first segment
     const int nseg = block_exclusive_scan_ceil(cnt, nsg, nq, kSegLen, wsum);
-    if (t < nt) {
+    if (valid) {
 #pragma unroll
-        for (int k = 0; k <= D; ++k)
-            list[cnt[q[k]] + pos[k]] = (uint16_t)((t << 5) | k);
+        for (int k = 0; k <= D; ++k) {
+            sw[t * (D + 1) + k] = b[k];
+            slist[cnt[q[k]] + pos[k]] = (uint16_t)((t << 5) | k);
+        }
     }
     // segments in (window, row) order, and a histogram of (window, length)
     for (int qq = t; qq < nq; qq += T) {
         const int e0 = cnt[qq], e1 = (qq + 1 < nq) ? cnt[qq + 1] : nc;
         const int w = qq / nrows, r = qq - w * nrows;
         sfirst[qq] = (uint16_t)nsg[qq];
-        pent[qq] = (uint16_t)e0;
         for (int j = 0, e = e0; e < e1; ++j, e += kSegLen) {
             const int len = min(kSegLen, e1 - e);
             seg[nsg[qq] + j] = seg_encode(e, len, r);
@@ -846,6 +918,10 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
         }
     }
     __syncthreads();
+    for (int e = t; e < nc; e += T) {
+        const int pk = slist[e];
+        entry[e] = make_int2(__float_as_int(sw[(pk >> 5) * (D + 1) + (pk & 31)]), pk);
+    }
     if (t < 64) {
         // bucket starts (then used as cursors): an exclusive scan of the
         // histogram by the first wave, each lane over NBL consecutive buckets
@@ -875,7 +951,6 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     }
     if (t == 0) {
         sfirst[nq] = (uint16_t)nseg;
-        pent[nq] = (uint16_t)nc;
         hdr[0] = (uint32_t)nrows;
         hdr[1] = (uint32_t)nwin << 8;
         hdr[2] = (uint32_t)nc;
@@ -885,10 +960,12 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     // work order: windows in turn, longest segments first within a window
     for (int qq = t; qq < nq; qq += T) {
         const int e0 = cnt[qq], e1 = (qq + 1 < nq) ? cnt[qq + 1] : nc;
-        const int w = qq / nrows;
+        const int w = qq / nrows, r = qq - w * nrows;
         for (int j = 0, e = e0; e < e1; ++j, e += kSegLen) {
             const int len = min(kSegLen, e1 - e);
-            order[atomicAdd(&hist[w * (kSegLen + 1) + kSegLen - len], 1)] = (uint16_t)(nsg[qq] + j);
+            const int at = atomicAdd(&hist[w * (kSegLen + 1) + kSegLen - len], 1);
+            order[at] = (uint16_t)(nsg[qq] + j);
+            wseg[at] = seg_encode(e, len, r);
         }
     }
 }

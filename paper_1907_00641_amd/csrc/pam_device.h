@@ -273,12 +273,12 @@ __host__ __device__ constexpr int tile_points(int d)
 //   order  : nseg segment indices (uint16), the work order: window by
 //            window, longest first within a window (window 0's are the first
 //            sfirst[nrows])
-//   list   : nc entries (p << 5) | k sorted by (window, row): point p of the
-//            tile contributes with its vertex k to that row (uint16); window
-//            w's entries are contiguous
+//   wseg   : the segments in that order
+//   entry  : nc entries sorted by (window, row): point p of the tile
+//            contributes to that row with its vertex k, as a pair of the
+//            barycentric weight's bits and (p << 5) | k; window w's entries
+//            are contiguous
 //   lrow   : nc rows, point-major: lrow[p * (d+1) + k] (uint16)
-//   pent   : nwin * nrows + 1 first entry of each (window, row) pair in
-//            list (uint16), window-major like sfirst
 // Fixed-size records; offsets in bytes.
 constexpr int kSegLen = 64;  // at most 64: the length field has 6 bits
 
@@ -305,7 +305,7 @@ __host__ __device__ constexpr int splat_windows(int d)
 
 struct TileRec {
     int d, T, NC;
-    size_t rowid, rowkey, sfirst, seg, order, list, lrow, pent, bytes;
+    size_t rowid, rowkey, sfirst, seg, order, lrow, wseg, entry, bytes;
     __host__ __device__ explicit TileRec(int d_) : d(d_)
     {
         T = tile_points(d_);
@@ -315,10 +315,10 @@ struct TileRec {
         sfirst = rowkey + (size_t)NC * 8;
         seg = sfirst + (((size_t)(NC + 1) * 2 + 15) & ~(size_t)15);
         order = seg + (size_t)NC * 4;
-        list = order + (((size_t)NC * 2 + 15) & ~(size_t)15);
-        lrow = list + (((size_t)NC * 2 + 15) & ~(size_t)15);
-        pent = lrow + (((size_t)NC * 2 + 15) & ~(size_t)15);
-        bytes = (pent + (size_t)(NC + 1) * 2 + 255) & ~(size_t)255;
+        lrow = order + (((size_t)NC * 2 + 15) & ~(size_t)15);
+        wseg = lrow + (((size_t)NC * 2 + 15) & ~(size_t)15);
+        entry = wseg + (size_t)NC * 4;
+        bytes = (entry + (size_t)NC * 8 + 255) & ~(size_t)255;
     }
 };
 
@@ -343,6 +343,22 @@ __device__ __forceinline__ LaneRun lane_run(uint64_t key, bool valid)
     const uint32_t lo = (uint32_t)key, hi = (uint32_t)(key >> 32);
     const uint32_t plo = __shfl_up(lo, 1), phi = __shfl_up(hi, 1);
     const bool start = valid && (lane == 0 || plo != lo || phi != hi);
+    const uint64_t starts = __ballot(start);
+    const uint64_t nvalid = __popcll(__ballot(valid));
+    const uint64_t upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);  // lanes 0..lane
+    const uint64_t below = starts & upto, above = starts & ~upto;
+    LaneRun r;
+    r.lead = below ? 63 - __clzll(below) : lane;
+    r.len = (above ? __ffsll((unsigned long long)above) - 1 : (int)nvalid) - r.lead;
+    return r;
+}
+
+// The same for 32-bit keys.
+__device__ __forceinline__ LaneRun lane_run32(uint32_t key, bool valid)
+{
+    const int lane = threadIdx.x & 63;
+    const uint32_t before = __shfl_up(key, 1);
+    const bool start = valid && (lane == 0 || before != key);
     const uint64_t starts = __ballot(start);
     const uint64_t nvalid = __popcll(__ballot(valid));
     const uint64_t upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);  // lanes 0..lane

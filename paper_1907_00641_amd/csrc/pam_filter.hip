@@ -24,11 +24,13 @@
 // 3 cycles per lane, so no kernel accumulates with them.
 #include "pam_device.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace pam {
 
 constexpr int kCH = 32;          // channels per pass over a tile
+constexpr unsigned kCus = 256;   // compute units of the chip
 
 // compile-time flag for specialising a loop on a block-uniform condition
 template <bool V>
@@ -59,7 +61,7 @@ constexpr int kDppXor2 = 0x4e;        // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141; // lane i <- 7 - i within each 8 lanes
 constexpr int kDppMirror = 0x140;     // lane i <- 15 - i within each 16 lanes
 constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
-constexpr int kDppShl1 = 0x101;
+constexpr int kDppShl1 = 0x101, kDppShl2 = 0x102, kDppShl4 = 0x104;
 
 // Orders the LDS accesses of one wave before and after it (lanes of a wave
 // exchanging data through LDS).
@@ -177,6 +179,15 @@ __device__ __forceinline__ int wave_max(int v)
     for (int off = 32; off > 0; off >>= 1)
         v = max(v, __shfl_xor(v, off));
     return v;
+}
+
+// Four floats as one 128-bit LDS access (member-wise float4 reads of an
+// address the compiler cannot prove aligned become two 64-bit halves or four
+// 32-bit reads).
+typedef float f4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f4 lds_f4(const float *p)
+{
+    return *reinterpret_cast<const f4 *>(__builtin_assume_aligned(p, 16));
 }
 
 template <int VEC>
@@ -330,25 +341,25 @@ struct TileView {
     const uint16_t *sfirst;
     const uint32_t *seg;
     const uint16_t *order;
-    const uint16_t *list;
     const uint16_t *lrow;
-    const uint16_t *pent;
+    const uint32_t *wseg;
+    const int2 *entry;
 };
 
 template <int D>
-__device__ __forceinline__ TileView tile_view(const uint8_t *tiles)
+__device__ __forceinline__ TileView tile_view(const uint8_t *tiles, int64_t tile)
 {
     const TileRec rec(D);
-    const uint8_t *R = tiles + (size_t)blockIdx.x * rec.bytes;
+    const uint8_t *R = tiles + (size_t)tile * rec.bytes;
     TileView v;
     v.hdr = reinterpret_cast<const uint32_t *>(R);
     v.rowid = reinterpret_cast<const int32_t *>(R + rec.rowid);
     v.sfirst = reinterpret_cast<const uint16_t *>(R + rec.sfirst);
     v.seg = reinterpret_cast<const uint32_t *>(R + rec.seg);
     v.order = reinterpret_cast<const uint16_t *>(R + rec.order);
-    v.list = reinterpret_cast<const uint16_t *>(R + rec.list);
     v.lrow = reinterpret_cast<const uint16_t *>(R + rec.lrow);
-    v.pent = reinterpret_cast<const uint16_t *>(R + rec.pent);
+    v.wseg = reinterpret_cast<const uint32_t *>(R + rec.wseg);
+    v.entry = reinterpret_cast<const int2 *>(R + rec.entry);
     return v;
 }
 
@@ -392,6 +403,254 @@ __device__ __forceinline__ void splat_direct(const FilterArgs &a, int64_t base, 
             if (weights)
                 atomic_add_f32(&row[C], b * (wcol ? wcol[p] : 1.0f));
         }
+    }
+}
+
+// The same straight from the points' records, for plain rows.
+template <int D>
+__device__ __forceinline__ void splat_points(const FilterArgs &a, int64_t base, int nt, const float *__restrict__ x,
+                                             bool weights, float *__restrict__ L)
+{
+    const int C = a.c, ld = a.ld;
+    for (int p = threadIdx.x; p < nt; p += blockDim.x) {
+        const int r = side_row(a, a.perm[base + p], a.side);
+        if (r < 0)
+            continue;
+        const float *b = reinterpret_cast<const float *>(a.pts + (base + p) * point_bytes(D));
+        const float *xr = x + (int64_t)r * C;
+        for (int k = 0; k <= D; ++k) {
+            float *row = L + (int64_t)a.svert[(base + p) * (D + 1) + k] * ld;
+            for (int c = 0; c < C; ++c)
+                atomic_add_f32(&row[c], b[k] * xr[c]);
+            if (weights)
+                atomic_add_f32(&row[C], b[k]);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Splat of plain rows: L[m] += sum over the tile's points of b_k x
+// (forward, and the raw backward splat of dL/dv').
+//
+// One block per sorted tile and pass of SCH channels.  The pass's channels
+// of every point's row of x are copied to LDS once (rows are read from HBM
+// once, not gathered d+1 times through the caches); the tile's segments
+// (runs of contributions to one lattice row, longest first) are handed to
+// groups of GS lanes, 4 channels per lane; with 8 channels, four shares of
+// the segment's entries, added at its end (one share: 32^3 points, d = 3, 8.0
+// us per launch; four: 5.1; with 16 channels two shares were no faster).
+// The lanes of a quad
+// (of a pair with 8 channels) load BL consecutive entries (weight and point)
+// straight from the tile record, the next batch while the current one is
+// summed, and broadcast them with DPP moves, so that entries take no LDS.  A
+// segment's sum goes to the lattice through a per-wave LDS transpose, so
+// that each atomic instruction covers whole rows.
+//
+// LDS (64 KB of rows for 512 points and 32 channels, 16 KB of transpose
+// scratch) leaves two blocks of 1024 threads per CU: one loads its rows
+// while the other sums.  Bound by the latency of its chain (record and row
+// numbers, rows of x, sums, flush) over two blocks per CU: 128^3 points,
+// d = 5, 32 channels 133 us per launch (150 us gathering the rows through
+// the caches), of which 121 remain without the sums and 92 without the rows.
+// A persistent variant with the next item's loads under way (spilled, 342
+// us), 512 threads (194 us) and windows of 256 points (142 us) were slower.
+// ---------------------------------------------------------------------------
+
+#ifndef PAM_SPLAT_THREADS
+#define PAM_SPLAT_THREADS 1024
+#endif
+template <int D, int SCH>
+__host__ __device__ constexpr int splat_rows_threads()
+{
+    // as many threads as the LDS rows leave room for: blocks of 1024 from
+    // 64 KB of rows, 512 from 16 KB, else 256
+    return tile_points(D) * SCH >= 16384 ? PAM_SPLAT_THREADS : (tile_points(D) * SCH >= 4096 ? 512 : 256);
+}
+
+// The 16-byte pieces of a point's row of x in LDS are permuted (piece l at l
+// xor this), so that groups reading the same piece of different rows spread
+// over the banks.
+template <int GL>
+__device__ __forceinline__ int xs_swizzle(int p)
+{
+    return (p / (8 / GL)) & (GL - 1);
+}
+
+// lane j of each aligned group of BL (2 or 4) lanes, to the whole group
+template <int BL, int J>
+__device__ __forceinline__ int quad_bcast(int x)
+{
+    constexpr int ctrl = BL == 4 ? J * 0x55 : (J | (J << 2) | ((2 + J) << 4) | ((2 + J) << 6));
+    return __builtin_amdgcn_update_dpp(0, x, ctrl, 0xf, 0xf, false);
+}
+
+template <int D, int VEC, int SCH, bool W>
+__global__ __launch_bounds__((splat_rows_threads<D, SCH>())) void k_splat_rows(FilterArgs a,
+                                                                               const uint8_t *__restrict__ tiles,
+                                                                               const float *__restrict__ x,
+                                                                               float *__restrict__ L)
+{
+    constexpr int T = tile_points(D);
+    static_assert(splat_windows(D) == 1, "segments longest first over the whole tile");
+    constexpr int NT = splat_rows_threads<D, SCH>(), NW = NT / 64;
+    constexpr int GL = SCH / 4, S = SCH == 8 ? 4 : 1;  // lanes per share, shares per segment
+    constexpr int GS = GL * S, GPW = 64 / GS;          // lanes per segment, segments per wave
+    constexpr int BL = GL < 4 ? GL : 4;                // lanes that load entries together
+    constexpr int K = 4, SB = S * BL, EB = K * SB;     // entries per lane, per step and per batch
+    __shared__ __attribute__((aligned(16))) float xs[T * SCH];
+    __shared__ __attribute__((aligned(16))) float scratch[NW * GPW * SCH];
+    const TileView tv = tile_view<D>(tiles, blockIdx.x);
+    const int t = threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * T;
+    const int nt = (int)min((int64_t)T, a.n - base);
+    const int C = a.c, ld = a.ld;
+    const int cc = (int)blockIdx.y * SCH;
+    const int chc = min(SCH, C - cc);
+    const int lane = t & 63, l = lane & (GL - 1), share = lane % GS / GL, gw = lane / GS, wave = t >> 6;
+    // Requested together, none waiting for another: the points' rows, the
+    // tile's header, and this group's first segment (the record has room for
+    // more segments than groups; past nseg it is not used).
+    constexpr int XL = VEC == 4 ? GL : SCH;  // lanes per row of x
+    constexpr int RPI = NT / XL < T ? NT / XL : T, NI = T / RPI;
+    const int xl = t % XL, xp = t / XL;
+    int pr[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int p = xp + i * RPI;
+        pr[i] = a.perm[base + min(p, nt - 1)];
+    }
+    const int first = ((int)blockIdx.z * NW + wave) * GPW, step = (int)gridDim.z * NW * GPW;
+    constexpr int kLast = T * (D + 1) - 1;  // the record's last segment place
+    uint32_t sd = tv.wseg[min(first + gw, kLast)], sdn = tv.wseg[min(first + step + gw, kLast)];
+    const int nseg = (int)tv.hdr[3];
+    if (tv.hdr[1] & kTileOverflow) {  // block-uniform
+        if (blockIdx.y == 0 && blockIdx.z == 0)
+            splat_points<D>(a, base, nt, x, W, L);
+        return;
+    }
+    Vec<VEC> xv[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int p = xp + i * RPI;
+        pr[i] = p < nt && xp < RPI ? side_row(a, pr[i], a.side) : -1;
+        xv[i] = load_vec<VEC>(x + (int64_t)max(pr[i], 0) * C + cc + xl * VEC, pr[i] >= 0 && xl * VEC < chc);
+    }
+    int e0 = 0, e1 = 0, row = -1, len = 0;
+    float wb[K];
+    int pb[K];
+    // segment number w, encoded in sd: entries and lattice row; none from
+    // nseg on
+    auto segment = [&](int w) {
+        int r = 0;
+        seg_decode(sd, e0, e1, r);
+        if (w >= nseg)
+            e0 = e1 = r = 0;
+        row = tv.rowid[r];
+        if (w >= nseg)
+            row = -1;
+        len = __builtin_amdgcn_readfirstlane(e1 - e0);  // the wave's longest: segments come longest first
+    };
+    // entries e0 + u .. of a batch: weights (0 past the end, where the last
+    // entry's point is read again) and LDS offsets of the points' rows
+    auto load = [&](int u, float(&w)[K], int(&p)[K]) {
+        int2 en[K];
+        int e[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            e[i] = e0 + u + i * SB + share * BL + (l & (BL - 1));
+            en[i] = tv.entry[max(min(e[i], e1 - 1), 0)];
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            w[i] = e[i] < e1 ? __int_as_float(en[i].x) : 0.0f;
+            const int pt = en[i].y >> 5;
+            p[i] = pt * SCH + xs_swizzle<GL>(pt) * 4;
+        }
+    };
+    segment(first + gw);
+    load(0, wb, pb);
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+        if (xp < RPI) {
+            const int p = xp + i * RPI;
+            store_vec<VEC>(xs + p * SCH + ((xl * VEC) ^ (xs_swizzle<GL>(p) * 4)), xv[i]);
+        }
+    __syncthreads();
+    for (int w0 = first; w0 < nseg; w0 += step) {  // wave-uniform
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        float accw = 0.0f;
+        for (int u = 0; u < len; u += EB) {
+            float wn[K];
+            int pn[K];
+            if (u + EB < len)
+                load(u + EB, wn, pn);
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                if (u + i * SB >= len)
+                    break;
+                auto entry = [&](auto jc) {
+                    constexpr int J = decltype(jc)::value;
+                    const float b = __int_as_float(quad_bcast<BL, J>(__float_as_int(wb[i])));
+                    const int off = quad_bcast<BL, J>(pb[i]);
+                    const f4 q = lds_f4(xs + (off ^ (l * 4)));
+                    acc.x += b * q.x;
+                    acc.y += b * q.y;
+                    acc.z += b * q.z;
+                    acc.w += b * q.w;
+                    if constexpr (W)
+                        accw += b;
+                };
+                entry(Int<0>{});
+                entry(Int<1>{});
+                if constexpr (BL == 4) {
+                    entry(Int<2>{});
+                    entry(Int<3>{});
+                }
+            }
+            if (u + EB < len) {
+#pragma unroll
+                for (int i = 0; i < K; ++i) {
+                    wb[i] = wn[i];
+                    pb[i] = pn[i];
+                }
+            }
+        }
+        if constexpr (S > 1) {  // the shares' sums, left in share 0
+            auto gather = [&](auto ctrl) {
+                constexpr int CTRL = decltype(ctrl)::value;
+                acc.x += dpp<CTRL>(acc.x);
+                acc.y += dpp<CTRL>(acc.y);
+                acc.z += dpp<CTRL>(acc.z);
+                acc.w += dpp<CTRL>(acc.w);
+                if constexpr (W)
+                    accw += dpp<CTRL>(accw);
+            };
+            gather(Int<kDppShl4>{});
+            gather(Int<kDppShl2>{});
+        }
+        const int frow = row;
+        const int w1 = w0 + step;
+        if (w1 < nseg) {  // the next segment's entries travel during the flush
+            sd = sdn;
+            sdn = tv.wseg[min(w1 + step + gw, kLast)];
+            segment(w1 + gw);
+            load(0, wb, pb);
+        }
+        if (W && blockIdx.y == 0 && lane % GS == 0 && frow >= 0)
+            atomic_add_f32(&L[(int64_t)frow * ld + C], accw);
+        float *wf = scratch + wave * GPW * SCH;
+        if (share == 0)
+            *reinterpret_cast<float4 *>(wf + gw * SCH + l * 4) = acc;
+        wave_sync();
+        const int c = lane % SCH;
+#pragma unroll
+        for (int i = 0; i < GPW * SCH / 64; ++i) {
+            const int g2 = i * (64 / SCH) + lane / SCH;  // group whose channel c this lane adds
+            const int r2 = __shfl(frow, g2 * GS);
+            if (r2 >= 0 && c < chc)
+                atomic_add_f32(&L[(int64_t)r2 * ld + cc + c], wf[g2 * SCH + c]);
+        }
+        wave_sync();  // the scratch is read before the next segments overwrite it
     }
 }
 
@@ -544,7 +803,7 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
     // each row d+1 times from global memory.  A row then has about one
     // segment, so segment sums go straight to the lattice (no LDS slots),
     // and the segment tables stay in LDS up to kXsSegCap segments.
-    constexpr bool XS = (MODE == kSplatPlain || NORMB) && !HA && VEC == 4 && PAM_SPLAT_SPREAD == 1 && T == 256 &&
+    constexpr bool XS = NORMB && VEC == 4 && PAM_SPLAT_SPREAD == 1 && T == 256 &&
                         T * SCH * (int)sizeof(float) <= kSplatXsBytes;
     // AUG: a pass covers a chunk of SCH channels of x and every feature
     // coordinate at once (each row of x is gathered once per contribution,
@@ -603,7 +862,7 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
     __shared__ int next_s;
     __shared__ __attribute__((aligned(16))) int32_t rowid_s[DIRECT ? kXsSegCap : 4];  // DIRECT: lattice row of each tile row
 
-    const TileView tv = tile_view<D>(tiles);
+    const TileView tv = tile_view<D>(tiles, blockIdx.x);
     const int nrows = (int)tv.hdr[0], nc = (int)tv.hdr[2], nseg = (int)tv.hdr[3];
     const bool overflow = (tv.hdr[1] & kTileOverflow) != 0;
     const int nwin = (int)(tv.hdr[1] >> 8);
@@ -639,7 +898,7 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int e = t + j * T;
-        lst[j] = (!overflow && e < nc) ? (uint32_t)tv.list[e] : 0u;
+        lst[j] = (!overflow && e < nc) ? (uint32_t)tv.entry[e].y : 0u;
     }
     const bool tables = !overflow && in_lds;
     const int n0 = (nseg * 4 + 15) / 16, n1 = (nseg * 2 + 15) / 16, n2 = ((nwin * nrows + 1) * 2 + 15) / 16;
@@ -1232,12 +1491,15 @@ __device__ __forceinline__ void stage_slice_points(const FilterArgs &a, const Ti
     }
 }
 
-// Floats of LDS for the staged rows of `nrows` rows at pitch kRowPitch, or
-// for the global vertex ids of a tile that stages none.
-template <int D>
+// Floats of LDS for the staged rows of a slice with passes of CH channels:
+// `nrows` rows of 32 channels (as many more of narrower ones), or kWideRows
+// rows of 64; or for the global vertex ids of a tile that stages none.
+constexpr int kWideRows = 88;
+template <int D, int CH>
 __host__ __device__ constexpr int stage_floats(int nrows)
 {
-    return nrows * kRowPitch > tile_points(D) * (D + 1) ? nrows * kRowPitch : tile_points(D) * (D + 1);
+    const int f = CH == 64 ? kWideRows * (CH + 4) : nrows * kRowPitch;
+    return f > tile_points(D) * (D + 1) ? f : tile_points(D) * (D + 1);
 }
 
 // Staged rows of the slices, one pass of CH channels: pitch CH + 4 floats
@@ -1307,13 +1569,13 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice(FilterArgs a, const uint8_
                                                       const float *__restrict__ A, float *__restrict__ out)
 {
     constexpr int T = Tile<D>::T;
-    constexpr int kFloats = stage_floats<D>(kSliceRows);
+    constexpr int kFloats = stage_floats<D, CH>(kSliceRows);
     constexpr int RS = kFloats / (CH + 4);  // rows the LDS holds
     __shared__ float sb[T][D + 1];
     __shared__ uint16_t slr[T][D + 1];
     __shared__ int sperm[T];
     __shared__ __attribute__((aligned(16))) float rows[kFloats];
-    const TileView tv = tile_view<D>(tiles);
+    const TileView tv = tile_view<D>(tiles, blockIdx.x);
     const int nrows = (int)tv.hdr[0];
     const bool ovf = (tv.hdr[1] & kTileOverflow) != 0;
     const int C = a.c, ld = a.ld;
@@ -1443,7 +1705,7 @@ __global__ __launch_bounds__(slice_aug_threads(D)) void k_slice_aug(FilterArgs a
     static_assert(sizeof(float) * T * (D + 1) <= sizeof(float) * NC * NVC, "point staging fits the slots");
     float(*sb)[D + 1] = reinterpret_cast<float(*)[D + 1]>(res);
 
-    const TileView tv = tile_view<D>(tiles);
+    const TileView tv = tile_view<D>(tiles, blockIdx.x);
     const int nrows = (int)tv.hdr[0], nc = (int)tv.hdr[2], nseg = (int)tv.hdr[3];
     const bool overflow = (tv.hdr[1] & kTileOverflow) != 0;
     const bool in_lds = !overflow && nseg <= kTab;
@@ -1492,7 +1754,7 @@ __global__ __launch_bounds__(slice_aug_threads(D)) void k_slice_aug(FilterArgs a
     // decode every contribution once: its weight (0 for a point without a
     // row) and row; its slot is its entry
     for (int e = t; e < nc; e += NT) {
-        const int pk = tv.list[e];
+        const int pk = tv.entry[e].y;
         const int p = pk >> 5, k = pk & 31;
         const int r = sperm[p];
         rec[e] = make_int2(__float_as_int(r >= 0 ? sb[p][k] : 0.0f), max(r, 0));
@@ -1707,14 +1969,15 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice_bwd(FilterArgs a, const ui
 {
     static_assert(!(HAIN && NORM), "the splat's <g, A_k> is taken in raw mode");
     constexpr int T = Tile<D>::T;
-    constexpr int RB = kSliceBwdRows * kRowPitch / (CH + 4);  // rows the LDS holds, per lattice
+    constexpr int kFloats = CH == 64 ? kWideRows * (CH + 4) : kSliceBwdRows * kRowPitch;
+    constexpr int RB = kFloats / (CH + 4);  // rows the LDS holds, per lattice
     __shared__ float sb[T][D + 1];
     __shared__ uint16_t slr[T][D + 1];
     __shared__ signed char srank[T][D + 1];
     __shared__ int sperm[T];
-    __shared__ __attribute__((aligned(16))) float rowsT[stage_floats<D>(kSliceBwdRows)];
-    __shared__ __attribute__((aligned(16))) float rowsA[kSliceBwdRows * kRowPitch];
-    const TileView tv = tile_view<D>(tiles);
+    __shared__ __attribute__((aligned(16))) float rowsT[stage_floats<D, CH>(kSliceBwdRows)];
+    __shared__ __attribute__((aligned(16))) float rowsA[kFloats];
+    const TileView tv = tile_view<D>(tiles, blockIdx.x);
     const int nrows = (int)tv.hdr[0];
     const int C = a.c, ld = a.ld;
     // the tile's rows are staged (all C channels at once) when they fit
@@ -1946,25 +2209,39 @@ static inline int tile_threads(int d) { return tile_points(d); }
         CALL;                                                                                     \
     }
 
-// Pass width of the splat and the slices: value rows of at most 8 or 16
-// channels (float4 rows, d <= 8) take lane groups of 2 or 4 lanes instead of
-// 8, so that no lane of a group idles; everything else passes over 32
-// channels at a time.
-#define PAM_DISPATCH_SCH(D_, VEC_, c_, CALL)                                                      \
-    if constexpr ((D_) <= 8 && (VEC_) == 4) {                                                     \
+// Pass width of the slices, and of float4 splats that form more than plain
+// sums: value rows of at most 8 or 16 channels take narrower lane groups (2
+// or 4 lanes of float4, 8 or 16 lanes of scalar rows) instead of 32 channels'
+// worth, so that no lane of a group idles (75x53x41 points, d = 5, 7
+// channels: slice 19, backward slice 48 us with groups of 32 scalar lanes);
+// more channels, and float4 rows above d = 8, pass over 32 at a time.
+#define PAM_DISPATCH_SCH(D_, VEC_, c_, ...)                                                       \
+    if constexpr ((D_) <= 8) {                                                                    \
         if ((c_) <= 8) {                                                                          \
             constexpr int SCH = 8;                                                                \
-            CALL;                                                                                 \
+            __VA_ARGS__;                                                                          \
         } else if ((c_) <= 16) {                                                                  \
             constexpr int SCH = 16;                                                               \
-            CALL;                                                                                 \
+            __VA_ARGS__;                                                                          \
         } else {                                                                                  \
             constexpr int SCH = kSCH;                                                             \
-            CALL;                                                                                 \
+            __VA_ARGS__;                                                                          \
         }                                                                                         \
     } else {                                                                                      \
         constexpr int SCH = kSCH;                                                                 \
-        CALL;                                                                                     \
+        __VA_ARGS__;                                                                              \
+    }
+
+// The slices of float4 rows of more than 32 channels on tiles of few rows (d
+// <= 5) pass over 64 at a time: whole rows of up to 256 bytes are read and
+// written at once, and the backward slice can stage the tile's rows, which it
+// does when one pass takes all channels (`all`; else it keeps passes of 32).
+#define PAM_DISPATCH_SLICE(D_, VEC_, c_, all, ...)                                                \
+    if ((D_) <= 5 && (VEC_) == 4 && (c_) > 32 && (!(all) || (c_) <= 64)) {                        \
+        constexpr int SCH = (D_) <= 5 && (VEC_) == 4 ? 64 : kSCH;                                 \
+        __VA_ARGS__;                                                                              \
+    } else {                                                                                      \
+        PAM_DISPATCH_SCH(D_, VEC_, c_, __VA_ARGS__)                                               \
     }
 
 hipError_t launch_splat(int d, const FilterArgs &a, const uint8_t *tiles, const float *x, const float *A,
@@ -1986,8 +2263,30 @@ hipError_t launch_splat(int d, const FilterArgs &a, const uint8_t *tiles, const 
         PAM_DISPATCH_D(d, PAM_DISPATCH_SCH(D, VEC, a.c, hipLaunchKernelGGL((k_splat<D, VEC, kSplatPlain, SCH, true>),
                                                                          grid, block, 0, s, a, tiles, x, A, L, hA)));
     } else {
-        PAM_DISPATCH_D(d, PAM_DISPATCH_VEC(a, PAM_DISPATCH_SCH(D, VEC, a.c, hipLaunchKernelGGL((k_splat<D, VEC, kSplatPlain, SCH>),
-                                                                 grid, block, 0, s, a, tiles, x, A, L, hA))));
+        // passes of 8, 16 or 32 channels; x is staged in LDS whatever its
+        // alignment, so narrow passes serve scalar rows too
+        auto rows = [&](auto d_c, auto vec_c, auto sch_c) {
+            constexpr int D = decltype(d_c)::value, VEC = decltype(vec_c)::value, SCH = decltype(sch_c)::value;
+            // few tiles: their segments are dealt to several blocks each, up
+            // to two rounds of blocks on the chip (40x36x28 points, d = 12:
+            // 158 tiles of thousands of short segments, 280 us per launch
+            // with one block each)
+            const unsigned passes = (unsigned)((a.c + SCH - 1) / SCH);
+            const unsigned deal = std::max(1u, std::min(8u, 2 * kCus / (grid.x * passes)));
+            const dim3 g(grid.x, passes, deal), b(splat_rows_threads<D, SCH>());
+            if (a.normalize)
+                hipLaunchKernelGGL((k_splat_rows<D, VEC, SCH, true>), g, b, 0, s, a, tiles, x, L);
+            else
+                hipLaunchKernelGGL((k_splat_rows<D, VEC, SCH, false>), g, b, 0, s, a, tiles, x, L);
+        };
+        PAM_DISPATCH_D(d, PAM_DISPATCH_VEC(a, {
+                           if (a.c <= 8)
+                               rows(Int<D>{}, Int<VEC>{}, Int<8>{});
+                           else if (a.c <= 16)
+                               rows(Int<D>{}, Int<VEC>{}, Int<16>{});
+                           else
+                               rows(Int<D>{}, Int<VEC>{}, Int<32>{});
+                       }));
     }
     return hipGetLastError();
 }
@@ -2019,7 +2318,7 @@ hipError_t launch_slice(int d, const FilterArgs &a, const uint8_t *tiles, const 
 {
     if (a.n <= 0)
         return hipSuccess;
-    PAM_DISPATCH_D(d, PAM_DISPATCH_VEC(a, PAM_DISPATCH_SCH(D, VEC, a.c, hipLaunchKernelGGL((k_slice<D, VEC, SCH>),
+    PAM_DISPATCH_D(d, PAM_DISPATCH_VEC(a, PAM_DISPATCH_SLICE(D, VEC, a.c, false, hipLaunchKernelGGL((k_slice<D, VEC, SCH>),
                                                              dim3(tiles_for(d, a.n)), dim3(tile_threads(d)), 0, s, a,
                                                              tiles, A, out))));
     return hipGetLastError();
@@ -2057,7 +2356,7 @@ hipError_t launch_slice_bwd(int d, const FilterArgs &a, const uint8_t *tiles, co
                                                                      grad_val, grad_feat)));
         }
     } else if (a.normalize) {
-        PAM_DISPATCH_D(d, PAM_DISPATCH_VEC(a, PAM_DISPATCH_SCH(D, VEC, a.c, hipLaunchKernelGGL((k_slice_bwd<D, VEC, true, false, SCH, false>),
+        PAM_DISPATCH_D(d, PAM_DISPATCH_VEC(a, PAM_DISPATCH_SLICE(D, VEC, a.c, true, hipLaunchKernelGGL((k_slice_bwd<D, VEC, true, false, SCH, false>),
                                                                  grid, block, 0, s, a, tiles, val, grad, A, At, hA,
                                                                  grad_val, grad_feat))));
     } else if (hA) {
@@ -2065,7 +2364,7 @@ hipError_t launch_slice_bwd(int d, const FilterArgs &a, const uint8_t *tiles, co
                                                                  grid, block, 0, s, a, tiles, val, grad, A, At, hA,
                                                                  grad_val, grad_feat))));
     } else {
-        PAM_DISPATCH_D(d, PAM_DISPATCH_VEC(a, PAM_DISPATCH_SCH(D, VEC, a.c, hipLaunchKernelGGL((k_slice_bwd<D, VEC, false, false, SCH, false>),
+        PAM_DISPATCH_D(d, PAM_DISPATCH_VEC(a, PAM_DISPATCH_SLICE(D, VEC, a.c, true, hipLaunchKernelGGL((k_slice_bwd<D, VEC, false, false, SCH, false>),
                                                                  grid, block, 0, s, a, tiles, val, grad, A, At, hA,
                                                                  grad_val, grad_feat))));
     }

@@ -398,6 +398,24 @@ def test_narrow_channel_groups(O, d, C):
         check_filter(res, O, olat, v, g, flags)
 
 
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("d,C,n", [(2, 1, 511), (3, 8, 4099), (5, 5, 1025), (5, 13, 1537), (4, 17, 513), (7, 9, 769),
+                                   (8, 21, 257), (5, 36, 2050), (4, 64, 1023), (3, 68, 515), (12, 6, 700)])
+def test_pass_widths(O, d, C, n, flags):
+    """Splat passes of 8, 16 and 32 channels over float4 and scalar rows,
+    slice passes of 8 to 64, each with channels left over, on tiles that are
+    one point short, one over, and several; few tiles deal their segments to
+    several blocks.  At d = 12 a tile's vertices nearly fill its LDS table."""
+    rng = np.random.default_rng(150 + d + C)
+    f = rng.uniform(0.0, 3.0, size=(n, d)).astype(np.float32)
+    v = rng.standard_normal((n, C)).astype(np.float32)
+    g = rng.standard_normal((n, C)).astype(np.float32)
+    res = gpu_run(f, v, g, flags)
+    olat = O.lattice(f)
+    assert_lattice_equal(res, olat)
+    check_filter(res, O, olat, v, g, flags)
+
+
 @pytest.mark.parametrize("d", [1, 2, 7, 12, 16])
 def test_dimensions(O, d):
     log(f"[edge] d={d}")
