@@ -102,7 +102,7 @@ struct pam_lattice_s {
     uint32_t attempt = 0;               // number of the last build attempt
     BuildResult result{};               // its outcome
     // groups of buffers (ensure_group), each with its shared allocation
-    DevBuf table_own, tkeys, tids, bkeys, bcount;  // vertex table; bucket table (distinct vertex-0 keys): keys;
+    DevBuf table_own, table, bkeys, bcount;        // vertex table; bucket table (distinct vertex-0 keys): keys;
                                                    // point counts, then starts
     DevBuf points_own, place, perm, pts, svert, tiles;  // per point: bucket slot and place within the bucket; the
                                                         // simplex-sorted order and its tile view
@@ -410,7 +410,7 @@ pam_status_t compact_and_resolve(pam_lattice_s *h, int64_t M_estimate)
     hipStream_t s = h->stream;
     const uint32_t vcap = vertex_capacity(h);
     PAM_LAUNCH(h, kKCompact,
-               launch_compact((const uint64_t *)h->tkeys.ptr, (int32_t *)h->tids.ptr, (uint64_t *)h->vkeys.ptr, vcap,
+               launch_compact((Slot *)h->table.ptr, (uint64_t *)h->vkeys.ptr, vcap,
                               h->cap, h->ctl, h->host_result, ++h->attempt, s),
                "compact");
     // the resolve also clears the splat targets of the next forward and
@@ -419,7 +419,7 @@ pam_status_t compact_and_resolve(pam_lattice_s *h, int64_t M_estimate)
     const int64_t zcap = (int64_t)(std::min(h->lat[0].bytes, h->lat[2].bytes) / sizeof(float));
     PAM_LAUNCH(h, kKResolve,
                launch_resolve(h->d, h->feat, h->n, h->E, groups_of(h), h->ctl, (const int32_t *)h->perm.ptr,
-                              (const uint64_t *)h->tkeys.ptr, (const int32_t *)h->tids.ptr, h->cap,
+                              (const Slot *)h->table.ptr, h->cap,
                               (uint8_t *)h->tiles.ptr, (int32_t *)h->svert.ptr, (const uint64_t *)h->vkeys.ptr, vcap,
                               M_estimate, (int32_t *)h->nbr.ptr, (float *)h->lat[0].ptr, (float *)h->lat[2].ptr,
                               h->last_ld, zcap, (uint64_t *)h->bkeys.ptr, (int32_t *)h->bcount.ptr, h->bcap, s),
@@ -449,8 +449,7 @@ pam_status_t build_pass(pam_lattice_s *h, bool allow_fixed)
     const int64_t n = h->n, ntiles = (n + rec.T - 1) / rec.T;
     bool moved = false;
     if ((st = ensure_group(h->table_own,
-                           {{&h->tkeys, h->cap * sizeof(uint64_t)},
-                            {&h->tids, h->cap * sizeof(int32_t)},
+                           {{&h->table, h->cap * sizeof(Slot)},
                             {&h->bkeys, h->bcap * sizeof(uint64_t)},
                             {&h->bcount, h->bcap * sizeof(int32_t)}},
                            "hash tables", &moved)) != PAM_OK ||
@@ -477,7 +476,7 @@ pam_status_t build_pass(pam_lattice_s *h, bool allow_fixed)
     PAM_LAUNCH(h, kKInsert,
                launch_insert(h->d, h->feat, n, h->E, groups_of(h), h->ctl, fast ? &fixed : nullptr,
                              (uint64_t *)h->bkeys.ptr, (int32_t *)h->bcount.ptr, h->bcap, (int2 *)h->place.ptr,
-                             (uint64_t *)h->tkeys.ptr, h->cap, s),
+                             (Slot *)h->table.ptr, h->cap, s),
                "insert");
     PAM_LAUNCH(h, kKScan, launch_starts((int32_t *)h->bcount.ptr, h->bcap, h->ctl, s), "scan");
     PAM_LAUNCH(h, kKScatter,
@@ -486,7 +485,7 @@ pam_status_t build_pass(pam_lattice_s *h, bool allow_fixed)
                "scatter");
     PAM_LAUNCH(h, kKTiles,
                launch_sorted_tiles(h->d, h->feat, n, h->E, groups_of(h), h->ctl, (const int32_t *)h->perm.ptr,
-                                   (uint8_t *)h->pts.ptr, (uint64_t *)h->tkeys.ptr, h->cap, (uint8_t *)h->tiles.ptr,
+                                   (uint8_t *)h->pts.ptr, (Slot *)h->table.ptr, h->cap, (uint8_t *)h->tiles.ptr,
                                    s),
                "tiles");
     if ((st = compact_and_resolve(h, h->prev_M > 0 ? h->prev_M + h->prev_M / 4 : 1)) != PAM_OK)
@@ -1253,7 +1252,7 @@ void pam_lattice_destroy(pam_lattice_t lat)
         drain_timing(lat);
         for (hipEvent_t e : lat->event_pool)
             (void)hipEventDestroy(e);
-        DevBuf *bufs[] = {&lat->tkeys,     &lat->tids,       &lat->bkeys,      &lat->bcount, &lat->place,
+        DevBuf *bufs[] = {&lat->table,     &lat->bkeys,      &lat->bcount, &lat->place,
                           &lat->perm,      &lat->pts,        &lat->svert,      &lat->tiles,  &lat->vkeys,
                           &lat->nbr,       &lat->lat[0],     &lat->lat[1],     &lat->lat[2], &lat->lat[3],
                           &lat->table_own, &lat->points_own, &lat->vertex_own, &lat->lat_own, &lat->part,

@@ -216,16 +216,18 @@ __global__ void k_fill_f32(float *p, float value, int64_t count)
 // one half), so that a table far too small is given up at once.  Returns the
 // key's slot (all ones when the table is full).
 constexpr uint64_t kMaxProbe = 512;
+// STRIDE: 64-bit words per slot, the key first.
+template <int STRIDE>
 __device__ __forceinline__ uint64_t table_insert(uint64_t *tkeys, uint64_t mask, uint64_t key, uint32_t &added,
                                                  bool &full)
 {
     uint64_t h = mix64(key) & mask;
     for (uint64_t probe = 0; probe <= mask && probe < kMaxProbe; ++probe) {
-        const uint64_t cur = tkeys[h];
+        const uint64_t cur = tkeys[h * STRIDE];
         if (cur == key)
             return h;
         if (cur == kEmptyKey) {
-            const uint64_t prev = atomicCAS((unsigned long long *)&tkeys[h], (unsigned long long)kEmptyKey,
+            const uint64_t prev = atomicCAS((unsigned long long *)&tkeys[h * STRIDE], (unsigned long long)kEmptyKey,
                                             (unsigned long long)key);
             if (prev == kEmptyKey) {
                 ++added;
@@ -252,7 +254,7 @@ __device__ __forceinline__ uint64_t table_insert(uint64_t *tkeys, uint64_t mask,
 constexpr uint64_t kCompactWideCap = 1ull << 20;  // tables from this size take 16 slots per thread, else 4
 
 template <int PER>
-__global__ __launch_bounds__(kBlock) void k_compact(const uint64_t *__restrict__ tkeys, int32_t *tids,
+__global__ __launch_bounds__(kBlock) void k_compact(Slot *__restrict__ table,
                                                     uint64_t *vkeys, uint32_t vcap, uint64_t cap, Ctl *ctl,
                                                     HostResult *result, uint32_t attempt)
 {
@@ -280,7 +282,7 @@ __global__ __launch_bounds__(kBlock) void k_compact(const uint64_t *__restrict__
 #pragma unroll
     for (int j = 0; j < kCompactPer; ++j) {
         const uint64_t s = b0 + (uint64_t)j * kBlock;
-        key[j] = s < cap ? tkeys[s] : kEmptyKey;
+        key[j] = s < cap ? table[s].key : kEmptyKey;
         c += key[j] != kEmptyKey ? 1 : 0;
     }
     cs[threadIdx.x] = c;
@@ -294,7 +296,7 @@ __global__ __launch_bounds__(kBlock) void k_compact(const uint64_t *__restrict__
     for (int j = 0; j < kCompactPer; ++j) {
         const uint64_t s = b0 + (uint64_t)j * kBlock;
         if (key[j] != kEmptyKey) {
-            tids[s] = (int32_t)id;
+            table[s].id = (int32_t)id;
             if (id < vcap)
                 vkeys[id] = key[j];
             ++id;
@@ -302,16 +304,20 @@ __global__ __launch_bounds__(kBlock) void k_compact(const uint64_t *__restrict__
     }
 }
 
-__device__ __forceinline__ int32_t probe_id(const uint64_t *__restrict__ tkeys,
-                                            const int32_t *__restrict__ tids, uint64_t mask,
-                                            uint64_t key)
+__device__ __forceinline__ Slot load_slot(const Slot *__restrict__ table, uint64_t h)
+{
+    const ulonglong2 v = reinterpret_cast<const ulonglong2 *>(table)[h];
+    return {v.x, (int32_t)(uint32_t)v.y, 0};
+}
+
+__device__ __forceinline__ int32_t probe_id(const Slot *__restrict__ table, uint64_t mask, uint64_t key)
 {
     uint64_t h = mix64(key) & mask;
     for (uint64_t probe = 0; probe <= mask; ++probe) {
-        uint64_t cur = tkeys[h];
-        if (cur == key)
-            return tids[h];
-        if (cur == kEmptyKey)
+        const Slot cur = load_slot(table, h);
+        if (cur.key == key)
+            return cur.id;
+        if (cur.key == kEmptyKey)
             return -1;
         h = (h + 1) & mask;
     }
@@ -336,8 +342,7 @@ __device__ __forceinline__ void unpack_key(uint64_t key, int d, const KeyLayout 
 // u_j is the reverse.  A quotient that would leave its field has no vertex.
 template <int D>
 __device__ __forceinline__ void neighbour_item(const uint64_t *__restrict__ vkeys, uint32_t M, const KeyLayout &lay,
-                                               const uint64_t *__restrict__ tkeys, const int32_t *__restrict__ tids,
-                                               uint64_t mask, int32_t *__restrict__ nbr, uint32_t e)
+                                               const Slot *__restrict__ table, uint64_t mask, int32_t *__restrict__ nbr, uint32_t e)
 {
     const int j = (int)(e / M);
     const uint32_t m = e - (uint32_t)j * M;
@@ -375,30 +380,28 @@ __device__ __forceinline__ void neighbour_item(const uint64_t *__restrict__ vkey
         key[1] = key_m + D - others;
         ok[1] = !o_min;
     }
-    // both probes side by side: their first slots, then their ids, are
-    // requested together
-    uint64_t h[2], cur[2];
+    // both probes side by side: their first slots are requested together
+    uint64_t h[2];
+    Slot cur[2];
+    int32_t id[2];
     for (int sgn = 0; sgn < 2; ++sgn) {
         h[sgn] = mix64(key[sgn]) & mask;
-        cur[sgn] = ok[sgn] ? tkeys[h[sgn]] : kEmptyKey;
+        cur[sgn] = ok[sgn] ? load_slot(table, h[sgn]) : Slot{kEmptyKey, -1, 0};
     }
-    int64_t slot[2];
     for (int sgn = 0; sgn < 2; ++sgn) {
-        slot[sgn] = -1;
+        id[sgn] = -1;
         for (uint64_t probe = 0; ok[sgn] && probe <= mask; ++probe) {
-            if (cur[sgn] == key[sgn]) {
-                slot[sgn] = (int64_t)h[sgn];
+            if (cur[sgn].key == key[sgn]) {
+                id[sgn] = cur[sgn].id;
                 break;
             }
-            if (cur[sgn] == kEmptyKey)
+            if (cur[sgn].key == kEmptyKey)
                 break;
             h[sgn] = (h[sgn] + 1) & mask;
-            cur[sgn] = tkeys[h[sgn]];
+            cur[sgn] = load_slot(table, h[sgn]);
         }
     }
-    const int32_t id0 = slot[0] >= 0 ? tids[slot[0]] : -1;
-    const int32_t id1 = slot[1] >= 0 ? tids[slot[1]] : -1;
-    reinterpret_cast<int2 *>(nbr)[e] = make_int2(id0, id1);
+    reinterpret_cast<int2 *>(nbr)[e] = make_int2(id[0], id[1]);
 }
 
 __global__ void k_vertex_groups(const uint64_t *__restrict__ vkeys, int64_t M, const Ctl *ctl, int32_t *vgroup)
@@ -465,7 +468,7 @@ template <int D>
 __global__ __launch_bounds__(kInsertPoints) void k_insert(const float *__restrict__ feat, int64_t n, Elev E,
                                                           Groups64 grp, Ctl *ctl, KeyLayout fixed, int use_fixed,
                                                           uint64_t *bkeys, uint64_t bmask, int32_t *bcount,
-                                                          int2 *__restrict__ place, uint64_t *__restrict__ tkeys,
+                                                          int2 *__restrict__ place, Slot *__restrict__ table,
                                                           uint64_t cap)
 {
     constexpr int T = kInsertPoints;
@@ -478,9 +481,9 @@ __global__ __launch_bounds__(kInsertPoints) void k_insert(const float *__restric
     const int t = threadIdx.x;
     const int64_t ntiles = (n + T - 1) / T;
     if ((int64_t)blockIdx.x >= ntiles) {  // block-uniform
-        const uint64_t e = (uint64_t)((int64_t)blockIdx.x - ntiles) * T + t;  // two slots each
-        if (2 * e < cap)  // cap is a power of two >= 64: whole pieces
-            reinterpret_cast<ulonglong2 *>(tkeys)[e] = make_ulonglong2(kEmptyKey, kEmptyKey);
+        const uint64_t e = (uint64_t)((int64_t)blockIdx.x - ntiles) * T + t;
+        if (e < cap)
+            reinterpret_cast<ulonglong2 *>(table)[e] = make_ulonglong2(kEmptyKey, 0);
         return;
     }
     if (!use_fixed && (ctl->flags & (kFlagKeyRange | kFlagBadFeature)))
@@ -546,7 +549,7 @@ __global__ __launch_bounds__(kInsertPoints) void k_insert(const float *__restric
     bool full = false;
     for (int e = t; e < H; e += T) {
         if (hkey[e] != kEmptyKey) {
-            const uint64_t slot = table_insert(bkeys, bmask, hkey[e], added, full);
+            const uint64_t slot = table_insert<1>(bkeys, bmask, hkey[e], added, full);
             if (!full) {
                 hslot[e] = (int)slot;  // the bucket table has at most 2^31 slots
                 hcnt[e] = atomicAdd(&bcount[slot], hcnt[e]);
@@ -653,7 +656,7 @@ template <int D>
 __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__restrict__ feat, int64_t n, Elev E,
                                                                  Groups64 grp, Ctl *ctl,
                                                                  const int32_t *__restrict__ perm,
-                                                                 uint8_t *__restrict__ psort, uint64_t *tkeys,
+                                                                 uint8_t *__restrict__ psort, Slot *table,
                                                                  uint64_t mask, uint8_t *__restrict__ tiles)
 {
     constexpr int T = tile_points(D), NW = T / 64;
@@ -826,7 +829,7 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
             const uint64_t gfield = group_field(grp, lay, i);
 #pragma unroll
             for (int k = 0; k <= D; ++k)
-                table_insert(tkeys, mask, pack_vertex<D>(s, k, lay, gfield), added, full);
+                table_insert<2>(reinterpret_cast<uint64_t *>(table), mask, pack_vertex<D>(s, k, lay, gfield), added, full);
         }
     } else {
         // each distinct key's slot, for the resolve; -1 when it does not fit
@@ -839,7 +842,7 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
 #pragma unroll
             for (int c = 0; c < D; ++c)
                 kr -= (uint64_t)((lk >> c) & 1) << lay.shift[c];
-            const uint64_t h = table_insert(tkeys, mask, kr, added, full);
+            const uint64_t h = table_insert<2>(reinterpret_cast<uint64_t *>(table), mask, kr, added, full);
             rowkey[r] = kr;
             rowid[r] = h <= 0x7fffffffull ? (int32_t)h : -1;
         }
@@ -991,8 +994,7 @@ __host__ __device__ constexpr int resolve_waves(int d) { return d <= 8 ? 1 : 4; 
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_resolve(const float *__restrict__ feat, int64_t n, Elev E, Groups64 grp,
                                                     Ctl *ctl, const int32_t *__restrict__ perm,
-                                                    const uint64_t *__restrict__ tkeys,
-                                                    const int32_t *__restrict__ tids, uint64_t mask,
+                                                    const Slot *__restrict__ table, uint64_t mask,
                                                     uint8_t *__restrict__ tiles, int32_t *__restrict__ svert,
                                                     const uint64_t *__restrict__ vkeys, uint32_t vcap,
                                                     int32_t *__restrict__ nbr, unsigned tile_blocks,
@@ -1027,7 +1029,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(const float *__restrict__ fe
                 const uint64_t gfield = group_field(grp, lay, i);
                 for (int k = 0; k <= D; ++k)
                     svert[(base + p) * (D + 1) + k] =
-                        max(probe_id(tkeys, tids, mask, pack_vertex<D>(s, k, lay, gfield)), 0);
+                        max(probe_id(table, mask, pack_vertex<D>(s, k, lay, gfield)), 0);
             }
             return;
         }
@@ -1042,12 +1044,12 @@ __global__ __launch_bounds__(kBlock) void k_resolve(const float *__restrict__ fe
                 hs[j] = r0 + j * 64 * W < nrows ? rowid[r0 + j * 64 * W] : 0;
 #pragma unroll
             for (int j = 0; j < J; ++j)
-                ids[j] = hs[j] >= 0 ? tids[hs[j]] : 0;
+                ids[j] = hs[j] >= 0 ? table[hs[j]].id : 0;
 #pragma unroll
             for (int j = 0; j < J; ++j) {
                 const int r = r0 + j * 64 * W;
                 if (r < nrows)
-                    rowid[r] = hs[j] >= 0 ? ids[j] : max(probe_id(tkeys, tids, mask, rowkey[r]), 0);
+                    rowid[r] = hs[j] >= 0 ? ids[j] : max(probe_id(table, mask, rowkey[r]), 0);
             }
         }
         return;
@@ -1056,7 +1058,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(const float *__restrict__ fe
     if (b < nbr_blocks) {
         const uint64_t items = (uint64_t)M * (D + 1);  // < 2^31
         for (uint64_t e = (uint64_t)b * kBlock + threadIdx.x; e < items; e += (uint64_t)nbr_blocks * kBlock)
-            neighbour_item<D>(vkeys, M, lay, tkeys, tids, mask, nbr, (uint32_t)e);
+            neighbour_item<D>(vkeys, M, lay, table, mask, nbr, (uint32_t)e);
         return;
     }
     const uint64_t first = (uint64_t)(b - nbr_blocks) * kBlock + threadIdx.x;
@@ -1121,18 +1123,18 @@ hipError_t launch_fill_f32(float *p, float value, int64_t count, hipStream_t s)
 
 hipError_t launch_insert(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
                          const KeyLayout *fixed, uint64_t *bkeys, int32_t *bcount, uint64_t bcap, int2 *place,
-                         uint64_t *tkeys, uint64_t cap, hipStream_t s)
+                         Slot *table, uint64_t cap, hipStream_t s)
 {
     if (n <= 0)
         return hipSuccess;
     if (bcap < 64 || (bcap & (bcap - 1)) != 0 || bcap > ((uint64_t)1 << 31) || cap < 64 || (cap & (cap - 1)) != 0)
         return hipErrorInvalidValue;
     const uint64_t T = kInsertPoints;
-    const uint64_t grid = ((uint64_t)n + T - 1) / T + (cap / 2 + T - 1) / T;
+    const uint64_t grid = ((uint64_t)n + T - 1) / T + (cap + T - 1) / T;
     const KeyLayout lay = fixed ? *fixed : KeyLayout{};
     const int use_fixed = fixed ? 1 : 0;
     PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_insert<D>, dim3((unsigned)grid), dim3(kInsertPoints), 0, s, feat, n, E,
-                                         grp, ctl, lay, use_fixed, bkeys, bcap - 1, bcount, place, tkeys, cap));
+                                         grp, ctl, lay, use_fixed, bkeys, bcap - 1, bcount, place, table, cap));
     return hipGetLastError();
 }
 
@@ -1186,7 +1188,7 @@ hipError_t launch_scatter(const int2 *place, const int32_t *start, int64_t n, co
 }
 
 hipError_t launch_sorted_tiles(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
-                               const int32_t *perm, uint8_t *psort, uint64_t *tkeys, uint64_t cap, uint8_t *tiles,
+                               const int32_t *perm, uint8_t *psort, Slot *table, uint64_t cap, uint8_t *tiles,
                                hipStream_t s)
 {
     if (n <= 0)
@@ -1195,27 +1197,27 @@ hipError_t launch_sorted_tiles(int d, const float *feat, int64_t n, const Elev &
         return hipErrorInvalidValue;
     const int T = tile_points(d);
     PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_sorted_tiles<D>, dim3((unsigned)((n + T - 1) / T)), dim3(T), 0, s, feat, n,
-                                         E, grp, ctl, perm, psort, tkeys, cap - 1, tiles));
+                                         E, grp, ctl, perm, psort, table, cap - 1, tiles));
     return hipGetLastError();
 }
 
-hipError_t launch_compact(const uint64_t *tkeys, int32_t *tids, uint64_t *vkeys, uint32_t vcap, uint64_t cap,
+hipError_t launch_compact(Slot *table, uint64_t *vkeys, uint32_t vcap, uint64_t cap,
                           Ctl *ctl, HostResult *result, uint32_t attempt, hipStream_t s)
 {
     if (cap >= kCompactWideCap) {
         const uint64_t per_block = (uint64_t)kBlock * 16;
         hipLaunchKernelGGL(k_compact<16>, dim3((unsigned)((cap + per_block - 1) / per_block)), dim3(kBlock), 0, s,
-                           tkeys, tids, vkeys, vcap, cap, ctl, result, attempt);
+                           table, vkeys, vcap, cap, ctl, result, attempt);
     } else {
         const uint64_t per_block = (uint64_t)kBlock * 4;
         hipLaunchKernelGGL(k_compact<4>, dim3((unsigned)((cap + per_block - 1) / per_block)), dim3(kBlock), 0, s,
-                           tkeys, tids, vkeys, vcap, cap, ctl, result, attempt);
+                           table, vkeys, vcap, cap, ctl, result, attempt);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
-                          const int32_t *perm, const uint64_t *tkeys, const int32_t *tids, uint64_t cap,
+                          const int32_t *perm, const Slot *table, uint64_t cap,
                           uint8_t *tiles, int32_t *svert, const uint64_t *vkeys, uint32_t vcap, int64_t M_estimate,
                           int32_t *nbr, float *z0, float *z1, int32_t zld, int64_t zcap, uint64_t *bkeys,
                           int32_t *bcount, uint64_t bcap, hipStream_t s)
@@ -1233,7 +1235,7 @@ hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, co
     const int64_t pieces = std::max<int64_t>(M_estimate * zld / 4, (int64_t)(bcap / 2));
     const int64_t clear_blocks = std::min<int64_t>((pieces + kBlock - 1) / kBlock, 4096);
     PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_resolve<D>, dim3((unsigned)(tile_blocks + nbr_blocks + clear_blocks)),
-                                         dim3(kBlock), 0, s, feat, n, E, grp, ctl, perm, tkeys, tids, cap - 1, tiles,
+                                         dim3(kBlock), 0, s, feat, n, E, grp, ctl, perm, table, cap - 1, tiles,
                                          svert, vkeys, vcap, nbr, (unsigned)tile_blocks, (unsigned)nbr_blocks, z0, z1,
                                          zld, zcap, bkeys, bcount, bcap));
     return hipGetLastError();

@@ -52,6 +52,15 @@ struct KeyLayout {
     int32_t total_bits;
 };
 
+// Slot of the vertex hash table: a key and, from the compaction on, its id,
+// in one 16-byte access, so that a look-up that finds its key has the id
+// without a second random access.  kEmptyKey marks an empty slot.
+struct __attribute__((aligned(16))) Slot {
+    uint64_t key;
+    int32_t id;
+    int32_t pad;
+};
+
 // Point groups of a batched build: points [gstart[g], gstart[g+1]) form
 // group g (device array of G+1 entries; G = 1 and gstart = null for one
 // group).
@@ -160,7 +169,7 @@ hipError_t launch_fill_f32(float *p, float value, int64_t count, hipStream_t s);
 // in the bucket.  Also empties the vertex table (cap slots).
 hipError_t launch_insert(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
                          const KeyLayout *fixed, uint64_t *bkeys, int32_t *bcount, uint64_t bcap, int2 *place,
-                         uint64_t *tkeys, uint64_t cap, hipStream_t s);
+                         Slot *table, uint64_t cap, hipStream_t s);
 // A key layout that needs no range pass: every stored coordinate's quotient
 // in [-2^(b-1), 2^(b-1)) with b bits, b = (63 - bits of k - gbits) / d;
 // false when b < 6 (then the range pass always runs).
@@ -172,18 +181,18 @@ hipError_t launch_scatter(const int2 *place, const int32_t *start, int64_t n, co
 // the sorted tiles' records (rows as slots of the vertex table, filled here)
 // and the points' records
 hipError_t launch_sorted_tiles(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
-                               const int32_t *perm, uint8_t *psort, uint64_t *tkeys, uint64_t cap, uint8_t *tiles,
+                               const int32_t *perm, uint8_t *psort, Slot *table, uint64_t cap, uint8_t *tiles,
                                hipStream_t s);
 // dense ids; publishes the outcome to ctl->result and *result (pinned host
 // memory), as attempt number `attempt`; vkeys holds vcap keys
-hipError_t launch_compact(const uint64_t *tkeys, int32_t *tids, uint64_t *vkeys, uint32_t vcap, uint64_t cap,
+hipError_t launch_compact(Slot *table, uint64_t *vkeys, uint32_t vcap, uint64_t cap,
                           Ctl *ctl, HostResult *result, uint32_t attempt, hipStream_t s);
 // the tiles' rows as vertex ids, the neighbour table (vcap vertices at most;
 // else nothing is done), and the clears for the calls that follow: M * zld
 // floats of z0 and z1 when they hold them (zcap), the bucket table, ctl's
 // flags and counters.  M_estimate sizes the launch only.
 hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
-                          const int32_t *perm, const uint64_t *tkeys, const int32_t *tids, uint64_t cap,
+                          const int32_t *perm, const Slot *table, uint64_t cap,
                           uint8_t *tiles, int32_t *svert, const uint64_t *vkeys, uint32_t vcap, int64_t M_estimate,
                           int32_t *nbr, float *z0, float *z1, int32_t zld, int64_t zcap, uint64_t *bkeys,
                           int32_t *bcount, uint64_t bcap, hipStream_t s);
