@@ -304,7 +304,7 @@ def row_ceiling(x, torch, P, reps: int = 10) -> dict:
 KERNEL_SYMBOL = {  # timing kind -> kernel symbol (without template arguments)
     "range": "k_range", "layout": "k_layout", "fill": "k_fill_f32", "insert": "k_insert",
     "compact": "k_compact", "resolve": "k_resolve", "scan": "k_starts", "scatter": "k_scatter",
-    "tiles": "k_sorted_tiles", "splat": "k_splat", "splat_bwd": "k_splat", "blur": "k_blur2", "slice": "k_slice",
+    "tiles": "k_sorted_tiles", "splat": "k_splat_rows", "splat_bwd": "k_splat_rows", "blur": "k_blur2", "slice": "k_slice",
     "slice_bwd": "k_slice_bwd", "splat_aug": "k_splat", "slice_aug": "k_slice_aug",
 }
 

@@ -17,11 +17,12 @@
 // inside the group with cross-lane shuffles.
 //
 // Splat kernels read the tile's view of the lattice prepared by the build
-// (its distinct vertices as rows and its contributions sorted by row): lanes
-// own whole rows and sum their contributions in registers from an LDS copy
-// of the tile's values, and each row reaches the global lattice with one
-// coalesced fp32 atomic per channel.  On gfx950 LDS float atomics cost about
-// 3 cycles per lane, so no kernel accumulates with them.
+// (its distinct vertices as rows and its contributions sorted by row, cut
+// into segments): lane groups sum a segment in registers, from an LDS copy of
+// the tile's rows (k_splat_rows: plain rows) or gathering them through the
+// caches (k_splat: sums that need more), and each sum reaches the global
+// lattice with fp32 atomics that cover whole rows.  On gfx950 LDS float
+// atomics cost about 3 cycles per lane, so no kernel accumulates with them.
 #include "pam_device.h"
 
 #include <algorithm>
@@ -293,7 +294,8 @@ struct Groups {
 };
 
 // ---------------------------------------------------------------------------
-// Splat (forward): L[m] += sum over the tile's points of b_k v.
+// Splat of more than plain rows (normalised backward, augmented channels, the
+// fused eq. 8 term): L[m] += sum over the tile's points of b_k x.
 //
 // The build's per-tile view (TileRec) lists the tile's contributions sorted
 // by row and cut into segments of at most kSegLen.  Segments are handed out
@@ -326,8 +328,7 @@ __host__ __device__ constexpr int seg_cap(int T) { return T >= 512 ? PAM_SEG_CAP
 #endif
 __host__ __device__ constexpr int splat_threads(int d) { return tile_points(d) * PAM_SPLAT_SPREAD; }
 
-// Splat modes: x as given (forward, and the backward splat of dL/dv' in raw
-// mode), or, for the normalised backward pass, x = g / z with the weight
+// Splat modes: x as given (with the fused eq. 8 term), or, for the normalised backward pass, x = g / z with the weight
 // column taking b * gamma, or the augmented channels of the embedding
 // gradient: d*C lattice channels, channel a*C + c taking f_a x_c (f the
 // build's features).
@@ -796,8 +797,8 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
     constexpr bool NORMB = MODE == kSplatNormBwd;
     constexpr bool AUG = MODE == kSplatAug;
     constexpr int NZ = NORMB ? T : 1;
-    // XS, for tiles of 256 points (d > 5: many rows, few contributions
-    // each) with passes of at most 16 channels: the pass's channels of
+    // XS, for the normalised backward pass on tiles of 256 points (d > 5:
+    // many rows, few contributions each) with passes of at most 16 channels: the pass's channels of
     // every point's row of x are copied to LDS once (thread t holds point
     // t's row), and the contributions read them there instead of gathering
     // each row d+1 times from global memory.  A row then has about one

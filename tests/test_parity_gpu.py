@@ -761,6 +761,13 @@ def test_augmented_embedding_gradient(O, d, C, size):
     log("  " + check_array("eq. 8 df", df8, odf8, msg, cancel))
 
 
+@pytest.mark.parametrize("d,C", [(3, 13), (5, 3), (8, 10)])
+def test_augmented_narrow_scalar_rows(O, d, C):
+    """The augmented gradient over scalar rows of at most 16 channels: lane
+    groups of 8 and 16 in its splats and its slice."""
+    test_augmented_embedding_gradient(O, d, C, 1300)
+
+
 @pytest.mark.parametrize("d,C,scale", [(12, 4, 1.0), (16, 6, 0.5)], ids=["d12c4", "d16c6"])
 def test_augmented_high_dimensions(O, d, C, scale):
     """PAM_EGRAD_AUGMENTED above d = 8, where a tile's d+1 values per
