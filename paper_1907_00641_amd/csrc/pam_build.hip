@@ -23,6 +23,7 @@
 // about 330 against 940), so the d+1 keys of a point are deduplicated and
 // inserted once, in the sorted order.
 #include "pam_device.h"
+#include "pam_grid.h"
 
 #include <algorithm>
 
@@ -333,8 +334,8 @@ __device__ __forceinline__ void unpack_key(uint64_t key, int d, const KeyLayout 
     }
 }
 
-// One entry of the neighbour table: the ids of key_m -/+ u_j (-1 if
-// absent), u_j = (d+1) e_j - 1.  nbr is direction-major:
+// Entry nbr_entry(j, m, M) of the neighbour table: the ids of key_m -/+ u_j
+// (-1 if absent), u_j = (d+1) e_j - 1.  nbr is direction-major:
 // nbr[(j * M + m) * 2 + 0] = id(key_m - u_j), nbr[(j * M + m) * 2 + 1] = id(key_m + u_j).
 // On the packed key (remainder k, quotients t_c): adding u_j lowers every
 // coordinate by one and raises coordinate j by d+1, so k becomes k - 1 with
@@ -342,10 +343,9 @@ __device__ __forceinline__ void unpack_key(uint64_t key, int d, const KeyLayout 
 // u_j is the reverse.  A quotient that would leave its field has no vertex.
 template <int D>
 __device__ __forceinline__ void neighbour_item(const uint64_t *__restrict__ vkeys, uint32_t M, const KeyLayout &lay,
-                                               const Slot *__restrict__ table, uint64_t mask, int32_t *__restrict__ nbr, uint32_t e)
+                                               const Slot *__restrict__ table, uint64_t mask,
+                                               int32_t *__restrict__ nbr, int j, int64_t m)
 {
-    const int j = (int)(e / M);
-    const uint32_t m = e - (uint32_t)j * M;
     const uint64_t key_m = vkeys[m];
     const int k = (int)(key_m & ((1ull << lay.kbits) - 1));
     uint64_t one_j = 0, others = 0;  // 1 in field j; 1 in every other field
@@ -401,7 +401,7 @@ __device__ __forceinline__ void neighbour_item(const uint64_t *__restrict__ vkey
             cur[sgn] = load_slot(table, h[sgn]);
         }
     }
-    reinterpret_cast<int2 *>(nbr)[e] = make_int2(id[0], id[1]);
+    reinterpret_cast<int2 *>(nbr)[nbr_entry(j, m, M)] = make_int2(id[0], id[1]);
 }
 
 __global__ void k_vertex_groups(const uint64_t *__restrict__ vkeys, int64_t M, const Ctl *ctl, int32_t *vgroup)
@@ -981,7 +981,7 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
 //   vertex id (kResolveRows rows per lane requested together: slots, then
 //   ids); a tile that overflowed its LDS table looks up its points' keys one
 //   by one and writes their ids to svert;
-// * the neighbour table, one item per thread and trip;
+// * the neighbour table, one vertex of one direction per thread and trip;
 // * clears: the first M * zld floats of z0 and z1 (the lattice buffers the
 //   next filter calls splat into, zcap floats each, so that those calls
 //   need no clearing launch of their own), the bucket table, and the
@@ -989,6 +989,7 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
 // Reads the outcome the compaction published; does nothing when the build
 // failed or its vertices do not fit vcap (the buffers of vkeys and nbr).
 constexpr int kResolveRows = 4;
+static_assert(kBlock == kGridBlock, "the neighbour blocks' arithmetic");
 __host__ __device__ constexpr int resolve_waves(int d) { return d <= 8 ? 1 : 4; }
 
 template <int D>
@@ -1056,9 +1057,10 @@ __global__ __launch_bounds__(kBlock) void k_resolve(const float *__restrict__ fe
     }
     const unsigned b = blockIdx.x - tile_blocks;
     if (b < nbr_blocks) {
-        const uint64_t items = (uint64_t)M * (D + 1);  // < 2^31
-        for (uint64_t e = (uint64_t)b * kBlock + threadIdx.x; e < items; e += (uint64_t)nbr_blocks * kBlock)
-            neighbour_item<D>(vkeys, M, lay, table, mask, nbr, (uint32_t)e);
+        const unsigned per_dir = nbr_blocks / (D + 1);
+        const int j = nbr_dir(b, per_dir);
+        for (int64_t m = nbr_first(b, per_dir, (int)threadIdx.x); m < (int64_t)M; m += nbr_stride(per_dir))
+            neighbour_item<D>(vkeys, M, lay, table, mask, nbr, j, m);
         return;
     }
     const uint64_t first = (uint64_t)(b - nbr_blocks) * kBlock + threadIdx.x;
@@ -1230,8 +1232,7 @@ hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, co
     const int64_t tile_blocks = (ntiles * resolve_waves(d) + kBlock / 64 - 1) / (kBlock / 64);
     // the item and clear loops stride over whatever their extents turn out
     // to be; the estimate only sizes the launch
-    const int64_t items = std::max<int64_t>(M_estimate, 1) * (d + 1);
-    const int64_t nbr_blocks = (items + kBlock - 1) / kBlock;
+    const int64_t nbr_blocks = (int64_t)nbr_blocks_per_dir(M_estimate) * (d + 1);
     const int64_t pieces = std::max<int64_t>(M_estimate * zld / 4, (int64_t)(bcap / 2));
     const int64_t clear_blocks = std::min<int64_t>((pieces + kBlock - 1) / kBlock, 4096);
     PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_resolve<D>, dim3((unsigned)(tile_blocks + nbr_blocks + clear_blocks)),
