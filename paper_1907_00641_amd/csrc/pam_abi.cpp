@@ -448,11 +448,14 @@ pam_status_t build_pass(pam_lattice_s *h, bool allow_fixed)
     const TileRec rec(h->d);
     const int64_t n = h->n, ntiles = (n + rec.T - 1) / rec.T;
     bool moved = false;
-    if ((st = ensure_group(h->table_own,
-                           {{&h->table, h->cap * sizeof(Slot)},
-                            {&h->bkeys, h->bcap * sizeof(uint64_t)},
-                            {&h->bcount, h->bcap * sizeof(int32_t)}},
-                           "hash tables", &moved)) != PAM_OK ||
+    st = ensure_group(h->table_own,
+                      {{&h->table, h->cap * sizeof(Slot)},
+                       {&h->bkeys, h->bcap * sizeof(uint64_t)},
+                       {&h->bcount, h->bcap * sizeof(int32_t)}},
+                      "hash tables", &moved);
+    if (moved)
+        h->clean_bcap = 0;  // at once: a failure below returns, and a later build must not take the table as empty
+    if (st != PAM_OK ||
         (st = ensure_group(h->points_own,
                            {{&h->place, (size_t)n * sizeof(int2)},
                             {&h->perm, (size_t)n * sizeof(int32_t)},
@@ -462,7 +465,7 @@ pam_status_t build_pass(pam_lattice_s *h, bool allow_fixed)
                            "sorted points")) != PAM_OK)
         return st;
     KeyLayout fixed{};
-    const bool fast = allow_fixed && !moved && h->clean_bcap == h->bcap && fixed_layout(h->d, h->gbits, &fixed);
+    const bool fast = allow_fixed && h->clean_bcap == h->bcap && fixed_layout(h->d, h->gbits, &fixed);
     h->clean_bcap = 0;  // the insert fills the table
     if (!fast) {
         if ((st = ensure(h->part, (size_t)kRangePartInts * sizeof(int32_t), "range partials")) != PAM_OK)

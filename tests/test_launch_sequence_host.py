@@ -122,3 +122,24 @@ int main()
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", csrc, str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
+
+
+def test_range_pass_after_a_failed_allocation(run):
+    """A build whose vertex table grows moves the bucket table too; when it
+    then runs out of memory for the points, the next build finds a bucket
+    table that nothing has emptied, and must not take it as empty."""
+    out = run("""
+out['grow'] = [build(4000, 3, 100), build(4000, 3, 200000)]
+shim.fake_fail_above(1 << 25)
+out['fails'] = build(1000000, 3, 200000)
+shim.fake_fail_above((1 << 64) - 1)
+out['next'] = build(4000, 3, 100)
+out['again'] = build(4000, 3, 100)
+""")
+    assert [st for st, _ in out["grow"]] == [0, 0]
+    st, rows = out["fails"]
+    assert st == 2 and rows == []  # out of memory, before any launch
+    st, rows = out["next"]
+    assert st == 0 and [r[0] for r in rows][:3] == ["k_range", "k_layout", "k_insert"]
+    st, rows = out["again"]
+    assert st == 0
