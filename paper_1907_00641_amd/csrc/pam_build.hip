@@ -481,8 +481,8 @@ __global__ __launch_bounds__(kInsertPoints) void k_insert(const float *__restric
     const int t = threadIdx.x;
     const int64_t ntiles = (n + T - 1) / T;
     if ((int64_t)blockIdx.x >= ntiles) {  // block-uniform
-        const uint64_t e = (uint64_t)((int64_t)blockIdx.x - ntiles) * T + t;
-        if (e < cap)
+        const uint64_t stride = (uint64_t)(gridDim.x - ntiles) * T;
+        for (uint64_t e = (uint64_t)((int64_t)blockIdx.x - ntiles) * T + t; e < cap; e += stride)
             reinterpret_cast<ulonglong2 *>(table)[e] = make_ulonglong2(kEmptyKey, 0);
         return;
     }
@@ -1132,7 +1132,7 @@ hipError_t launch_insert(int d, const float *feat, int64_t n, const Elev &E, con
     if (bcap < 64 || (bcap & (bcap - 1)) != 0 || bcap > ((uint64_t)1 << 31) || cap < 64 || (cap & (cap - 1)) != 0)
         return hipErrorInvalidValue;
     const uint64_t T = kInsertPoints;
-    const uint64_t grid = ((uint64_t)n + T - 1) / T + (cap + T - 1) / T;
+    const uint64_t grid = ((uint64_t)n + T - 1) / T + table_clear_blocks(cap, kInsertPoints);
     const KeyLayout lay = fixed ? *fixed : KeyLayout{};
     const int use_fixed = fixed ? 1 : 0;
     PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_insert<D>, dim3((unsigned)grid), dim3(kInsertPoints), 0, s, feat, n, E,

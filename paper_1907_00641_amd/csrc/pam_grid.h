@@ -31,4 +31,13 @@ constexpr int64_t nbr_stride(unsigned per_dir) { return (int64_t)per_dir * kGrid
 // direction-major place of vertex m's pair of neighbours in direction j
 constexpr int64_t nbr_entry(int j, int64_t m, int64_t M) { return (int64_t)j * M + m; }
 
+// Clearing blocks of `threads` threads for a table of cap slots, a slot per
+// thread and trip: at most 2^30 work items, next to fewer than 2^31 for the
+// points of the same launch.
+constexpr unsigned table_clear_blocks(uint64_t cap, int threads)
+{
+    const uint64_t blocks = (cap + threads - 1) / threads, most = ((uint64_t)1 << 30) / threads;
+    return (unsigned)(blocks < most ? blocks : most);
+}
+
 }  // namespace pam

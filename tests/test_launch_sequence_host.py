@@ -143,3 +143,16 @@ out['again'] = build(4000, 3, 100)
     assert st == 0 and [r[0] for r in rows][:3] == ["k_range", "k_layout", "k_insert"]
     st, rows = out["again"]
     assert st == 0
+
+
+def test_largest_table_capacity(run):
+    """pam_lattice_set_capacity takes up to 2^34 slots; no launch of the
+    build may then exceed what a launch may have."""
+    out = run("""
+build(4000, 3, 100)
+out['set'] = L.pam_lattice_set_capacity(h, 1 << 34, 1)
+out['large'] = build(4000, 3, 100)
+""")
+    st, rows = out["large"]
+    assert out["set"] == 0
+    assert st == 0 and not any(r[3] for r in rows), rows
