@@ -634,11 +634,10 @@ constexpr int kTileProbe = 512;
 // the filter kernels read; the tile's distinct vertices become dense rows
 // (LDS hash) whose keys are inserted into the vertex hash table, their slots
 // kept in the tile record for the resolve; the tile's (point, vertex)
-// contributions are counting-sorted by (window, row) (integer LDS atomics
-// give each its position within its pair); each pair's contributions are cut
-// into segments of at most kSegLen, and the segments are counting-sorted
-// window by window and by length, longest first, the order in which the
-// splat hands them out.
+// contributions are counting-sorted by row (integer LDS atomics give each its
+// position within its row); each row's contributions are cut into segments of
+// at most kSegLen, and the segments are counting-sorted by length, longest
+// first, the order in which the splat hands them out.
 //
 // A point's vertices are told apart within the tile by the bucket the point
 // belongs to (its vertex 0; a bucket's points are consecutive) and the set of
@@ -665,9 +664,6 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     static_assert(NC < (1 << 13), "segment start and row must fit their 13-bit fields");
     constexpr int kTileHashBits = tile_hash_bits(D);
     constexpr int kTileHash = 1 << kTileHashBits;
-    constexpr int kWin = splat_windows(D);  // point windows per tile
-    constexpr int kWinPts = T / kWin;
-    static_assert(kWin == 1 || kWinPts >= 64, "a wave must not span two windows");
     // two uses of one piece of LDS: the hash (local keys, their rows) and the
     // buckets' keys, until every contribution has its row; then the weights
     // and the sorted entries, on their way to coalesced stores
@@ -679,12 +675,12 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     uint16_t *hrow = reinterpret_cast<uint16_t *>(pool + T * 8 + kTileHash * 4);
     float *sw = reinterpret_cast<float *>(pool);
     uint16_t *slist = reinterpret_cast<uint16_t *>(pool + NC * 4);
-    // per (window, row): count, then first entry (cnt), and segment count,
-    // then first segment (nsg); before that the local keys in row order
+    // per row: count, then first entry (cnt), and segment count, then first
+    // segment (nsg); before that the local keys in row order
     __shared__ int cnt[kTileHash + 1];
     __shared__ int nsg[kTileHash + 1];
     uint32_t *rkey = reinterpret_cast<uint32_t *>(cnt);
-    __shared__ int hist[kWin * (kSegLen + 1)];
+    __shared__ int hist[kSegLen + 1];
     __shared__ int wsum[2 * (T / 64 + 1)];
     __shared__ uint64_t last_s[NW];
     __shared__ int starts_s[NW];
@@ -712,7 +708,7 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     const int64_t i = valid ? perm[base + t] : 0;
     for (int e = t; e < kTileHash; e += T)
         hkey[e] = ~0u;
-    for (int e = t; e < kWin * (kSegLen + 1); e += T)
+    for (int e = t; e <= kSegLen; e += T)
         hist[e] = 0;
     if (t == 0) {
         nrows_s = 0;
@@ -812,13 +808,6 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
             overflow_s = 1;
     }
     __syncthreads();
-    // a tile whose (window, row) pairs do not fit the counters or the record
-    // takes the overflow path too
-    if (kWin > 1) {
-        if (t == 0 && !(nrows_s * kWin <= kTileHash && nrows_s * kWin <= NC))
-            overflow_s = 1;
-        __syncthreads();
-    }
     const int nrows = nrows_s;
     uint32_t added = 0;
     bool full = false;
@@ -869,19 +858,13 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
         }
         return;
     }
-    // Contributions are counting-sorted by (point window, row): a row's
-    // contributions from one window of consecutive points form their own
-    // segments, and window w's entries and segments are contiguous.
-    const int nwin = kWin;
-    const int nq = nrows * nwin;
-    for (int e = t; e < nq; e += T)
+    for (int e = t; e < nrows; e += T)
         cnt[e] = 0;
     __syncthreads();
-    const int win = nwin > 1 ? t / kWinPts : 0;
     int q[D + 1], pos[D + 1];
 #pragma unroll
     for (int k = 0; k <= D; ++k) {
-        q[k] = win * nrows + (valid ? (int)hrow[slot[k]] : 0);
+        q[k] = valid ? (int)hrow[slot[k]] : 0;
         int first_pos = 0;
         if (valid && run[k].lead == lane)
             first_pos = atomicAdd(&cnt[q[k]], run[k].len);
@@ -892,16 +875,16 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
             uint32_t *lr = reinterpret_cast<uint32_t *>(lrow + t * (D + 1));
 #pragma unroll
             for (int k = 0; k <= D; k += 2)
-                lr[k / 2] = (uint32_t)(q[k] - win * nrows) | ((uint32_t)(q[k + 1] - win * nrows) << 16);
+                lr[k / 2] = (uint32_t)q[k] | ((uint32_t)q[k + 1] << 16);
         } else {
 #pragma unroll
             for (int k = 0; k <= D; ++k)
-                lrow[t * (D + 1) + k] = (uint16_t)(q[k] - win * nrows);
+                lrow[t * (D + 1) + k] = (uint16_t)q[k];
         }
     }
     __syncthreads();  // hkey, hrow and bkey are dead from here: their LDS takes the entries
-    // cnt[q]: first entry of pair q; nsg[q]: its first segment
-    const int nseg = block_exclusive_scan_ceil(cnt, nsg, nq, kSegLen, wsum);
+    // cnt[r]: first entry of row r; nsg[r]: its first segment
+    const int nseg = block_exclusive_scan_ceil(cnt, nsg, nrows, kSegLen, wsum);
     if (valid) {
 #pragma unroll
         for (int k = 0; k <= D; ++k) {
@@ -909,15 +892,14 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
             slist[cnt[q[k]] + pos[k]] = (uint16_t)((t << 5) | k);
         }
     }
-    // segments in (window, row) order, and a histogram of (window, length)
-    for (int qq = t; qq < nq; qq += T) {
-        const int e0 = cnt[qq], e1 = (qq + 1 < nq) ? cnt[qq + 1] : nc;
-        const int w = qq / nrows, r = qq - w * nrows;
-        sfirst[qq] = (uint16_t)nsg[qq];
+    // segments in row order, and a histogram of their lengths
+    for (int r = t; r < nrows; r += T) {
+        const int e0 = cnt[r], e1 = (r + 1 < nrows) ? cnt[r + 1] : nc;
+        sfirst[r] = (uint16_t)nsg[r];
         for (int j = 0, e = e0; e < e1; ++j, e += kSegLen) {
             const int len = min(kSegLen, e1 - e);
-            seg[nsg[qq] + j] = seg_encode(e, len, r);
-            atomicAdd(&hist[w * (kSegLen + 1) + kSegLen - len], 1);  // longest first within a window
+            seg[nsg[r] + j] = seg_encode(e, len, r);
+            atomicAdd(&hist[kSegLen - len], 1);  // longest first
         }
     }
     __syncthreads();
@@ -928,7 +910,7 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     if (t < 64) {
         // bucket starts (then used as cursors): an exclusive scan of the
         // histogram by the first wave, each lane over NBL consecutive buckets
-        constexpr int NB = kWin * (kSegLen + 1), NBL = (NB + 63) / 64;
+        constexpr int NB = kSegLen + 1, NBL = (NB + 63) / 64;
         int v[NBL], sum = 0;
 #pragma unroll
         for (int u = 0; u < NBL; ++u) {
@@ -953,21 +935,20 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
         }
     }
     if (t == 0) {
-        sfirst[nq] = (uint16_t)nseg;
+        sfirst[nrows] = (uint16_t)nseg;
         hdr[0] = (uint32_t)nrows;
-        hdr[1] = (uint32_t)nwin << 8;
+        hdr[1] = 0;
         hdr[2] = (uint32_t)nc;
         hdr[3] = (uint32_t)nseg;
     }
     __syncthreads();
-    // work order: windows in turn, longest segments first within a window
-    for (int qq = t; qq < nq; qq += T) {
-        const int e0 = cnt[qq], e1 = (qq + 1 < nq) ? cnt[qq + 1] : nc;
-        const int w = qq / nrows, r = qq - w * nrows;
+    // work order: longest segments first
+    for (int r = t; r < nrows; r += T) {
+        const int e0 = cnt[r], e1 = (r + 1 < nrows) ? cnt[r + 1] : nc;
         for (int j = 0, e = e0; e < e1; ++j, e += kSegLen) {
             const int len = min(kSegLen, e1 - e);
-            const int at = atomicAdd(&hist[w * (kSegLen + 1) + kSegLen - len], 1);
-            order[at] = (uint16_t)(nsg[qq] + j);
+            const int at = atomicAdd(&hist[kSegLen - len], 1);
+            order[at] = (uint16_t)(nsg[r] + j);
             wseg[at] = seg_encode(e, len, r);
         }
     }

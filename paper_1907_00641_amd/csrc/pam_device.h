@@ -256,28 +256,22 @@ __host__ __device__ constexpr int tile_points(int d)
 }
 
 // Per-tile view of the lattice, for the tiles of the simplex-sorted order.
-// A tile is cut into nwin windows of consecutive points.
 // With nc = (points in the tile) * (d+1):
 //   hdr    : nrows; flags (bit 0: the tile's vertices did not fit the LDS
-//            dedup table, then only the per-point ids are valid) | nwin << 8;
-//            nc; nseg
+//            dedup table, then only the per-point ids are valid); nc; nseg
 //   rowid  : nrows global vertex ids, one per distinct vertex of the tile
 //            (slots of the vertex table until the resolve)
 //   rowkey : nrows packed keys of those vertices (uint64)
-//   sfirst : nwin * nrows + 1 first segment of each (window, row) pair,
-//            window-major (uint16); the window-w segments of row r are
-//            [sfirst[w nrows + r], sfirst[w nrows + r + 1])
-//   seg    : nseg segments in (window, row) order, start | (length - 1) << 13
-//            | row << 19 (uint32); a (window, row) pair's contributions are
-//            cut into segments of at most kSegLen
-//   order  : nseg segment indices (uint16), the work order: window by
-//            window, longest first within a window (window 0's are the first
-//            sfirst[nrows])
+//   sfirst : nrows + 1 first segments (uint16): row r's are
+//            [sfirst[r], sfirst[r + 1])
+//   seg    : nseg segments in row order, start | (length - 1) << 13
+//            | row << 19 (uint32); a row's contributions are cut into
+//            segments of at most kSegLen
+//   order  : nseg segment indices (uint16), the work order: longest first
 //   wseg   : the segments in that order
-//   entry  : nc entries sorted by (window, row): point p of the tile
-//            contributes to that row with its vertex k, as a pair of the
-//            barycentric weight's bits and (p << 5) | k; window w's entries
-//            are contiguous
+//   entry  : nc entries sorted by row: point p of the tile contributes to
+//            that row with its vertex k, as a pair of the barycentric
+//            weight's bits and (p << 5) | k
 //   lrow   : nc rows, point-major: lrow[p * (d+1) + k] (uint16)
 // Fixed-size records; offsets in bytes.
 constexpr int kSegLen = 64;  // at most 64: the length field has 6 bits
@@ -291,16 +285,6 @@ __device__ __forceinline__ void seg_decode(uint32_t sd, int &e0, int &e1, int &r
     e0 = (int)(sd & 0x1fff);
     e1 = e0 + (int)((sd >> 13) & 63) + 1;
     row = (int)(sd >> 19);
-}
-
-// Points per window of a sorted tile: a (window, row) pair's contributions
-// form their own segments, taken window by window.
-#ifndef PAM_SPLAT_WINDOW
-#define PAM_SPLAT_WINDOW 512
-#endif
-__host__ __device__ constexpr int splat_windows(int d)
-{
-    return tile_points(d) > PAM_SPLAT_WINDOW ? tile_points(d) / PAM_SPLAT_WINDOW : 1;
 }
 
 struct TileRec {

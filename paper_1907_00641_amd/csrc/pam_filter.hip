@@ -236,12 +236,12 @@ __device__ __forceinline__ int side_row(const FilterArgs &a, int64_t i, int side
 }
 
 // Phase A: one thread per point stages its barycentric weights and,
-// optionally, its vertex ids, ranks and row (the original index mapped by
-// side_row) in LDS (all from the build's sorted per-point records).
+// optionally, its ranks and row (the original index mapped by side_row) in
+// LDS (all from the build's sorted per-point records).
 template <int D>
 __device__ __forceinline__ void stage_points(const FilterArgs &a, int64_t base, int nt,
-                                             float (*sb)[D + 1], int (*sm)[D + 1],
-                                             signed char (*srank)[D + 1], int *sperm, int side = kRowNatural)
+                                             float (*sb)[D + 1], signed char (*srank)[D + 1], int *sperm,
+                                             int side = kRowNatural)
 {
     constexpr int PW = point_bytes(D) / 4;
     const int t = threadIdx.x;
@@ -261,11 +261,6 @@ __device__ __forceinline__ void stage_points(const FilterArgs &a, int64_t base, 
 #pragma unroll
     for (int k = 0; k <= D; ++k)
         sb[t][k] = __uint_as_float(w[k]);
-    if (sm) {
-#pragma unroll
-        for (int k = 0; k <= D; ++k)
-            sm[t][k] = a.svert[i * (D + 1) + k];
-    }
     if (srank) {
 #pragma unroll
         for (int c = 0; c <= D; ++c)
@@ -375,12 +370,12 @@ __device__ __forceinline__ void copy16(void *dst, const void *src, int bytes)
 
 // Tiles whose vertices did not fit the build's LDS table: each point adds
 // its contributions to the lattice directly (one thread per point).
-//   x row p is scaled by scale[p] when given; with `weights`, the weight
-//   column C gets b * wcol[p] (b when wcol is null).
+//   x row p is scaled by scale[p] when given; the weight column C gets
+//   b * wcol[p] when that is given.
 template <int D, bool AUG = false>
 __device__ __forceinline__ void splat_direct(const FilterArgs &a, int64_t base, int nt, const float (*sb)[D + 1],
                                              const int *sperm, const float *__restrict__ x, const float *scale,
-                                             bool weights, const float *wcol, float *__restrict__ L)
+                                             const float *wcol, float *__restrict__ L)
 {
     const int C = a.c, ld = a.ld;
     for (int p = threadIdx.x; p < nt; p += blockDim.x) {
@@ -401,8 +396,8 @@ __device__ __forceinline__ void splat_direct(const FilterArgs &a, int64_t base, 
             }
             for (int c = 0; c < C; ++c)
                 atomic_add_f32(&row[c], b * sc * xr[c]);
-            if (weights)
-                atomic_add_f32(&row[C], b * (wcol ? wcol[p] : 1.0f));
+            if (wcol)
+                atomic_add_f32(&row[C], b * wcol[p]);
         }
     }
 }
@@ -492,7 +487,6 @@ __global__ __launch_bounds__((splat_rows_threads<D, SCH>())) void k_splat_rows(F
                                                                                float *__restrict__ L)
 {
     constexpr int T = tile_points(D);
-    static_assert(splat_windows(D) == 1, "segments longest first over the whole tile");
     constexpr int NT = splat_rows_threads<D, SCH>(), NW = NT / 64;
     constexpr int GL = SCH / 4, S = SCH == 8 ? 4 : 1;  // lanes per share, shares per segment
     constexpr int GS = GL * S, GPW = 64 / GS;          // lanes per segment, segments per wave
@@ -858,7 +852,7 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
     __shared__ uint16_t lst_s[HA ? NC : 1];  // (point << 5) | k of every entry, for eq. 8's term
     __shared__ __attribute__((aligned(16))) uint32_t seg_s[kTabCap];
     __shared__ __attribute__((aligned(16))) uint16_t order_s[(kTabCap + 7) / 8 * 8];
-    constexpr int kFirstCap = DIRECT ? 1 : 2 * kSegCap + 1;  // (window, row) pairs whose first segments stay in LDS
+    constexpr int kFirstCap = DIRECT ? 1 : kSegCap + 1;  // rows whose first segments stay in LDS: at most a segment each
     __shared__ __attribute__((aligned(16))) uint16_t sfirst_s[(kFirstCap + 7) / 8 * 8];
     __shared__ int next_s;
     __shared__ __attribute__((aligned(16))) int32_t rowid_s[DIRECT ? kXsSegCap : 4];  // DIRECT: lattice row of each tile row
@@ -866,13 +860,11 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
     const TileView tv = tile_view<D>(tiles, blockIdx.x);
     const int nrows = (int)tv.hdr[0], nc = (int)tv.hdr[2], nseg = (int)tv.hdr[3];
     const bool overflow = (tv.hdr[1] & kTileOverflow) != 0;
-    const int nwin = (int)(tv.hdr[1] >> 8);
-    const bool in_lds = nseg <= kTabCap && (DIRECT || nwin * nrows + 1 <= kFirstCap);
+    const bool in_lds = nseg <= kTabCap;
     const int t = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * T;
     const int nt = (int)min((int64_t)T, a.n - base);
     const int C = a.c, ld = a.ld;
-    const bool weights = !AUG && a.normalize != 0;  // weight column: b (plain) or b * gamma
     const float *scale = nullptr, *wcol = nullptr;
     // Set-up: every global load of this phase (the point's record and row,
     // the contributions this thread decodes, its 16-byte pieces of the
@@ -902,7 +894,7 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
         lst[j] = (!overflow && e < nc) ? (uint32_t)tv.entry[e].y : 0u;
     }
     const bool tables = !overflow && in_lds;
-    const int n0 = (nseg * 4 + 15) / 16, n1 = (nseg * 2 + 15) / 16, n2 = ((nwin * nrows + 1) * 2 + 15) / 16;
+    const int n0 = (nseg * 4 + 15) / 16, n1 = (nseg * 2 + 15) / 16, n2 = ((nrows + 1) * 2 + 15) / 16;
     const int n3 = (nrows * 4 + 15) / 16;  // every row has a segment: nrows <= nseg
     uint4 q0, q1, q2, q3;
     if (DIRECT && tables && t < n3)
@@ -938,7 +930,7 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
         wcol = sgam;
     }
     if (overflow) {
-        splat_direct<D, AUG>(a, base, nt, sb, sperm, x, scale, weights, wcol, L);
+        splat_direct<D, AUG>(a, base, nt, sb, sperm, x, scale, wcol, L);
         if constexpr (HA) {  // eq. 8's term of every contribution, 0 without a row of x
             for (int p = t; p < nt; p += (int)blockDim.x) {
                 for (int k = 0; k <= D; ++k) {
@@ -1152,7 +1144,7 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
                     for (int j = 0; j < B; ++j) {
                         bx[j] = e + j < e1 ? __int_as_float(r[j].x) : 0.0f;
                         if constexpr (W)
-                            bw[j] = NORMB ? (e + j < e1 ? recg[min(e + j, e1 - 1)] : 0.0f) : bx[j];
+                            bw[j] = e + j < e1 ? recg[min(e + j, e1 - 1)] : 0.0f;
                     }
                     Vec<VEC> xv[B];
 #pragma unroll
@@ -1223,17 +1215,15 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
                 if (c >= chc)
                     continue;
                 float sum = 0.0f;
-                for (int w = 0; w < nwin; ++w)
-                    for (int sx = sfirst_s[w * nrows + r]; sx < sfirst_s[w * nrows + r + 1]; ++sx)
-                        sum += Ps[sx * SCH + c];
+                for (int sx = sfirst_s[r]; sx < sfirst_s[r + 1]; ++sx)
+                    sum += Ps[sx * SCH + c];
                 atomic_add_f32(&L[(int64_t)tv.rowid[r] * ld + cc + c], sum);
             }
             if constexpr (W) {
                 for (int r = t; r < nrows; r += (int)blockDim.x) {
                     float sum = 0.0f;
-                    for (int w = 0; w < nwin; ++w)
-                        for (int sx = sfirst_s[w * nrows + r]; sx < sfirst_s[w * nrows + r + 1]; ++sx)
-                            sum += Pw[sx];
+                    for (int sx = sfirst_s[r]; sx < sfirst_s[r + 1]; ++sx)
+                        sum += Pw[sx];
                     atomic_add_f32(&L[(int64_t)tv.rowid[r] * ld + C], sum);
                 }
             }
@@ -1319,7 +1309,6 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
     };
     store_x();
     for (int cc = 0; cc < C; cc += SCH) {
-        const bool wpass = weights && cc == 0;
         if (t == 0)
             next_s = 0;
         if (XS && cc > 0) {  // the previous pass ended with a barrier: xs is free
@@ -1332,16 +1321,20 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
                 pass_aug(Flag<true>{}, cc);
             else
                 pass_aug(Flag<false>{}, cc);
-        } else if (in_lds) {
-            if (wpass)
-                pass(Flag<true>{}, Flag<true>{}, cc);
-            else
-                pass(Flag<true>{}, Flag<false>{}, cc);
         } else {
-            if (wpass)
-                pass(Flag<false>{}, Flag<true>{}, cc);
+            auto take = [&](auto in_lds_flag) {
+                if constexpr (NORMB) {
+                    if (cc == 0) {  // with the weight column: b * gamma
+                        pass(in_lds_flag, Flag<true>{}, cc);
+                        return;
+                    }
+                }
+                pass(in_lds_flag, Flag<false>{}, cc);
+            };
+            if (in_lds)
+                take(Flag<true>{});
             else
-                pass(Flag<false>{}, Flag<false>{}, cc);
+                take(Flag<false>{});
         }
         __syncthreads();
     }
@@ -1464,7 +1457,7 @@ __device__ __forceinline__ void stage_slice_points(const FilterArgs &a, const Ti
                                                    int32_t (*sid)[D + 1], signed char (*srank)[D + 1], int *sperm,
                                                    int side = kRowNatural)
 {
-    stage_points<D>(a, base, nt, sb, nullptr, srank, sperm, side);
+    stage_points<D>(a, base, nt, sb, srank, sperm, side);
     const int t = threadIdx.x;
     if (t >= nt)
         return;
@@ -1715,7 +1708,7 @@ __global__ __launch_bounds__(slice_aug_threads(D)) void k_slice_aug(FilterArgs a
     const int nt = (int)min((int64_t)T, a.n - base);
     const int C = a.c, ld = a.ld;
     const float s = a.E.raw_scale;
-    stage_points<D>(a, base, nt, sb, nullptr, nullptr, sperm);  // threads t < nt
+    stage_points<D>(a, base, nt, sb, nullptr, sperm);  // threads t < nt
     if (in_lds) {
         for (int e = t; e < nseg; e += NT) {
             seg_s[e] = tv.seg[e];
