@@ -104,8 +104,8 @@ struct pam_lattice_s {
     // groups of buffers (ensure_group), each with its shared allocation
     DevBuf table_own, table, bkeys, bcount;        // vertex table; bucket table (distinct vertex-0 keys): keys;
                                                    // point counts, then starts
-    DevBuf points_own, place, perm, pts, svert, tiles;  // per point: bucket slot and place within the bucket; the
-                                                        // simplex-sorted order and its tile view
+    DevBuf points_own, place, perm, pts, tiles;  // per point: bucket slot and place within the bucket; the
+                                                 // simplex-sorted order and its tile view
     DevBuf vertex_own, vkeys, nbr;
     DevBuf lat_own, lat[4];
     DevBuf aug_own, aug[3];  // augmented-channel lattices of the embedding gradient
@@ -418,11 +418,10 @@ pam_status_t compact_and_resolve(pam_lattice_s *h, int64_t M_estimate)
     h->zeroed[0] = h->zeroed[2] = 0;
     const int64_t zcap = (int64_t)(std::min(h->lat[0].bytes, h->lat[2].bytes) / sizeof(float));
     PAM_LAUNCH(h, kKResolve,
-               launch_resolve(h->d, h->feat, h->n, h->E, groups_of(h), h->ctl, (const int32_t *)h->perm.ptr,
-                              (const Slot *)h->table.ptr, h->cap,
-                              (uint8_t *)h->tiles.ptr, (int32_t *)h->svert.ptr, (const uint64_t *)h->vkeys.ptr, vcap,
-                              M_estimate, (int32_t *)h->nbr.ptr, (float *)h->lat[0].ptr, (float *)h->lat[2].ptr,
-                              h->last_ld, zcap, (uint64_t *)h->bkeys.ptr, (int32_t *)h->bcount.ptr, h->bcap, s),
+               launch_resolve(h->d, h->n, h->ctl, (const Slot *)h->table.ptr, h->cap, (uint8_t *)h->tiles.ptr,
+                              (const uint64_t *)h->vkeys.ptr, vcap, M_estimate, (int32_t *)h->nbr.ptr,
+                              (float *)h->lat[0].ptr, (float *)h->lat[2].ptr, h->last_ld, zcap,
+                              (uint64_t *)h->bkeys.ptr, (int32_t *)h->bcount.ptr, h->bcap, s),
                "resolve");
     pam_status_t st = await_result(h);
     if (st != PAM_OK)
@@ -460,7 +459,6 @@ pam_status_t build_pass(pam_lattice_s *h, bool allow_fixed)
                            {{&h->place, (size_t)n * sizeof(int2)},
                             {&h->perm, (size_t)n * sizeof(int32_t)},
                             {&h->pts, (size_t)n * point_bytes(h->d)},
-                            {&h->svert, (size_t)n * (h->d + 1) * sizeof(int32_t)},
                             {&h->tiles, (size_t)ntiles * rec.bytes}},
                            "sorted points")) != PAM_OK)
         return st;
@@ -718,7 +716,6 @@ static FilterArgs filter_args(pam_lattice_s *h, int32_t c, uint32_t flags,
 {
     FilterArgs a{};
     a.pts = (const uint8_t *)h->pts.ptr;
-    a.svert = (const int32_t *)h->svert.ptr;
     a.perm = (const int32_t *)h->perm.ptr;
     a.n = h->n;
     a.c = c;
@@ -1152,8 +1149,7 @@ pam_status_t pam_lattice_export(pam_lattice_t lat, int32_t *keys, int32_t *vert,
         PAM_HIP(hipMalloc(&tmp, ib + fb), "export points");
         int32_t *tv = (int32_t *)tmp;
         float *tb = (float *)((char *)tmp + ib);
-        hipError_t e = launch_export_points(d, (const uint8_t *)h->pts.ptr, (const int32_t *)h->svert.ptr,
-                                            (const uint8_t *)h->tiles.ptr,
+        hipError_t e = launch_export_points(d, (const uint8_t *)h->pts.ptr, (const uint8_t *)h->tiles.ptr,
                                             (const int32_t *)h->perm.ptr, n, tv, tb, s);
         if (e == hipSuccess && vert)
             e = hipMemcpyAsync(vert, tv, ib, hipMemcpyDeviceToHost, s);
@@ -1256,7 +1252,7 @@ void pam_lattice_destroy(pam_lattice_t lat)
         for (hipEvent_t e : lat->event_pool)
             (void)hipEventDestroy(e);
         DevBuf *bufs[] = {&lat->table,     &lat->bkeys,      &lat->bcount, &lat->place,
-                          &lat->perm,      &lat->pts,        &lat->svert,      &lat->tiles,  &lat->vkeys,
+                          &lat->perm,      &lat->pts,        &lat->tiles,      &lat->vkeys,
                           &lat->nbr,       &lat->lat[0],     &lat->lat[1],     &lat->lat[2], &lat->lat[3],
                           &lat->table_own, &lat->points_own, &lat->vertex_own, &lat->lat_own, &lat->part,
                           &lat->gstart,    &lat->aug[0],     &lat->aug[1],     &lat->aug[2], &lat->aug_own,

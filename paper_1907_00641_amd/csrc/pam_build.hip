@@ -23,7 +23,6 @@
 // about 330 against 940), so the d+1 keys of a point are deduplicated and
 // inserted once, in the sorted order.
 #include "pam_device.h"
-#include "pam_grid.h"
 
 #include <algorithm>
 
@@ -428,9 +427,8 @@ __global__ void k_unpack_keys(int d, const uint64_t *__restrict__ vkeys, int64_t
 // Per sorted position s: the point's vertex ids and barycentric weights as
 // the filter kernels read them (the sorted records and the tile's rows),
 // written back at the point's original index perm[s].
-__global__ void k_export_points(int d, const uint8_t *__restrict__ pts, const int32_t *__restrict__ svert,
-                                const uint8_t *__restrict__ tiles, const int32_t *__restrict__ perm, int64_t n,
-                                int32_t *vert, float *bary)
+__global__ void k_export_points(int d, const uint8_t *__restrict__ pts, const uint8_t *__restrict__ tiles,
+                                const int32_t *__restrict__ perm, int64_t n, int32_t *vert, float *bary)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n)
@@ -441,12 +439,11 @@ __global__ void k_export_points(int d, const uint8_t *__restrict__ pts, const in
     const int64_t tile = s / rec.T;
     const int p = (int)(s - tile * rec.T);
     const uint8_t *R = tiles + (size_t)tile * rec.bytes;
-    const bool overflow = (reinterpret_cast<const uint32_t *>(R)[1] & kTileOverflow) != 0;
     const int32_t *rowid = reinterpret_cast<const int32_t *>(R + rec.rowid);
     const uint16_t *lrow = reinterpret_cast<const uint16_t *>(R + rec.lrow);
     for (int k = 0; k <= d; ++k) {
         bary[i * (d + 1) + k] = w[k];
-        vert[i * (d + 1) + k] = overflow ? svert[s * (d + 1) + k] : rowid[lrow[p * (d + 1) + k]];
+        vert[i * (d + 1) + k] = rowid[lrow[p * (d + 1) + k]];
     }
 }
 
@@ -624,11 +621,6 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const int2 *__restrict__ pla
     perm[start[sp.x] + sp.y] = (int32_t)i;
 }
 
-// LDS hash of a tile: 2048 slots while a tile has at most 3072
-// contributions (d <= 5 at 512 points), else 4096.
-__host__ __device__ constexpr int tile_hash_bits(int d) { return tile_points(d) * (d + 1) <= 3072 ? 11 : 12; }
-constexpr int kTileProbe = 512;
-
 // Per tile of the sorted order (one thread per point): the point's simplex
 // and barycentric weights from its features; the record of weights and ranks
 // the filter kernels read; the tile's distinct vertices become dense rows
@@ -662,29 +654,30 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     constexpr int NC = T * (D + 1);
     constexpr int PW = point_bytes(D) / 4;
     static_assert(NC < (1 << 13), "segment start and row must fit their 13-bit fields");
-    constexpr int kTileHashBits = tile_hash_bits(D);
-    constexpr int kTileHash = 1 << kTileHashBits;
-    // two uses of one piece of LDS: the hash (local keys, their rows) and the
-    // buckets' keys, until every contribution has its row; then the weights
-    // and the sorted entries, on their way to coalesced stores
-    constexpr int kHashBytes = kTileHash * 4 + kTileHash * 2 + T * 8;
-    constexpr int kEntryBytes = NC * 4 + NC * 2;
+    constexpr int H = tile_slots(D);
+    static_assert(H > NC, "a free slot whatever the keys: every probe ends");
+    // two uses of one piece of LDS.  Until every contribution has its row:
+    // the buckets' keys, the local keys in row order, and the hash (local
+    // keys, their rows).  Then per row the count, then first entry (cnt), and
+    // the first segment (nsg); and the weights and the sorted entries, on
+    // their way to coalesced stores.
+    constexpr int kCntBytes = (NC + 4) * 4, kNsgBytes = (NC + 8) * 2;
+    constexpr int kHashBytes = T * 8 + NC * 4 + H * 4 + H * 2;
+    constexpr int kEntryBytes = kCntBytes + kNsgBytes + NC * 4 + NC * 2;
     __shared__ __attribute__((aligned(16))) uint8_t pool[kHashBytes > kEntryBytes ? kHashBytes : kEntryBytes];
     uint64_t *bkey = reinterpret_cast<uint64_t *>(pool);
-    uint32_t *hkey = reinterpret_cast<uint32_t *>(pool + T * 8);
-    uint16_t *hrow = reinterpret_cast<uint16_t *>(pool + T * 8 + kTileHash * 4);
-    float *sw = reinterpret_cast<float *>(pool);
-    uint16_t *slist = reinterpret_cast<uint16_t *>(pool + NC * 4);
-    // per row: count, then first entry (cnt), and segment count, then first
-    // segment (nsg); before that the local keys in row order
-    __shared__ int cnt[kTileHash + 1];
-    __shared__ int nsg[kTileHash + 1];
-    uint32_t *rkey = reinterpret_cast<uint32_t *>(cnt);
+    uint32_t *rkey = reinterpret_cast<uint32_t *>(pool + T * 8);
+    uint32_t *hkey = rkey + NC;
+    uint16_t *hrow = reinterpret_cast<uint16_t *>(hkey + H);
+    int *cnt = reinterpret_cast<int *>(pool);
+    uint16_t *nsg = reinterpret_cast<uint16_t *>(pool + kCntBytes);
+    float *sw = reinterpret_cast<float *>(pool + kCntBytes + kNsgBytes);
+    uint16_t *slist = reinterpret_cast<uint16_t *>(sw + NC);
     __shared__ int hist[kSegLen + 1];
     __shared__ int wsum[2 * (T / 64 + 1)];
     __shared__ uint64_t last_s[NW];
     __shared__ int starts_s[NW];
-    __shared__ int nrows_s, overflow_s, full_s;
+    __shared__ int nrows_s, full_s;
     __shared__ uint32_t added_s;
     if (ctl->flags & ~kFlagTableFull)  // set by other blocks of this launch: TableFull only
         return;
@@ -706,13 +699,12 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     int2 *entry = reinterpret_cast<int2 *>(R + rec.entry);
     const bool valid = t < nt;
     const int64_t i = valid ? perm[base + t] : 0;
-    for (int e = t; e < kTileHash; e += T)
+    for (int e = t; e < H; e += T)
         hkey[e] = ~0u;
     for (int e = t; e <= kSegLen; e += T)
         hist[e] = 0;
     if (t == 0) {
         nrows_s = 0;
-        overflow_s = 0;
         full_s = 0;
         added_s = 0;
     }
@@ -783,64 +775,51 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
             lkey |= 1u << c;
         }
         run[k] = lane_run32(lkey, valid);
-        int found = -1;
+        uint32_t h = 0;
         if (valid && run[k].lead == lane) {
-            uint32_t h = (lkey * 2654435761u) >> (32 - kTileHashBits);
-            for (int probe = 0; probe < kTileProbe; ++probe) {
+            h = tile_hash(lkey, H);
+            for (;;) {  // at most NC of the H slots are ever taken: ends at the key or an empty slot
                 const uint32_t was = atomicCAS(&hkey[h], ~0u, lkey);
                 if (was == ~0u) {
                     const int r = atomicAdd(&nrows_s, 1);
                     hrow[h] = (uint16_t)r;
                     rkey[r] = lkey;
-                    found = (int)h;
                     break;
                 }
-                if (was == lkey) {
-                    found = (int)h;
+                if (was == lkey)
                     break;
-                }
-                h = (h + 1) & (kTileHash - 1);
+                h = h + 1 < (uint32_t)H ? h + 1 : 0;
             }
         }
-        found = __shfl(found, run[k].lead);
-        slot[k] = found;
-        if (valid && found < 0)
-            overflow_s = 1;
+        slot[k] = __shfl((int)h, run[k].lead);
     }
     __syncthreads();
     const int nrows = nrows_s;
     uint32_t added = 0;
     bool full = false;
-    if (overflow_s) {
-        // no room to deduplicate: every key of the tile goes to the table,
-        // and the resolve looks the points' ids up one by one
-        if (valid) {
-            const uint64_t gfield = group_field(grp, lay, i);
+    // each distinct key's slot, for the resolve; -1 when it does not fit an
+    // int32 (the resolve then looks the key up)
+    for (int r = t; r < nrows; r += T) {
+        const uint32_t lk = rkey[r];
+        // vertex k: the bucket's vertex 0 plus k, minus 1 in the field of
+        // every stepped-down coordinate (coordinate d has no field)
+        uint64_t kr = bkey[lk >> (D + 1)] + (uint32_t)__popc(lk & ((2u << D) - 1));
 #pragma unroll
-            for (int k = 0; k <= D; ++k)
-                table_insert<2>(reinterpret_cast<uint64_t *>(table), mask, pack_vertex<D>(s, k, lay, gfield), added, full);
-        }
-    } else {
-        // each distinct key's slot, for the resolve; -1 when it does not fit
-        // an int32 (the resolve then looks the key up)
-        for (int r = t; r < nrows; r += T) {
-            const uint32_t lk = rkey[r];
-            // vertex k: the bucket's vertex 0 plus k, minus 1 in the field of
-            // every stepped-down coordinate (coordinate d has no field)
-            uint64_t kr = bkey[lk >> (D + 1)] + (uint32_t)__popc(lk & ((2u << D) - 1));
-#pragma unroll
-            for (int c = 0; c < D; ++c)
-                kr -= (uint64_t)((lk >> c) & 1) << lay.shift[c];
-            const uint64_t h = table_insert<2>(reinterpret_cast<uint64_t *>(table), mask, kr, added, full);
-            rowkey[r] = kr;
-            rowid[r] = h <= 0x7fffffffull ? (int32_t)h : -1;
-        }
+        for (int c = 0; c < D; ++c)
+            kr -= (uint64_t)((lk >> c) & 1) << lay.shift[c];
+        const uint64_t h = table_insert<2>(reinterpret_cast<uint64_t *>(table), mask, kr, added, full);
+        rowkey[r] = kr;
+        rowid[r] = h <= 0x7fffffffull ? (int32_t)h : -1;
     }
+    int q[D + 1], pos[D + 1];
+#pragma unroll
+    for (int k = 0; k <= D; ++k)
+        q[k] = valid ? (int)hrow[slot[k]] : 0;
     if (added)
         atomicAdd(&added_s, added);
     if (full)
         full_s = 1;
-    __syncthreads();  // rkey is dead from here: its LDS takes the counters
+    __syncthreads();  // the keys and the hash are dead from here: their LDS takes the counters and entries
     if (t == 0) {
         // the count's result is not needed here (the compaction compares the
         // final count with the load limit), so the add does not return
@@ -849,22 +828,11 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
         if (full_s)
             atomicOr(&ctl->flags, kFlagTableFull);
     }
-    if (overflow_s) {
-        if (t == 0) {
-            hdr[0] = 0;
-            hdr[1] = kTileOverflow;
-            hdr[2] = (uint32_t)nc;
-            hdr[3] = 0;
-        }
-        return;
-    }
     for (int e = t; e < nrows; e += T)
         cnt[e] = 0;
     __syncthreads();
-    int q[D + 1], pos[D + 1];
 #pragma unroll
     for (int k = 0; k <= D; ++k) {
-        q[k] = valid ? (int)hrow[slot[k]] : 0;
         int first_pos = 0;
         if (valid && run[k].lead == lane)
             first_pos = atomicAdd(&cnt[q[k]], run[k].len);
@@ -882,7 +850,7 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
                 lrow[t * (D + 1) + k] = (uint16_t)q[k];
         }
     }
-    __syncthreads();  // hkey, hrow and bkey are dead from here: their LDS takes the entries
+    __syncthreads();
     // cnt[r]: first entry of row r; nsg[r]: its first segment
     const int nseg = block_exclusive_scan_ceil(cnt, nsg, nrows, kSegLen, wsum);
     if (valid) {
@@ -960,8 +928,7 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
 //   wave's trips became the launch's tail: 40x36x28 points, d = 12, launch
 //   181 us with one wave per tile): the slot of each row's key becomes its
 //   vertex id (kResolveRows rows per lane requested together: slots, then
-//   ids); a tile that overflowed its LDS table looks up its points' keys one
-//   by one and writes their ids to svert;
+//   ids);
 // * the neighbour table, one vertex of one direction per thread and trip;
 // * clears: the first M * zld floats of z0 and z1 (the lattice buffers the
 //   next filter calls splat into, zcap floats each, so that those calls
@@ -974,10 +941,8 @@ static_assert(kBlock == kGridBlock, "the neighbour blocks' arithmetic");
 __host__ __device__ constexpr int resolve_waves(int d) { return d <= 8 ? 1 : 4; }
 
 template <int D>
-__global__ __launch_bounds__(kBlock) void k_resolve(const float *__restrict__ feat, int64_t n, Elev E, Groups64 grp,
-                                                    Ctl *ctl, const int32_t *__restrict__ perm,
-                                                    const Slot *__restrict__ table, uint64_t mask,
-                                                    uint8_t *__restrict__ tiles, int32_t *__restrict__ svert,
+__global__ __launch_bounds__(kBlock) void k_resolve(int64_t n, Ctl *ctl, const Slot *__restrict__ table,
+                                                    uint64_t mask, uint8_t *__restrict__ tiles,
                                                     const uint64_t *__restrict__ vkeys, uint32_t vcap,
                                                     int32_t *__restrict__ nbr, unsigned tile_blocks,
                                                     unsigned nbr_blocks, float *__restrict__ z0,
@@ -1001,20 +966,6 @@ __global__ __launch_bounds__(kBlock) void k_resolve(const float *__restrict__ fe
             return;
         uint8_t *R = tiles + (size_t)tile * rec.bytes;
         const uint32_t *hdr = reinterpret_cast<const uint32_t *>(R);
-        if (hdr[1] & kTileOverflow) {
-            const int64_t base = tile * T;
-            const int nt = (int)min((int64_t)T, n - base);
-            for (int p = part; p < nt; p += 64 * W) {
-                const int64_t i = perm[base + p];
-                Simplex<D> s;
-                embed<D>(feat + i * D, E, s);
-                const uint64_t gfield = group_field(grp, lay, i);
-                for (int k = 0; k <= D; ++k)
-                    svert[(base + p) * (D + 1) + k] =
-                        max(probe_id(table, mask, pack_vertex<D>(s, k, lay, gfield)), 0);
-            }
-            return;
-        }
         int32_t *rowid = reinterpret_cast<int32_t *>(R + rec.rowid);
         const uint64_t *rowkey = reinterpret_cast<const uint64_t *>(R + rec.rowkey);
         const int nrows = (int)hdr[0];
@@ -1199,9 +1150,8 @@ hipError_t launch_compact(Slot *table, uint64_t *vkeys, uint32_t vcap, uint64_t 
     return hipGetLastError();
 }
 
-hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
-                          const int32_t *perm, const Slot *table, uint64_t cap,
-                          uint8_t *tiles, int32_t *svert, const uint64_t *vkeys, uint32_t vcap, int64_t M_estimate,
+hipError_t launch_resolve(int d, int64_t n, Ctl *ctl, const Slot *table, uint64_t cap, uint8_t *tiles,
+                          const uint64_t *vkeys, uint32_t vcap, int64_t M_estimate,
                           int32_t *nbr, float *z0, float *z1, int32_t zld, int64_t zcap, uint64_t *bkeys,
                           int32_t *bcount, uint64_t bcap, hipStream_t s)
 {
@@ -1217,19 +1167,17 @@ hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, co
     const int64_t pieces = std::max<int64_t>(M_estimate * zld / 4, (int64_t)(bcap / 2));
     const int64_t clear_blocks = std::min<int64_t>((pieces + kBlock - 1) / kBlock, 4096);
     PAM_DISPATCH_D(d, hipLaunchKernelGGL(k_resolve<D>, dim3((unsigned)(tile_blocks + nbr_blocks + clear_blocks)),
-                                         dim3(kBlock), 0, s, feat, n, E, grp, ctl, perm, table, cap - 1, tiles,
-                                         svert, vkeys, vcap, nbr, (unsigned)tile_blocks, (unsigned)nbr_blocks, z0, z1,
+                                         dim3(kBlock), 0, s, n, ctl, table, cap - 1, tiles, vkeys, vcap, nbr, (unsigned)tile_blocks, (unsigned)nbr_blocks, z0, z1,
                                          zld, zcap, bkeys, bcount, bcap));
     return hipGetLastError();
 }
 
-hipError_t launch_export_points(int d, const uint8_t *pts, const int32_t *svert, const uint8_t *tiles,
-                                const int32_t *perm, int64_t n, int32_t *vert, float *bary, hipStream_t s)
+hipError_t launch_export_points(int d, const uint8_t *pts, const uint8_t *tiles, const int32_t *perm, int64_t n,
+                                int32_t *vert, float *bary, hipStream_t s)
 {
     if (n <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL(k_export_points, dim3(blocks_for(n)), dim3(kBlock), 0, s, d, pts, svert, tiles, perm, n, vert,
-                       bary);
+    hipLaunchKernelGGL(k_export_points, dim3(blocks_for(n)), dim3(kBlock), 0, s, d, pts, tiles, perm, n, vert, bary);
     return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 // fixed operation order, barycentric weights, key hashing.
 #pragma once
 
+#include "pam_grid.h"
 #include "pam_internal.h"
 
 #include <climits>
@@ -216,16 +217,6 @@ namespace pam {
 // one block (one thread per point) per tile.
 // ---------------------------------------------------------------------------
 
-#ifndef PAM_TILE_POINTS
-#define PAM_TILE_POINTS 512
-#endif
-#ifndef PAM_TILE_BIG_D
-#define PAM_TILE_BIG_D 5  // largest d with PAM_TILE_POINTS-point tiles
-#endif
-#ifndef PAM_TILE_POINTS_HIGH_D
-#define PAM_TILE_POINTS_HIGH_D 256  // tile points above PAM_TILE_BIG_D
-#endif
-
 // Tile order of the hash-table insert.  The hardware hands blocks to the 8
 // XCDs in turn (block b to XCD b mod 8), each with its own L2.  Here each
 // XCD takes a contiguous range of tiles instead, so that the table lines
@@ -249,16 +240,9 @@ __device__ __forceinline__ int64_t insert_tile(int64_t ntiles)
     return PAM_XCD_INSERT ? xcd_tile(blockIdx.x, ntiles) : (int64_t)blockIdx.x;
 }
 
-__host__ __device__ constexpr int tile_points(int d)
-{
-    return d <= PAM_TILE_BIG_D ? PAM_TILE_POINTS
-                               : (PAM_TILE_POINTS < PAM_TILE_POINTS_HIGH_D ? PAM_TILE_POINTS : PAM_TILE_POINTS_HIGH_D);
-}
-
 // Per-tile view of the lattice, for the tiles of the simplex-sorted order.
 // With nc = (points in the tile) * (d+1):
-//   hdr    : nrows; flags (bit 0: the tile's vertices did not fit the LDS
-//            dedup table, then only the per-point ids are valid); nc; nseg
+//   hdr    : nrows; 0; nc; nseg
 //   rowid  : nrows global vertex ids, one per distinct vertex of the tile
 //            (slots of the vertex table until the resolve)
 //   rowkey : nrows packed keys of those vertices (uint64)
@@ -305,8 +289,6 @@ struct TileRec {
         bytes = (entry + (size_t)NC * 8 + 255) & ~(size_t)255;
     }
 };
-
-constexpr uint32_t kTileOverflow = 1u;
 
 // Per-point simplex record in sorted order: the d+1 barycentric weights
 // (fp32) followed by the d+1 ranks (int8), padded to 16 bytes.
@@ -401,8 +383,9 @@ __device__ __forceinline__ int block_exclusive_scan(int *cnt, int count, int *ws
 
 // One pass over cnt[0..count): cnt becomes its exclusive prefix sum and
 // nsg the exclusive prefix sum of ceil(cnt / len).  wsum holds
-// 2 * (blockDim.x / 64 + 1) ints.  Returns the sum of ceil(cnt / len).
-__device__ __forceinline__ int block_exclusive_scan_ceil(int *cnt, int *nsg, int count, int len, int *wsum)
+// 2 * (blockDim.x / 64 + 1) ints.  Returns the sum of ceil(cnt / len), which
+// must be below 2^16.
+__device__ __forceinline__ int block_exclusive_scan_ceil(int *cnt, uint16_t *nsg, int count, int len, int *wsum)
 {
     const int T = blockDim.x, t = threadIdx.x, NW = T / 64;
     const int per = (count + T - 1) / T;
@@ -444,7 +427,7 @@ __device__ __forceinline__ int block_exclusive_scan_ceil(int *cnt, int *nsg, int
     for (int i = beg; i < end; ++i) {
         const int c = cnt[i];
         cnt[i] = excl;
-        nsg[i] = exg;
+        nsg[i] = (uint16_t)exg;
         excl += c;
         exg += (c + len - 1) / len;
     }

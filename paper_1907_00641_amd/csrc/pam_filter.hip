@@ -368,62 +368,6 @@ __device__ __forceinline__ void copy16(void *dst, const void *src, int bytes)
         reinterpret_cast<uint4 *>(dst)[e] = reinterpret_cast<const uint4 *>(src)[e];
 }
 
-// Tiles whose vertices did not fit the build's LDS table: each point adds
-// its contributions to the lattice directly (one thread per point).
-//   x row p is scaled by scale[p] when given; the weight column C gets
-//   b * wcol[p] when that is given.
-template <int D, bool AUG = false>
-__device__ __forceinline__ void splat_direct(const FilterArgs &a, int64_t base, int nt, const float (*sb)[D + 1],
-                                             const int *sperm, const float *__restrict__ x, const float *scale,
-                                             const float *wcol, float *__restrict__ L)
-{
-    const int C = a.c, ld = a.ld;
-    for (int p = threadIdx.x; p < nt; p += blockDim.x) {
-        if (sperm[p] < 0)
-            continue;
-        const float sc = scale ? scale[p] : 1.0f;
-        const float *xr = x + (int64_t)sperm[p] * C;
-        for (int k = 0; k <= D; ++k) {
-            const int m = a.svert[(base + p) * (D + 1) + k];
-            const float b = sb[p][k];
-            float *row = L + (int64_t)m * ld;
-            if constexpr (AUG) {
-                const float *fr = a.feat + (int64_t)sperm[p] * D;
-                for (int q = 0; q < D; ++q)
-                    for (int c = 0; c < C; ++c)
-                        atomic_add_f32(&row[q * C + c], b * fr[q] * xr[c]);
-                continue;
-            }
-            for (int c = 0; c < C; ++c)
-                atomic_add_f32(&row[c], b * sc * xr[c]);
-            if (wcol)
-                atomic_add_f32(&row[C], b * wcol[p]);
-        }
-    }
-}
-
-// The same straight from the points' records, for plain rows.
-template <int D>
-__device__ __forceinline__ void splat_points(const FilterArgs &a, int64_t base, int nt, const float *__restrict__ x,
-                                             bool weights, float *__restrict__ L)
-{
-    const int C = a.c, ld = a.ld;
-    for (int p = threadIdx.x; p < nt; p += blockDim.x) {
-        const int r = side_row(a, a.perm[base + p], a.side);
-        if (r < 0)
-            continue;
-        const float *b = reinterpret_cast<const float *>(a.pts + (base + p) * point_bytes(D));
-        const float *xr = x + (int64_t)r * C;
-        for (int k = 0; k <= D; ++k) {
-            float *row = L + (int64_t)a.svert[(base + p) * (D + 1) + k] * ld;
-            for (int c = 0; c < C; ++c)
-                atomic_add_f32(&row[c], b[k] * xr[c]);
-            if (weights)
-                atomic_add_f32(&row[C], b[k]);
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Splat of plain rows: L[m] += sum over the tile's points of b_k x
 // (forward, and the raw backward splat of dL/dv').
@@ -518,11 +462,6 @@ __global__ __launch_bounds__((splat_rows_threads<D, SCH>())) void k_splat_rows(F
     constexpr int kLast = T * (D + 1) - 1;  // the record's last segment place
     uint32_t sd = tv.wseg[min(first + gw, kLast)], sdn = tv.wseg[min(first + step + gw, kLast)];
     const int nseg = (int)tv.hdr[3];
-    if (tv.hdr[1] & kTileOverflow) {  // block-uniform
-        if (blockIdx.y == 0 && blockIdx.z == 0)
-            splat_points<D>(a, base, nt, x, W, L);
-        return;
-    }
     Vec<VEC> xv[NI];
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -707,7 +646,6 @@ __device__ __forceinline__ void norm_bwd_prologue(const FilterArgs &a, const Til
     constexpr int GL = SCH / VEC;
     const int l = threadIdx.x & (GL - 1), q = threadIdx.x / GL, ng = blockDim.x / GL;
     const int C = a.c, ld = a.ld, nrows = (int)tv.hdr[0];
-    const bool ovf = (tv.hdr[1] & kTileOverflow) != 0;
     auto chunk = [&](auto staged_flag, int cc) {
         constexpr bool S = decltype(staged_flag)::value;
         // uniform trip count for the whole block; the group reduction below
@@ -719,8 +657,8 @@ __device__ __forceinline__ void norm_bwd_prologue(const FilterArgs &a, const Til
             int m[D + 1];
 #pragma unroll
             for (int k = 0; k <= D; ++k)
-                m[k] = S || !ovf ? (int)tv.lrow[pc * (D + 1) + k] : a.svert[(base + pc) * (D + 1) + k];
-            if (!S && !ovf) {
+                m[k] = (int)tv.lrow[pc * (D + 1) + k];
+            if (!S) {
 #pragma unroll
                 for (int k = 0; k <= D; ++k)
                     m[k] = tv.rowid[m[k]];
@@ -859,7 +797,6 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
 
     const TileView tv = tile_view<D>(tiles, blockIdx.x);
     const int nrows = (int)tv.hdr[0], nc = (int)tv.hdr[2], nseg = (int)tv.hdr[3];
-    const bool overflow = (tv.hdr[1] & kTileOverflow) != 0;
     const bool in_lds = nseg <= kTabCap;
     const int t = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * T;
@@ -891,19 +828,18 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int e = t + j * T;
-        lst[j] = (!overflow && e < nc) ? (uint32_t)tv.entry[e].y : 0u;
+        lst[j] = e < nc ? (uint32_t)tv.entry[e].y : 0u;
     }
-    const bool tables = !overflow && in_lds;
     const int n0 = (nseg * 4 + 15) / 16, n1 = (nseg * 2 + 15) / 16, n2 = ((nrows + 1) * 2 + 15) / 16;
     const int n3 = (nrows * 4 + 15) / 16;  // every row has a segment: nrows <= nseg
     uint4 q0, q1, q2, q3;
-    if (DIRECT && tables && t < n3)
+    if (DIRECT && in_lds && t < n3)
         q3 = reinterpret_cast<const uint4 *>(tv.rowid)[t];
-    if (tables && t < n0)
+    if (in_lds && t < n0)
         q0 = reinterpret_cast<const uint4 *>(tv.seg)[t];
-    if (tables && t < n1)
+    if (in_lds && t < n1)
         q1 = reinterpret_cast<const uint4 *>(tv.order)[t];
-    if (!DIRECT && tables && t < n2)
+    if (!DIRECT && in_lds && t < n2)
         q2 = reinterpret_cast<const uint4 *>(tv.sfirst)[t];
     if (t < nt) {
 #pragma unroll
@@ -911,7 +847,7 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
             sb[t][k] = __uint_as_float(w[k]);
         sperm[t] = prow;
     }
-    if (tables) {
+    if (in_lds) {
         if (t < n0)
             reinterpret_cast<uint4 *>(seg_s)[t] = q0;
         if (t < n1)
@@ -923,29 +859,11 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
     }
     __syncthreads();
     if constexpr (NORMB) {
-        const bool staged = !overflow && nrows <= kSliceRows;
+        const bool staged = nrows <= kSliceRows;
         norm_bwd_prologue<D, VEC, SCH>(a, tv, staged, rowsA, wrowA, base, nt, sb, sperm, x, A, sz, sgam);
         __syncthreads();
         scale = sz;
         wcol = sgam;
-    }
-    if (overflow) {
-        splat_direct<D, AUG>(a, base, nt, sb, sperm, x, scale, wcol, L);
-        if constexpr (HA) {  // eq. 8's term of every contribution, 0 without a row of x
-            for (int p = t; p < nt; p += (int)blockDim.x) {
-                for (int k = 0; k <= D; ++k) {
-                    float h = 0.0f;
-                    if (sperm[p] >= 0) {
-                        const float *xr = x + (int64_t)sperm[p] * C;
-                        const float *Am = A + (int64_t)a.svert[(base + p) * (D + 1) + k] * ld;
-                        for (int c = 0; c < C; ++c)
-                            h += xr[c] * Am[c];
-                    }
-                    hA[(base + p) * (D + 1) + k] = h;
-                }
-            }
-        }
-        return;
     }
     // XS: thread t's point's row of x, channels [cc, cc + SCH) (zeros past
     // C and for points without a row), requested before the decode so that
@@ -1449,8 +1367,7 @@ __global__ __launch_bounds__(kBlock) void k_blur2(const float *__restrict__ in, 
 // Phase A of the slice kernels: weights, original index, ranks (when
 // asked) and rows of each point's vertices: tile-local (slr) when the tile's
 // rows are staged, else global vertex ids (sid, in LDS the staged rows do
-// not use then), from the tile's row ids or, for a tile that overflowed the
-// build's LDS table, from the points' own ids.
+// not use then).
 template <int D>
 __device__ __forceinline__ void stage_slice_points(const FilterArgs &a, const TileView &tv, bool staged, int64_t base,
                                                    int nt, float (*sb)[D + 1], uint16_t (*slr)[D + 1],
@@ -1461,12 +1378,6 @@ __device__ __forceinline__ void stage_slice_points(const FilterArgs &a, const Ti
     const int t = threadIdx.x;
     if (t >= nt)
         return;
-    if (tv.hdr[1] & kTileOverflow) {  // block-uniform
-#pragma unroll
-        for (int k = 0; k <= D; ++k)
-            sid[t][k] = a.svert[(base + t) * (D + 1) + k];
-        return;
-    }
     int r[D + 1];
 #pragma unroll
     for (int k = 0; k <= D; ++k)
@@ -1571,9 +1482,8 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice(FilterArgs a, const uint8_
     __shared__ __attribute__((aligned(16))) float rows[kFloats];
     const TileView tv = tile_view<D>(tiles, blockIdx.x);
     const int nrows = (int)tv.hdr[0];
-    const bool ovf = (tv.hdr[1] & kTileOverflow) != 0;
     const int C = a.c, ld = a.ld;
-    const bool full = !ovf && nrows <= RS;
+    const bool full = nrows <= RS;
     const int64_t base = (int64_t)blockIdx.x * T;
     const int nt = (int)min((int64_t)T, a.n - base);
     int32_t(*sid)[D + 1] = reinterpret_cast<int32_t(*)[D + 1]>(rows);
@@ -1655,8 +1565,7 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice(FilterArgs a, const uint8_
 // map from (point, vertex) to entry.
 // Slots hold NVC values (all d+1 unless the tile's slots would not fit
 // LDS; then the values are taken NVC at a time, g and v re-gathered per
-// chunk).  Tiles whose vertices overflowed the build's table take a
-// thread-per-point path from global memory.
+// chunk).
 // ---------------------------------------------------------------------------
 __host__ __device__ constexpr int slice_aug_threads(int d) { return d <= PAM_TILE_BIG_D ? 1024 : 512; }
 __host__ __device__ constexpr int slice_aug_nvc(int d)
@@ -1701,8 +1610,7 @@ __global__ __launch_bounds__(slice_aug_threads(D)) void k_slice_aug(FilterArgs a
 
     const TileView tv = tile_view<D>(tiles, blockIdx.x);
     const int nrows = (int)tv.hdr[0], nc = (int)tv.hdr[2], nseg = (int)tv.hdr[3];
-    const bool overflow = (tv.hdr[1] & kTileOverflow) != 0;
-    const bool in_lds = !overflow && nseg <= kTab;
+    const bool in_lds = nseg <= kTab;
     const int t = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * T;
     const int nt = (int)min((int64_t)T, a.n - base);
@@ -1718,33 +1626,6 @@ __global__ __launch_bounds__(slice_aug_threads(D)) void k_slice_aug(FilterArgs a
             rowid_s[e] = tv.rowid[e];
     }
     __syncthreads();
-    if (overflow) {
-        // a thread per point, every row read from global memory
-        for (int p = t; p < nt; p += NT) {
-            const int64_t row = sperm[p];
-            if (row < 0)
-                continue;
-            float hq[D], h0 = 0.0f;
-#pragma unroll
-            for (int q = 0; q < D; ++q)
-                hq[q] = 0.0f;
-            for (int k = 0; k <= D; ++k) {
-                const int64_t m = a.svert[(base + p) * (D + 1) + k];
-                const float b = sb[p][k];
-                for (int c = 0; c < C; ++c) {
-                    const float gc = b * grad[row * C + c], vc = b * val[row * C + c];
-                    h0 += gc * A[m * ld + c] + vc * At[m * ld + c];
-#pragma unroll
-                    for (int q = 0; q < D; ++q)
-                        hq[q] += gc * L1[m * ldq + q * C + c] + vc * L2[m * ldq + q * C + c];
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < D; ++q)
-                grad_feat[row * D + q] = s * (hq[q] - a.feat[row * D + q] * h0);
-        }
-        return;
-    }
     // decode every contribution once: its weight (0 for a point without a
     // row) and row; its slot is its entry
     for (int e = t; e < nc; e += NT) {
@@ -1975,7 +1856,7 @@ __global__ __launch_bounds__(Tile<D>::T) void k_slice_bwd(FilterArgs a, const ui
     const int nrows = (int)tv.hdr[0];
     const int C = a.c, ld = a.ld;
     // the tile's rows are staged (all C channels at once) when they fit
-    const bool full = !(tv.hdr[1] & kTileOverflow) && C <= CH && nrows <= RB;
+    const bool full = C <= CH && nrows <= RB;
     const int64_t base = (int64_t)blockIdx.x * T;
     const int nt = (int)min((int64_t)T, a.n - base);
     const float sc = NORM ? 1.0f : a.E.raw_scale;

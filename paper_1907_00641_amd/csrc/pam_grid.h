@@ -1,6 +1,7 @@
-// Launch geometry of the build kernels whose extent is a vertex or table
-// count rather than the points': plain arithmetic, used by the kernels and by
-// the host that sizes their grids.
+// Sizes of the tiles and of their LDS hash, and the launch geometry of the
+// build kernels whose extent is a vertex or table count rather than the
+// points': plain arithmetic, used by the kernels and by the host that sizes
+// their buffers and grids.
 //
 // A launch may have fewer than 2^32 work items per dimension, and a lattice
 // may have up to 2^31 - 1 vertices, so M (d+1) neighbour items, or a table's
@@ -11,6 +12,38 @@
 #include <stdint.h>
 
 namespace pam {
+
+#ifndef PAM_TILE_POINTS
+#define PAM_TILE_POINTS 512
+#endif
+#ifndef PAM_TILE_BIG_D
+#define PAM_TILE_BIG_D 5  // largest d with PAM_TILE_POINTS-point tiles
+#endif
+#ifndef PAM_TILE_POINTS_HIGH_D
+#define PAM_TILE_POINTS_HIGH_D 256  // tile points above PAM_TILE_BIG_D
+#endif
+constexpr int tile_points(int d)
+{
+    return d <= PAM_TILE_BIG_D ? PAM_TILE_POINTS
+                               : (PAM_TILE_POINTS < PAM_TILE_POINTS_HIGH_D ? PAM_TILE_POINTS : PAM_TILE_POINTS_HIGH_D);
+}
+
+// Slots of a tile's LDS hash: at least an eighth more than its contributions,
+// so that every tile has room for its rows, whatever its points, and as many
+// as fit the LDS that the tile's sorted entries take later (d >= 6).  With
+// 2048 slots up to d = 11 and 4096 above, tiles of scattered points did not
+// fit and went on without rows: 1000 points, d = 5, 16 channels 559 us per
+// step (120 with room), 40x36x28 points, d = 11, 24 channels 2227 us (580).
+constexpr int tile_slots(int d)
+{
+    const int least = tile_points(d) * (d + 1) / 8 * 9, room = tile_points(d) * d / 3 * 4;
+    return room > least ? room : least;
+}
+// first slot probed for a local key
+constexpr uint32_t tile_hash(uint32_t lkey, uint32_t slots)
+{
+    return (uint32_t)(((uint64_t)(uint32_t)(lkey * 2654435761u) * slots) >> 32);
+}
 
 constexpr int kGridBlock = 256;  // threads per block of the resolve launch
 

@@ -123,7 +123,6 @@ const char *kernel_name(int32_t kind);
 // simplex-sorted point order
 struct FilterArgs {
     const uint8_t *pts;    // per sorted point: barycentric weights and ranks
-    const int32_t *svert;  // per sorted point: its d+1 vertex ids (tiles that overflowed their LDS table only)
     const int32_t *perm;   // per sorted point: its index in the caller's arrays
     int64_t n;
     int32_t c;       // value channels
@@ -191,9 +190,8 @@ hipError_t launch_compact(Slot *table, uint64_t *vkeys, uint32_t vcap, uint64_t 
 // else nothing is done), and the clears for the calls that follow: M * zld
 // floats of z0 and z1 when they hold them (zcap), the bucket table, ctl's
 // flags and counters.  M_estimate sizes the launch only.
-hipError_t launch_resolve(int d, const float *feat, int64_t n, const Elev &E, const Groups64 &grp, Ctl *ctl,
-                          const int32_t *perm, const Slot *table, uint64_t cap,
-                          uint8_t *tiles, int32_t *svert, const uint64_t *vkeys, uint32_t vcap, int64_t M_estimate,
+hipError_t launch_resolve(int d, int64_t n, Ctl *ctl, const Slot *table, uint64_t cap, uint8_t *tiles,
+                          const uint64_t *vkeys, uint32_t vcap, int64_t M_estimate,
                           int32_t *nbr, float *z0, float *z1, int32_t zld, int64_t zcap, uint64_t *bkeys,
                           int32_t *bcount, uint64_t bcap, hipStream_t s);
 // x onto L.  mode: kSplatModePlain (forward, or backward raw),
@@ -224,8 +222,8 @@ hipError_t launch_slice_aug(int d, const FilterArgs &a, const uint8_t *tiles, co
                             const float *A, const float *At, const float *L1, const float *L2, int32_t ldq,
                             float *grad_feat, hipStream_t s);
 // per-point vertex ids and weights from the sorted records, in the caller's order
-hipError_t launch_export_points(int d, const uint8_t *pts, const int32_t *svert, const uint8_t *tiles,
-                                const int32_t *perm, int64_t n, int32_t *vert, float *bary, hipStream_t s);
+hipError_t launch_export_points(int d, const uint8_t *pts, const uint8_t *tiles, const int32_t *perm, int64_t n,
+                                int32_t *vert, float *bary, hipStream_t s);
 hipError_t launch_unpack_keys(int d, const uint64_t *vkeys, int64_t M, const Ctl *ctl,
                               int32_t *keys, hipStream_t s);
 hipError_t launch_vertex_groups(const uint64_t *vkeys, int64_t M, const Ctl *ctl, int32_t *vgroup, hipStream_t s);

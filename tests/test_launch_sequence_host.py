@@ -124,6 +124,55 @@ int main()
     assert r.returncode == 0, r.stdout
 
 
+def test_tile_hash_holds_every_row(tmp_path):
+    """A tile's LDS hash has room for as many rows as contributions, with
+    probes of bounded length: tiles of points that share no bucket, whose
+    vertices step down the coordinates in random orders."""
+    src = tmp_path / "hash.cpp"
+    src.write_text(r'''
+#include "pam_grid.h"
+#include <algorithm>
+#include <cstdio>
+#include <random>
+#include <vector>
+using namespace pam;
+int main()
+{
+    std::mt19937 rng(5);
+    for (int d = 1; d <= 16; ++d) {
+        const int T = tile_points(d), H = tile_slots(d);
+        long probes = 0, longest = 0, keys = 0;
+        for (int rep = 0; rep < 8; ++rep) {
+            std::vector<uint32_t> slot(H, ~0u);
+            std::vector<int> order(d + 1);
+            for (int p = 0; p < T; ++p) {
+                for (int c = 0; c <= d; ++c) order[c] = c;
+                std::shuffle(order.begin(), order.end(), rng);
+                uint32_t key = (uint32_t)p << (d + 1);
+                for (int k = 0; k <= d; ++k) {
+                    if (k) key |= 1u << order[k];
+                    uint32_t h = tile_hash(key, H);
+                    long n = 1;
+                    for (; slot[h] != ~0u; h = h + 1 < (uint32_t)H ? h + 1 : 0)
+                        if (++n > H) { printf("d=%d: no room for row %ld\n", d, keys); return 1; }
+                    slot[h] = key;
+                    probes += n, ++keys, longest = std::max(longest, n);
+                }
+            }
+        }
+        printf("d=%d mean %.1f longest %ld\n", d, (double)probes / keys, longest);
+        if ((double)probes / keys > 12 || longest > H / 2) return 2;
+    }
+    return 0;
+}
+''')
+    exe = tmp_path / "hash"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(os.path.dirname(LIB), "csrc"), str(src), "-o",
+                    str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout
+
+
 def test_range_pass_after_a_failed_allocation(run):
     """A build whose vertex table grows moves the bucket table too; when it
     then runs out of memory for the points, the next build finds a bucket

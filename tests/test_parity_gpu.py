@@ -622,9 +622,8 @@ def test_repeated_builds_are_deterministic():
 
 @pytest.mark.parametrize("flags", [0, 1])
 def test_tile_overflow_fallback(O, flags):
-    """d=8 isolated points: each tile of 512 points has 4608 distinct
-    vertices, more than the build's per-tile table holds, so the splat
-    kernels take their direct-atomic path for those tiles."""
+    """d=8 isolated points: every contribution of a tile (2304 at 256 points)
+    is a row of its own, the most that a tile's LDS hash ever holds."""
     log(f"[edge] tile overflow flags={flags}")
     d, n = 8, 1100
     rng = np.random.default_rng(120)
@@ -639,6 +638,62 @@ def test_tile_overflow_fallback(O, flags):
     assert_lattice_equal(res, olat)
     # isolated points: in normalised mode out = v, so dL/df is exactly 0
     check_filter(res, O, olat, v, g, flags, df_is_zero=bool(flags))
+
+
+@pytest.mark.parametrize("d,flags", [(3, 0), (4, 1), (5, 0), (5, 1), (9, 0), (9, 1), (10, 0), (11, 0), (11, 1),
+                                     (13, 0), (14, 1), (15, 0)])
+def test_scattered_tiles(O, d, flags):
+    """Tiles with (nearly) as many rows as contributions, where points up to
+    d = 11 share almost no vertex: two full tiles and a ragged one."""
+    n = 2 * (512 if d <= 5 else 256) + 77
+    log(f"[edge] scattered tiles d={d} flags={flags}")
+    rng = np.random.default_rng(123 + d)
+    f = rng.uniform(0.0, 60.0 if d <= 5 else (20.0 if d <= 11 else 3.0), size=(n, d)).astype(np.float32)
+    v = rng.standard_normal((n, 10)).astype(np.float32)
+    g = rng.standard_normal((n, 10)).astype(np.float32)
+    res = gpu_run(f, v, g, flags)
+    olat = O.lattice(f)
+    assert d > 11 or olat.M > 0.9 * n * (d + 1)
+    assert_lattice_equal(res, olat)
+    check_filter(res, O, olat, v, g, flags, df_is_zero=bool(flags) and olat.M == n * (d + 1))
+
+
+@pytest.mark.parametrize("d", [9, 10, 11, 13, 14, 15])
+def test_clustered_high_dimensions(O, d):
+    """A coarse map with d - 3 learned-like channels (blobs plus noise): a
+    tile's rows are most of its contributions.  Built twice on one handle,
+    with other features between (the fixed key layout up to d = 9, measured
+    ranges above), the last tile ragged."""
+    import torch
+
+    import paper_1907_00641_amd as P
+
+    log(f"[edge] clustered d={d}")
+    w, h, z = 11, 9, 8
+    rng = np.random.default_rng(140 + d)
+    xyz = np.stack(np.meshgrid(np.arange(z), np.arange(h), np.arange(w), indexing="ij"), -1).reshape(-1, 3)[:, ::-1]
+    comp = rng.integers(0, 6, size=(z // 2 + 1, h // 2 + 1, w // 2 + 1))[xyz[:, 2] // 2, xyz[:, 1] // 2, xyz[:, 0] // 2]
+
+    def features(s):
+        means = rng.uniform(-1.5, 1.5, size=(6, d - 3))
+        return np.concatenate([xyz * (8.0 / w), means[comp] + 0.4 * rng.standard_normal((len(xyz), d - 3))],
+                              1).astype(np.float32) * np.float32(s)
+
+    lat = None
+    v = rng.standard_normal((len(xyz), 9)).astype(np.float32)
+    g = rng.standard_normal((len(xyz), 9)).astype(np.float32)
+    vt, gt = torch.from_numpy(v).cuda(), torch.from_numpy(g).cuda()
+    for s in (0.5, 0.3, 0.5):
+        f = features(s)
+        lat = P.pam_lattice_build(torch.from_numpy(f).cuda(), lat=lat)
+        out = P.pam_filter_fwd(lat, vt)
+        dv, df = P.pam_filter_bwd(lat, vt, gt)
+        res = dict(zip(("keys", "vert", "bary", "nbr"), P.pam_lattice_export(lat)), M=P.pam_lattice_stats(lat)[0],
+                   out=out.cpu().numpy(), dv=dv.cpu().numpy(), df=df.cpu().numpy())
+        olat = O.lattice(f)
+        assert_lattice_equal(res, olat)
+        check_filter(res, O, olat, v, g, 0)
+    lat.destroy()
 
 
 def test_large_lattice_unfused_blur(O):
@@ -774,8 +829,8 @@ def test_augmented_high_dimensions(O, d, C, scale):
     contribution do not all fit the augmented slice's LDS slots and are
     taken in chunks (7 of 13 values per chunk at d=12, 5 of 17 at d=16);
     C = 6 runs scalar-lane rows (32-lane groups, whole-group sums) and C = 4
-    two-lane groups (reduce-scatter).  Clustered points (the whole lattice
-    under 4096 vertices) keep every tile within the build's per-tile table."""
+    two-lane groups (reduce-scatter).  Clustered points: fewer than 4096
+    vertices in all."""
     import torch
 
     import paper_1907_00641_amd as P
@@ -806,15 +861,14 @@ def test_augmented_high_dimensions(O, d, C, scale):
 
 
 def test_augmented_overflow_tiles(O):
-    """PAM_EGRAD_AUGMENTED on tiles whose vertices overflow the build's
-    per-tile table: d=8 pairs of points 1.5 apart, the pairs on a grid of
-    spacing 20 (|f| stays small: the estimator's f (x) v - f Wv cancels in
-    proportion to |f|), so that the points of a pair interact (a non-zero
-    gradient) while 256 points of full pairs have more distinct vertices
-    than the table's 2048 slots (checked on the oracle's lattice below; the
-    pairs share no vertex, and a pair split over two tiles gives each 9).
-    The full tiles take the per-point paths of the augmented splat and
-    slice, the last (76 points) the tiled ones; same bar as elsewhere."""
+    """PAM_EGRAD_AUGMENTED on tiles of many rows: d=8 pairs of points 1.5
+    apart, the pairs on a grid of spacing 20 (|f| stays small: the
+    estimator's f (x) v - f Wv cancels in proportion to |f|), so that the
+    points of a pair interact (a non-zero gradient) while 256 points of full
+    pairs have more than 2048 distinct vertices (checked on the oracle's
+    lattice below; the pairs share no vertex, and a pair split over two tiles
+    gives each 9).  The full tiles' segments do not fit the tables that the
+    augmented splat and slice keep in LDS; same bar as elsewhere."""
     import torch
 
     import paper_1907_00641_amd as P
@@ -837,7 +891,7 @@ def test_augmented_overflow_tiles(O):
     olat = O.lattice(f)
     per_pair = np.sort([len(set(olat.vert[2 * j]) | set(olat.vert[2 * j + 1])) for j in range(npair)])
     assert per_pair.sum() == olat.M  # no vertex shared between pairs
-    assert per_pair[:128].sum() > 2048  # any 128 full pairs overflow the table
+    assert per_pair[:128].sum() > 2048  # any 128 full pairs
     dev = torch.device("cuda:0")
     ft, vt, gt = (torch.from_numpy(a).to(dev) for a in (f, v, g))
     lat = P.pam_lattice_build(ft)
@@ -1057,7 +1111,8 @@ def test_fused_eq8_term(O, case, monkeypatch):
     """PAM_FUSE_EQ8=1: the backward splat forms eq. 8's slice-side term
     (raw mode, C <= 32) and the backward slice reads it instead of g; same
     bar as the default path, on a volume, on the asymmetric filter (the keys
-    have no row of g) and on tiles that take the direct-atomic path."""
+    have no row of g) and on tiles of isolated points, whose segments do not
+    fit the splat's LDS tables."""
     monkeypatch.setenv("PAM_FUSE_EQ8", "1")
     log(f"[fused eq. 8] {case}")
     if case == "C2":
