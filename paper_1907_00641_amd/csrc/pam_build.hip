@@ -696,7 +696,8 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     uint16_t *order = reinterpret_cast<uint16_t *>(R + rec.order);
     uint16_t *lrow = reinterpret_cast<uint16_t *>(R + rec.lrow);
     uint32_t *wseg = reinterpret_cast<uint32_t *>(R + rec.wseg);
-    int2 *entry = reinterpret_cast<int2 *>(R + rec.entry);
+    float *weight = reinterpret_cast<float *>(R + rec.weight);
+    uint16_t *point = reinterpret_cast<uint16_t *>(R + rec.point);
     const bool valid = t < nt;
     const int64_t i = valid ? perm[base + t] : 0;
     for (int e = t; e < H; e += T)
@@ -873,7 +874,8 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
     __syncthreads();
     for (int e = t; e < nc; e += T) {
         const int pk = slist[e];
-        entry[e] = make_int2(__float_as_int(sw[(pk >> 5) * (D + 1) + (pk & 31)]), pk);
+        weight[e] = sw[(pk >> 5) * (D + 1) + (pk & 31)];
+        point[e] = (uint16_t)pk;
     }
     if (t < 64) {
         // bucket starts (then used as cursors): an exclusive scan of the

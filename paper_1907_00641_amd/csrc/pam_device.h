@@ -253,9 +253,12 @@ __device__ __forceinline__ int64_t insert_tile(int64_t ntiles)
 //            segments of at most kSegLen
 //   order  : nseg segment indices (uint16), the work order: longest first
 //   wseg   : the segments in that order
-//   entry  : nc entries sorted by row: point p of the tile contributes to
-//            that row with its vertex k, as a pair of the barycentric
-//            weight's bits and (p << 5) | k
+//   weight, point : nc entries sorted by row: point p of the tile contributes
+//            to that row with its vertex k; the barycentric weight (fp32),
+//            and (p << 5) | k (uint16).  Two arrays, as some kernels need the
+//            point alone, and 6 bytes per entry, where pairs take 8 (128^3
+//            points, d = 5, 32 channels: plain splat 131 us with pairs, 123;
+//            normalised backward splat 276 and 269)
 //   lrow   : nc rows, point-major: lrow[p * (d+1) + k] (uint16)
 // Fixed-size records; offsets in bytes.
 constexpr int kSegLen = 64;  // at most 64: the length field has 6 bits
@@ -273,7 +276,7 @@ __device__ __forceinline__ void seg_decode(uint32_t sd, int &e0, int &e1, int &r
 
 struct TileRec {
     int d, T, NC;
-    size_t rowid, rowkey, sfirst, seg, order, lrow, wseg, entry, bytes;
+    size_t rowid, rowkey, sfirst, seg, order, lrow, wseg, weight, point, bytes;
     __host__ __device__ explicit TileRec(int d_) : d(d_)
     {
         T = tile_points(d_);
@@ -285,8 +288,9 @@ struct TileRec {
         order = seg + (size_t)NC * 4;
         lrow = order + (((size_t)NC * 2 + 15) & ~(size_t)15);
         wseg = lrow + (((size_t)NC * 2 + 15) & ~(size_t)15);
-        entry = wseg + (size_t)NC * 4;
-        bytes = (entry + (size_t)NC * 8 + 255) & ~(size_t)255;
+        weight = wseg + (size_t)NC * 4;
+        point = weight + (size_t)NC * 4;
+        bytes = (point + (size_t)NC * 2 + 255) & ~(size_t)255;
     }
 };
 

@@ -339,7 +339,8 @@ struct TileView {
     const uint16_t *order;
     const uint16_t *lrow;
     const uint32_t *wseg;
-    const int2 *entry;
+    const float *weight;
+    const uint16_t *point;
 };
 
 template <int D>
@@ -355,7 +356,8 @@ __device__ __forceinline__ TileView tile_view(const uint8_t *tiles, int64_t tile
     v.order = reinterpret_cast<const uint16_t *>(R + rec.order);
     v.lrow = reinterpret_cast<const uint16_t *>(R + rec.lrow);
     v.wseg = reinterpret_cast<const uint32_t *>(R + rec.wseg);
-    v.entry = reinterpret_cast<const int2 *>(R + rec.entry);
+    v.weight = reinterpret_cast<const float *>(R + rec.weight);
+    v.point = reinterpret_cast<const uint16_t *>(R + rec.point);
     return v;
 }
 
@@ -487,17 +489,19 @@ __global__ __launch_bounds__((splat_rows_threads<D, SCH>())) void k_splat_rows(F
     // entries e0 + u .. of a batch: weights (0 past the end, where the last
     // entry's point is read again) and LDS offsets of the points' rows
     auto load = [&](int u, float(&w)[K], int(&p)[K]) {
-        int2 en[K];
-        int e[K];
+        float wt[K];
+        int pk[K], e[K];
 #pragma unroll
         for (int i = 0; i < K; ++i) {
             e[i] = e0 + u + i * SB + share * BL + (l & (BL - 1));
-            en[i] = tv.entry[max(min(e[i], e1 - 1), 0)];
+            const int ec = max(min(e[i], e1 - 1), 0);
+            wt[i] = tv.weight[ec];
+            pk[i] = tv.point[ec];
         }
 #pragma unroll
         for (int i = 0; i < K; ++i) {
-            w[i] = e[i] < e1 ? __int_as_float(en[i].x) : 0.0f;
-            const int pt = en[i].y >> 5;
+            w[i] = e[i] < e1 ? wt[i] : 0.0f;
+            const int pt = pk[i] >> 5;
             p[i] = pt * SCH + xs_swizzle<GL>(pt) * 4;
         }
     };
@@ -828,7 +832,7 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int e = t + j * T;
-        lst[j] = e < nc ? (uint32_t)tv.entry[e].y : 0u;
+        lst[j] = e < nc ? (uint32_t)tv.point[e] : 0u;
     }
     const int n0 = (nseg * 4 + 15) / 16, n1 = (nseg * 2 + 15) / 16, n2 = ((nrows + 1) * 2 + 15) / 16;
     const int n3 = (nrows * 4 + 15) / 16;  // every row has a segment: nrows <= nseg
@@ -1629,7 +1633,7 @@ __global__ __launch_bounds__(slice_aug_threads(D)) void k_slice_aug(FilterArgs a
     // decode every contribution once: its weight (0 for a point without a
     // row) and row; its slot is its entry
     for (int e = t; e < nc; e += NT) {
-        const int pk = tv.entry[e].y;
+        const int pk = tv.point[e];
         const int p = pk >> 5, k = pk & 31;
         const int r = sperm[p];
         rec[e] = make_int2(__float_as_int(r >= 0 ? sb[p][k] : 0.0f), max(r, 0));
