@@ -627,9 +627,10 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const int2 *__restrict__ pla
 // (LDS hash) whose keys are inserted into the vertex hash table, their slots
 // kept in the tile record for the resolve; the tile's (point, vertex)
 // contributions are counting-sorted by row (integer LDS atomics give each its
-// position within its row); each row's contributions are cut into segments of
-// at most kSegLen, and the segments are counting-sorted by length, longest
-// first, the order in which the splat hands them out.
+// position within its row); each row's contributions are cut evenly into
+// segments of at most kSegLen, and the rows are counting-sorted by the length
+// of their segments, longest first, the order in which the splat hands the
+// segments out.
 //
 // A point's vertices are told apart within the tile by the bucket the point
 // belongs to (its vertex 0; a bucket's points are consecutive) and the set of
@@ -861,15 +862,15 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
             slist[cnt[q[k]] + pos[k]] = (uint16_t)((t << 5) | k);
         }
     }
-    // segments in row order, and a histogram of their lengths
+    // segments in row order, and a histogram of their lengths (a row's last
+    // segment counted with its others)
     for (int r = t; r < nrows; r += T) {
         const int e0 = cnt[r], e1 = (r + 1 < nrows) ? cnt[r + 1] : nc;
+        const int ns = (e1 - e0 + kSegLen - 1) / kSegLen, len = (e1 - e0 + ns - 1) / ns;
         sfirst[r] = (uint16_t)nsg[r];
-        for (int j = 0, e = e0; e < e1; ++j, e += kSegLen) {
-            const int len = min(kSegLen, e1 - e);
-            seg[nsg[r] + j] = seg_encode(e, len, r);
-            atomicAdd(&hist[kSegLen - len], 1);  // longest first
-        }
+        for (int j = 0, e = e0; j < ns; ++j, e += len)
+            seg[nsg[r] + j] = seg_encode(e, min(len, e1 - e), r);
+        atomicAdd(&hist[kSegLen - len], ns);  // longest first
     }
     __syncthreads();
     for (int e = t; e < nc; e += T) {
@@ -912,14 +913,14 @@ __global__ __launch_bounds__(tile_points(D)) void k_sorted_tiles(const float *__
         hdr[3] = (uint32_t)nseg;
     }
     __syncthreads();
-    // work order: longest segments first
+    // work order: rows of longest segments first, a row's segments together
     for (int r = t; r < nrows; r += T) {
         const int e0 = cnt[r], e1 = (r + 1 < nrows) ? cnt[r + 1] : nc;
-        for (int j = 0, e = e0; e < e1; ++j, e += kSegLen) {
-            const int len = min(kSegLen, e1 - e);
-            const int at = atomicAdd(&hist[kSegLen - len], 1);
-            order[at] = (uint16_t)(nsg[r] + j);
-            wseg[at] = seg_encode(e, len, r);
+        const int ns = (e1 - e0 + kSegLen - 1) / kSegLen, len = (e1 - e0 + ns - 1) / ns;
+        const int at = atomicAdd(&hist[kSegLen - len], ns);
+        for (int j = 0, e = e0; j < ns; ++j, e += len) {
+            order[at + j] = (uint16_t)(nsg[r] + j);
+            wseg[at + j] = seg_encode(e, min(len, e1 - e), r);
         }
     }
 }

@@ -249,9 +249,12 @@ __device__ __forceinline__ int64_t insert_tile(int64_t ntiles)
 //   sfirst : nrows + 1 first segments (uint16): row r's are
 //            [sfirst[r], sfirst[r + 1])
 //   seg    : nseg segments in row order, start | (length - 1) << 13
-//            | row << 19 (uint32); a row's contributions are cut into
-//            segments of at most kSegLen
-//   order  : nseg segment indices (uint16), the work order: longest first
+//            | row << 19 (uint32); a row's contributions are cut evenly into
+//            as few segments of at most kSegLen as hold them
+//   order  : nseg segment indices (uint16), the work order: the rows by the
+//            length of their segments, longest first; a row's segments are
+//            neighbours, so that a wave that takes several adds them up
+//            before they reach the lattice
 //   wseg   : the segments in that order
 //   weight, point : nc entries sorted by row: point p of the tile contributes
 //            to that row with its vertex k; the barycentric weight (fp32),

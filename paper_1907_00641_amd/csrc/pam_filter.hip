@@ -63,6 +63,7 @@ constexpr int kDppHalfMirror = 0x141; // lane i <- 7 - i within each 8 lanes
 constexpr int kDppMirror = 0x140;     // lane i <- 15 - i within each 16 lanes
 constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
 constexpr int kDppShl1 = 0x101, kDppShl2 = 0x102, kDppShl4 = 0x104;
+constexpr int kDppWaveShr1 = 0x138;  // lane i <- i - 1 over the whole wave
 
 // Orders the LDS accesses of one wave before and after it (lanes of a wave
 // exchanging data through LDS).
@@ -370,6 +371,83 @@ __device__ __forceinline__ void copy16(void *dst, const void *src, int bytes)
         reinterpret_cast<uint4 *>(dst)[e] = reinterpret_cast<const uint4 *>(src)[e];
 }
 
+// Groups whose segment opens a run of one lattice row among the wave's groups
+// of GS lanes, as a mask of their first lanes (two tile rows of one vertex may
+// be apart: two runs).  A row's segments are neighbours in
+// the work order: such a run adds up its sums and only its first group flushes
+// them, so that a dense tile of few rows does not send an atomic per segment
+// to the same few addresses (80x80x48 points in two groups, d = 5, 8
+// channels: 50 us per plain splat with one per segment, 26 with one per run).
+// Call in wave-uniform control flow.
+template <int GS>
+__device__ __forceinline__ uint64_t run_heads(int row)
+{
+    const int lane = threadIdx.x & 63;
+    const int before = __builtin_amdgcn_update_dpp(row, row, kDppWaveShr1, 0xf, 0xf, false);  // the lane before's
+    return __ballot(lane % GS == 0 && (lane == 0 || before != row || row < 0));
+}
+// the mask of a wave without runs: the first lane of every group
+__host__ __device__ constexpr uint64_t all_heads(int gs)
+{
+    uint64_t m = 0;
+    for (int lane = 0; lane < 64; lane += gs)
+        m |= 1ull << lane;
+    return m;
+}
+
+// Adds the wave's segment sums (wf: SCH floats per group) to columns
+// [0, chc) of the rows at L.  Each atomic instruction covers whole rows: lane
+// c of every SCH lanes adds channel c of one group's run.
+template <int GS, int SCH>
+__device__ __forceinline__ void flush_runs(const float *wf, int row, uint64_t heads, int chc, float *__restrict__ L,
+                                           int ld)
+{
+    constexpr int GPW = 64 / GS;
+    const int lane = threadIdx.x & 63, c = lane % SCH;
+    if (heads == all_heads(GS)) {  // wave-uniform: no run of two, as in most waves of a sparse tile
+#pragma unroll
+        for (int i = 0; i < GPW * SCH / 64; ++i) {
+            const int g = i * (64 / SCH) + lane / SCH;
+            const int r = __shfl(row, g * GS);
+            if (r >= 0 && c < chc)
+                atomic_add_f32(&L[(int64_t)r * ld + c], wf[g * SCH + c]);
+        }
+        return;
+    }
+#pragma unroll 1  // unrolled it takes 16 registers more, and k_splat_rows then a wave per SIMD less
+    for (int i = 0; i < GPW * SCH / 64; ++i) {
+        const int g = i * (64 / SCH) + lane / SCH;
+        const int r = __shfl(row, g * GS);
+        if (r >= 0 && c < chc && (heads >> (g * GS) & 1)) {
+            const uint64_t next = heads >> (g * GS) >> GS;  // the heads after g
+            const int end = next ? g + 1 + (__ffsll((unsigned long long)next) - 1) / GS : GPW;
+            float sum = wf[g * SCH + c];
+            for (int j = g + 1; j < end; ++j)
+                sum += wf[j * SCH + c];
+            atomic_add_f32(&L[(int64_t)r * ld + c], sum);
+        }
+    }
+}
+
+// The sum of x (one value per group, in its first lane) over the run that a
+// group opens, left there.
+template <int GS>
+__device__ __forceinline__ float run_sum(float x, uint64_t heads)
+{
+    if (heads != all_heads(GS)) {  // wave-uniform
+        const int lane = threadIdx.x & 63, last = lane | (GS - 1);  // the group's last lane
+        const uint64_t next = heads >> last >> 1;                  // the heads after the group
+        const int end = next ? last + __ffsll((unsigned long long)next) : 64;  // the run's end
+#pragma unroll
+        for (int off = GS; off < 64; off <<= 1) {
+            const float y = __shfl_down(x, off);
+            if (lane + off < end)
+                x += y;
+        }
+    }
+    return x;
+}
+
 // ---------------------------------------------------------------------------
 // Splat of plain rows: L[m] += sum over the tile's points of b_k x
 // (forward, and the raw backward splat of dL/dv').
@@ -427,10 +505,8 @@ __device__ __forceinline__ int quad_bcast(int x)
 }
 
 template <int D, int VEC, int SCH, bool W>
-__global__ __launch_bounds__((splat_rows_threads<D, SCH>())) void k_splat_rows(FilterArgs a,
-                                                                               const uint8_t *__restrict__ tiles,
-                                                                               const float *__restrict__ x,
-                                                                               float *__restrict__ L)
+__global__ __launch_bounds__((splat_rows_threads<D, SCH>()), 8) void k_splat_rows(
+    FilterArgs a, const uint8_t *__restrict__ tiles, const float *__restrict__ x, float *__restrict__ L)
 {
     constexpr int T = tile_points(D);
     constexpr int NT = splat_rows_threads<D, SCH>(), NW = NT / 64;
@@ -484,7 +560,9 @@ __global__ __launch_bounds__((splat_rows_threads<D, SCH>())) void k_splat_rows(F
         row = tv.rowid[r];
         if (w >= nseg)
             row = -1;
-        len = __builtin_amdgcn_readfirstlane(e1 - e0);  // the wave's longest: segments come longest first
+        // the wave's longest: its first, or, when that ends a row (and so may
+        // be shorter than that row's others), its second
+        len = max(__builtin_amdgcn_readlane(e1 - e0, 0), __builtin_amdgcn_readlane(e1 - e0, GS));
     };
     // entries e0 + u .. of a batch: weights (0 past the end, where the last
     // entry's point is read again) and LDS offsets of the points' rows
@@ -567,6 +645,7 @@ __global__ __launch_bounds__((splat_rows_threads<D, SCH>())) void k_splat_rows(F
             gather(Int<kDppShl2>{});
         }
         const int frow = row;
+        const uint64_t heads = run_heads<GS>(frow);
         const int w1 = w0 + step;
         if (w1 < nseg) {  // the next segment's entries travel during the flush
             sd = sdn;
@@ -574,20 +653,16 @@ __global__ __launch_bounds__((splat_rows_threads<D, SCH>())) void k_splat_rows(F
             segment(w1 + gw);
             load(0, wb, pb);
         }
-        if (W && blockIdx.y == 0 && lane % GS == 0 && frow >= 0)
-            atomic_add_f32(&L[(int64_t)frow * ld + C], accw);
+        if (W && blockIdx.y == 0) {
+            accw = run_sum<GS>(accw, heads);
+            if (lane % GS == 0 && frow >= 0 && (heads >> lane & 1))
+                atomic_add_f32(&L[(int64_t)frow * ld + C], accw);
+        }
         float *wf = scratch + wave * GPW * SCH;
         if (share == 0)
             *reinterpret_cast<float4 *>(wf + gw * SCH + l * 4) = acc;
         wave_sync();
-        const int c = lane % SCH;
-#pragma unroll
-        for (int i = 0; i < GPW * SCH / 64; ++i) {
-            const int g2 = i * (64 / SCH) + lane / SCH;  // group whose channel c this lane adds
-            const int r2 = __shfl(frow, g2 * GS);
-            if (r2 >= 0 && c < chc)
-                atomic_add_f32(&L[(int64_t)r2 * ld + cc + c], wf[g2 * SCH + c]);
-        }
+        flush_runs<GS, SCH>(wf, frow, heads, chc, L + cc, ld);
         wave_sync();  // the scratch is read before the next segments overwrite it
     }
 }
@@ -759,7 +834,7 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
     // decoded, so it shares LDS with the segment sums.
     constexpr size_t kPointBytes = sizeof(float) * T * (D + 1) + sizeof(int) * T + 2 * sizeof(float) * NZ;
     // DIRECT: per-wave scratch of the segment-sum transpose instead of slots
-    constexpr int kXsWaveFloats = 64 * VEC + 64 / GL;
+    constexpr int kXsWaveFloats = 64 * VEC;
     constexpr size_t kSumBytes = DIRECT ? sizeof(float) * kXsWaveFloats * (splat_threads(D) / 64)
                                     : sizeof(float) * kSegCap * SCH + sizeof(float) * kSegCap;
     constexpr size_t kPoolBytes = (kPointBytes > kSumBytes ? kPointBytes : kSumBytes);
@@ -1103,9 +1178,6 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
                     }
                     if (W && l == 0)
                         atomic_add_f32(&L[row + C], accw);
-                } else {
-                    if (W && l == 0)
-                        atomic_add_f32(&L[(int64_t)xrow_id * ld + C], accw);
                 }
             }
             if constexpr (XS) {
@@ -1114,19 +1186,15 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
                 // covers whole rows (64 / SCH rows of SCH consecutive
                 // channels) rather than VEC scattered floats of 64 / GL rows.
                 float *wf = Ps + (t >> 6) * kXsWaveFloats;
-                int *wrow = reinterpret_cast<int *>(wf + 64 * VEC);
-                store_vec<VEC>(wf + gw * SCH + l * VEC, acc);
-                if (l == 0)
-                    wrow[gw] = xrow_id;
-                wave_sync();
-                const int c = lane % SCH;
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) {
-                    const int g2 = i * (64 / SCH) + lane / SCH;  // group whose channel c this lane adds
-                    const int row = wrow[g2];
-                    if (row >= 0 && c < chc)
-                        atomic_add_f32(&L[(int64_t)row * ld + cc + c], wf[g2 * SCH + c]);
+                const uint64_t heads = run_heads<GL>(xrow_id);
+                if constexpr (W) {
+                    accw = run_sum<GL>(accw, heads);
+                    if (l == 0 && xrow_id >= 0 && (heads >> lane & 1))
+                        atomic_add_f32(&L[(int64_t)xrow_id * ld + C], accw);
                 }
+                store_vec<VEC>(wf + gw * SCH + l * VEC, acc);
+                wave_sync();
+                flush_runs<GL, SCH>(wf, xrow_id, heads, chc, L + cc, ld);
                 wave_sync();  // the scratch is read before the next segments overwrite it
             }
         }
@@ -1160,8 +1228,6 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
         const int chc = min(SCH, C - cc);
         const float *xc = x + min(cc + l * VEC, C - VEC);  // in bounds for every lane
         float *wf = Ps + (t >> 6) * kXsWaveFloats;
-        int *wrow = reinterpret_cast<int *>(wf + 64 * VEC);
-        const int cf = lane % SCH;  // the channel this lane flushes
         for (;;) {
             int wbase = 0;
             if (lane == 0)
@@ -1212,19 +1278,12 @@ __global__ __launch_bounds__(splat_threads(D)) void k_splat(FilterArgs a, const 
                     }
                 }
             }
-            if (l == 0)
-                wrow[gw] = xrow_id;
+            const uint64_t heads = run_heads<GL>(xrow_id);
 #pragma unroll
             for (int q = 0; q < D; ++q) {
                 store_vec<VEC>(wf + gw * SCH + l * VEC, acc[q]);
                 wave_sync();
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) {
-                    const int g2 = i * (64 / SCH) + lane / SCH;  // group whose channel cf this lane adds
-                    const int row = wrow[g2];
-                    if (row >= 0 && cf < chc)
-                        atomic_add_f32(&L[(int64_t)row * ld + q * C + cc + cf], wf[g2 * SCH + cf]);
-                }
+                flush_runs<GL, SCH>(wf, xrow_id, heads, chc, L + q * C + cc, ld);
                 wave_sync();  // read before the next vector overwrites it
             }
         }

@@ -658,6 +658,47 @@ def test_scattered_tiles(O, d, flags):
     check_filter(res, O, olat, v, g, flags, df_is_zero=bool(flags) and olat.M == n * (d + 1))
 
 
+@pytest.mark.parametrize("d,C,flags", [(1, 8, 0), (1, 8, 1), (1, 16, 0), (1, 32, 1), (2, 5, 1), (3, 24, 0), (5, 4, 1),
+                                       (6, 16, 1), (8, 8, 1), (8, 12, 0), (3, 12, 2), (5, 5, 2), (8, 16, 2)])
+def test_dense_tiles(O, d, C, flags):
+    """Tiles of few rows: a row has many segments, whose sums a wave adds up
+    before they reach the lattice (runs within a wave, runs cut by its end,
+    whole waves of one row); plain, normalised and augmented splats.  The
+    error against the 64-bit oracle stays below 6e-7: roundings of 2^-24 that
+    add up like the root of their number, in sums of at most 64 terms, of at
+    most 16 segments and of up to 10 tiles."""
+    import torch
+
+    import paper_1907_00641_amd as P
+    from paper_1907_00641_amd import binding as B
+
+    n = 5000 if d <= 5 else 2100
+    log(f"[edge] dense tiles d={d} C={C} flags={flags}")
+    rng = np.random.default_rng(170 + d + C)
+    f = rng.uniform(-0.4, 0.4, size=(n, d)).astype(np.float32)
+    v = rng.standard_normal((n, C)).astype(np.float32)
+    g = rng.standard_normal((n, C)).astype(np.float32)
+    olat = O.lattice(f)
+    if flags < 2:
+        res = gpu_run(f, v, g, flags)
+        assert_lattice_equal(res, olat)
+        check_filter(res, O, olat, v, g, flags)
+        out, st = O.forward(olat, v, bool(flags))
+        dv, _ = O.backward(olat, v, g, bool(flags), st)
+        for name, a, b in (("out", res["out"], out), ("dv", res["dv"], dv)):
+            assert rel_l2(a, b) < 6e-7, (name, rel_l2(a, b))
+        return
+    lat = P.pam_lattice_build(torch.from_numpy(f).cuda())
+    vt, gt = torch.from_numpy(v).cuda(), torch.from_numpy(g).cuda()
+    P.pam_filter_fwd(lat, vt, 0)
+    _, df = P.pam_filter_bwd(lat, vt, gt, B.PAM_EGRAD_AUGMENTED)
+    out, st = O.forward(olat, v, False)
+    dv, _ = O.backward(olat, v, g, False, st)
+    odf = O.backward_augmented(olat, f, v, g)
+    log("  " + check_array("augmented df", df.cpu().numpy(), odf, "", 1e-5 * df_term_scale(f, v, g, out, dv)))
+    lat.destroy()
+
+
 @pytest.mark.parametrize("d", [9, 10, 11, 13, 14, 15])
 def test_clustered_high_dimensions(O, d):
     """A coarse map with d - 3 learned-like channels (blobs plus noise): a
