@@ -514,8 +514,7 @@ __global__ __launch_bounds__((splat_rows_threads<D, SCH>()), 8) void k_splat_row
     constexpr int GS = GL * S, GPW = 64 / GS;          // lanes per segment, segments per wave
     constexpr int BL = GL < 4 ? GL : 4;                // lanes that load entries together
     constexpr int K = 4, SB = S * BL, EB = K * SB;     // entries per lane, per step and per batch
-    __shared__ __attribute__((aligned(16))) float xs[T * SCH];
-    __shared__ __attribute__((aligned(16))) float scratch[NW * GPW * SCH];
+    __shared__ __attribute__((aligned(16))) float xs[T * SCH + NW * GPW * SCH];  // rows of x, waves' scratch
     const TileView tv = tile_view<D>(tiles, blockIdx.x);
     const int t = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * T;
@@ -564,8 +563,17 @@ __global__ __launch_bounds__((splat_rows_threads<D, SCH>()), 8) void k_splat_row
         // be shorter than that row's others), its second
         len = max(__builtin_amdgcn_readlane(e1 - e0, 0), __builtin_amdgcn_readlane(e1 - e0, GS));
     };
-    // entries e0 + u .. of a batch: weights (0 past the end, where the last
-    // entry's point is read again) and LDS offsets of the points' rows
+    // Each group's place in its wave's scratch: the group's last sum, or
+    // zeros, but never an infinity or a NaN.
+    float *wf = xs + T * SCH + wave * GPW * SCH;
+    const int spare = T * SCH + (wave * GPW + gw) * SCH;
+    auto clear = [&]() {
+        if (share == 0)
+            *reinterpret_cast<float4 *>(wf + gw * SCH + l * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    // entries e0 + u .. of a batch: weights and LDS offsets of the points'
+    // rows; past the end weight 0 and the group's place in the scratch (not
+    // a point's row, whose values may be infinite)
     auto load = [&](int u, float(&w)[K], int(&p)[K]) {
         float wt[K];
         int pk[K], e[K];
@@ -580,11 +588,12 @@ __global__ __launch_bounds__((splat_rows_threads<D, SCH>()), 8) void k_splat_row
         for (int i = 0; i < K; ++i) {
             w[i] = e[i] < e1 ? wt[i] : 0.0f;
             const int pt = pk[i] >> 5;
-            p[i] = pt * SCH + xs_swizzle<GL>(pt) * 4;
+            p[i] = e[i] < e1 ? pt * SCH + xs_swizzle<GL>(pt) * 4 : spare;
         }
     };
     segment(first + gw);
     load(0, wb, pb);
+    clear();
 #pragma unroll
     for (int i = 0; i < NI; ++i)
         if (xp < RPI) {
@@ -658,12 +667,15 @@ __global__ __launch_bounds__((splat_rows_threads<D, SCH>()), 8) void k_splat_row
             if (lane % GS == 0 && frow >= 0 && (heads >> lane & 1))
                 atomic_add_f32(&L[(int64_t)frow * ld + C], accw);
         }
-        float *wf = scratch + wave * GPW * SCH;
         if (share == 0)
             *reinterpret_cast<float4 *>(wf + gw * SCH + l * 4) = acc;
         wave_sync();
         flush_runs<GS, SCH>(wf, frow, heads, chc, L + cc, ld);
         wave_sync();  // the scratch is read before the next segments overwrite it
+        if (__ballot(!(fabsf(acc.x) + fabsf(acc.y) + fabsf(acc.z) + fabsf(acc.w) <= 3.4e38f))) {
+            clear();
+            wave_sync();
+        }
     }
 }
 

@@ -737,6 +737,38 @@ def test_clustered_high_dimensions(O, d):
     lat.destroy()
 
 
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("d,C", [(5, 8), (5, 7), (3, 16), (5, 36), (8, 12), (8, 32)])
+def test_infinite_values(O, d, C, flags):
+    """Infinite and NaN values reach exactly the outputs that their points'
+    vertices do, as infinities of their sign and as NaN; channels without
+    any, and points out of reach, are untouched."""
+    n = 1800
+    log(f"[edge] infinite values d={d} C={C} flags={flags}")
+    rng = np.random.default_rng(180 + d + C)
+    f = rng.uniform(0.0, 9.0, size=(n, d)).astype(np.float32)
+    v = rng.standard_normal((n, C)).astype(np.float32)
+    g = rng.standard_normal((n, C)).astype(np.float32)
+    for x in (v, g):
+        at = rng.choice(n, 9, replace=False)
+        x[at[:3], 0] = np.inf
+        x[at[3:6], 1] = -np.inf
+        x[at[6:], C - 1] = np.nan
+    res = gpu_run(f, v, g, flags)
+    olat = O.lattice(f)
+    out, st = O.forward(olat, v, bool(flags))
+    checks = [("out", res["out"], out)]
+    if not flags:
+        checks.append(("dv", res["dv"], O.backward(olat, v, g, False, st)[0]))
+    for name, a, b in checks:
+        assert np.isinf(b[:, 0]).any() and np.isnan(b[:, C - 1]).any() and np.isfinite(b[:, 2:C - 1]).all()
+        assert np.array_equal(np.isnan(a), np.isnan(b)), name
+        inf = np.isinf(b)
+        assert np.array_equal(np.isinf(a), inf) and np.array_equal(a[inf], b[inf]), name
+        ok = np.isfinite(b)
+        log("  " + check_array(name, np.where(ok, a, 0.0), np.where(ok, b, 0.0), ""))
+
+
 def test_large_lattice_unfused_blur(O):
     """A lattice too large for the fused two-direction blur (M * ld * 4 bytes
     above 32 MiB: 2200 isolated points in d=3 give 8800 vertices of 1024
