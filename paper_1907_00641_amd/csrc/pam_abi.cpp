@@ -182,11 +182,12 @@ pam_status_t ensure(DevBuf &b, size_t bytes, const char *what)
 }
 
 // Buffers that are sized together.  An allocation of 2 MB and more costs the
-// host up to 0.3 ms, smaller ones a few us (a new handle of 614 400 points:
-// eight large buffers, 1.3 ms), so the large buffers of a group share one
-// allocation and small ones have their own.  Contents are lost when a buffer
-// of the group grows; `moved` tells.
-constexpr size_t kLargeBuffer = (size_t)1 << 20;
+// host 15 to 350 us, smaller ones about 1 us (a new handle of 614 400 points:
+// eight large buffers, 1.3 ms; four lattice buffers of 1.7 MB: 6 us apart, 36
+// in one), so the buffers of a group from 2 MB on share one allocation and
+// smaller ones have their own.  Contents are lost when a buffer of the group
+// grows; `moved` tells.
+constexpr size_t kLargeBuffer = ((size_t)2 << 20) - 1;  // the largest that has its own
 
 struct Want {
     DevBuf *buf;

@@ -1,5 +1,5 @@
 /* The HIP runtime calls that libpam_lattice.so makes, without a GPU: device
- * allocations are addresses that nothing reads, launches are recorded, and
+ * allocations are addresses that nothing reads, they and launches are recorded, and
  * the build's compaction publishes the outcome that the test sets, so that
  * the library's own launch sequence, grids and buffer handling run on the
  * CPU.  Loaded with RTLD_GLOBAL before the library, whose calls then resolve
@@ -46,6 +46,7 @@ int hipMalloc(void **p, size_t bytes)
 {
     if (bytes > g_fail_above)
         return kOutOfMemory;
+    g_len += (size_t)snprintf(g_log + g_len, sizeof g_log - g_len, "malloc %zu\n", bytes);
     *p = (void *)g_next;
     g_next += (bytes + 0xffff) & ~(uint64_t)0xffff;
     return kOk;

@@ -25,6 +25,7 @@ shim.fake_fail_above.argtypes = [ctypes.c_uint64]
 vp, i64, i32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32
 L.pam_lattice_build.argtypes = [vp, i64, i32, vp, ctypes.POINTER(vp)]
 L.pam_lattice_set_capacity.argtypes = [vp, i64, i32]
+L.pam_filter_fwd.argtypes = [vp, vp, i32, ctypes.c_uint32, vp, vp]
 FEAT = vp(0x200000)
 h = vp(None)
 
@@ -35,12 +36,14 @@ def build(n, d, vertices, buckets=200):
     st = L.pam_lattice_build(FEAT, n, d, None, ctypes.byref(h))
     rows = []
     for line in shim.fake_log().decode().splitlines():
+        if line.startswith("malloc"):
+            continue
         name, gx, gy, gz, bx = line.split()[:5]
         rows.append((re.search("(k_[a-z0-9_]+?)(ILi|E|$)", name).group(1), int(gx), int(bx), line.endswith("refused")))
     return st, rows
 
-def kernels(rows):
-    return [r[0] for r in rows]
+def mallocs():
+    return [int(line.split()[1]) for line in shim.fake_log().decode().splitlines() if line.startswith("malloc")]
 
 out = {}
 exec(sys.argv[3])
@@ -205,3 +208,19 @@ out['large'] = build(4000, 3, 100)
     st, rows = out["large"]
     assert out["set"] == 0
     assert st == 0 and not any(r[3] for r in rows), rows
+
+
+def test_shared_allocation_of_large_buffers_only(run):
+    """The four lattice buffers of a forward call: allocations below 2 MB
+    cost the host about 1 us each and stay apart, from 2 MB on (tens to
+    hundreds of us each) they share one."""
+    out = run("""
+for name, vertices in (('small', 16000), ('large', 17000)):
+    h = vp(None)
+    build(100000, 3, vertices)
+    shim.fake_clear()
+    out[name] = [L.pam_filter_fwd(h, vp(0x40000000), 32, 0, vp(0x60000000), None), mallocs()]
+""")
+    assert out["small"] == [0, [16000 * 128] * 4]
+    st, sizes = out["large"]
+    assert st == 0 and len(sizes) == 1 and sizes[0] >= 4 * 17000 * 128
