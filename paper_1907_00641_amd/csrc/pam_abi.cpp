@@ -628,10 +628,14 @@ static pam_status_t build_impl(const float *feat, int64_t n, int32_t d, const in
         h->cap = next_pow2((uint64_t)guess);
     }
 
-    // the bucket table keeps its capacity while its load stays between 1/16
-    // and 1/2 (a capacity that changes costs the next build a range pass)
+    // the bucket table keeps its capacity while its load is at most 1/2 and at
+    // least 1/16, or it has no more than kSmallBuckets slots, whose clearing
+    // and scan take no longer than those of fewer (a capacity that changes
+    // costs the build a range pass, two launches of 6 us each and their gaps)
+    constexpr int64_t kSmallBuckets = 1 << 16;
     if (h->prev_buckets >= 0) {
-        if ((int64_t)h->bcap < 2 * h->prev_buckets || (int64_t)h->bcap > std::max<int64_t>(16 * h->prev_buckets, 1024))
+        if ((int64_t)h->bcap < 2 * h->prev_buckets ||
+            (int64_t)h->bcap > std::max<int64_t>(16 * h->prev_buckets, kSmallBuckets))
             h->bcap = std::min<uint64_t>(next_pow2(std::max<int64_t>(4 * h->prev_buckets, 1024)), (uint64_t)1 << 31);
     } else
         h->bcap = next_pow2((uint64_t)std::min<int64_t>(std::max<int64_t>(n / 4, 1024), (int64_t)1 << 22));

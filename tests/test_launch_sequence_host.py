@@ -224,3 +224,20 @@ for name, vertices in (('small', 16000), ('large', 17000)):
     assert out["small"] == [0, [16000 * 128] * 4]
     st, sizes = out["large"]
     assert st == 0 and len(sizes) == 1 and sizes[0] >= 4 * 17000 * 128
+
+
+def test_second_build_needs_no_range_pass(run):
+    """A new handle guesses its bucket table from the point count.  A guess
+    of at most 2^16 slots is kept however few buckets there are, so that the
+    second build finds it emptied; a larger one that is far too large shrinks
+    once, and the build after that is fast."""
+    out = run("""
+for name, n in (('small', 32768), ('mid', 262144), ('large', 2000000)):
+    h = vp(None)
+    out[name] = [[r[0] for r in build(n, 3, 900, 300)[1]] for _ in range(3)]
+h = vp(None)
+out['wide'] = [[r[0] for r in build(32768, 3, 900, 20000)[1]] for _ in range(3)]  # over half full
+""")
+    takes_range = {k: ["k_range" in rows for rows in v] for k, v in out.items()}
+    assert takes_range == {"small": [True, False, False], "mid": [True, False, False], "large": [True, True, False],
+                           "wide": [True, True, False]}
