@@ -30,7 +30,7 @@ METRIC = "Mvoxels/s PAM lattice filter fwd+bwd, 128³ d=5 C=32; % HBM roofline"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_C3.json")
 PMC_FILE = os.path.join(ROOT, "profiles", "counters_C3.json")
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1907_00641_amd", "csrc", f)
-               for f in ("pam_device.h", "pam_build.hip", "pam_filter.hip")]
+               for f in ("pam_grid.h", "pam_device.h", "pam_build.hip", "pam_filter.hip")]
 
 
 def kernel_bytes(name: str, n: int, d: int, C: int, M: int, ldq: int = 0) -> float:

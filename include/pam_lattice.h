@@ -79,10 +79,11 @@ typedef enum {
  *          the handle is rebuilt in place, reusing its buffers (grown when
  *          needed) and sizing the hash table from the previous vertex count.
  * Waits for the vertex count of each attempt (the rest of the build then runs
- * while the caller goes on): once normally; once more when a rebuild's keys
- * do not fit the fixed key layout it tries first (it then measures their
- * range), and after each regrowth of a hash table.  Invalidates the forward
- * state kept for pam_filter_bwd.
+ * while the caller goes on; it no longer reads feat): once normally; once
+ * more when a rebuild's keys do not fit the fixed key layout it tries first
+ * (it then measures their range), after each regrowth of a hash table, and
+ * when the vertices outgrow the handle's buffers (always on its first build).
+ * Invalidates the forward state kept for pam_filter_bwd.
  */
 pam_status_t pam_lattice_build(const float *feat, int64_t n, int32_t d, void *stream,
                                pam_lattice_t *lat);

@@ -634,12 +634,16 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const int2 *__restrict__ pla
 //
 // A point's vertices are told apart within the tile by the bucket the point
 // belongs to (its vertex 0; a bucket's points are consecutive) and the set of
-// coordinates that vertex k has stepped down: a local key of 32 bits, where
-// the packed keys take 64 and a shift per coordinate.  Only the distinct
-// local keys are turned into packed keys (a vertex that two buckets share
-// becomes two rows with one id; buckets are in the order of a hash, so that
-// is rare).  The launch is bound by its vector instructions: with 64-bit keys
-// it took 1090 per wave and 94 us at 128^3, d = 5.
+// coordinates that vertex k has stepped down: a local key of 32 bits.  Only
+// the distinct local keys are turned into packed keys (a vertex that two
+// buckets share becomes two rows with one id; in dense tiles that is rare, and
+// tiles of scattered points have room for the rows).  Keys of 32 bits are for
+// LDS: a table of 64-bit packed keys that every tile fits would take 59 KB at
+// d = 5 instead of 37, two blocks per CU instead of four.  They hardly change
+// the time (128^3, d = 5: 1000 vector instructions per wave and 93 us; packed
+// keys in a table of 2048 slots 1090 and 94), which vector instructions (they
+// fill two thirds of the SIMDs' cycles) and memory (356 MB, 3.8 TB/s, where a
+// copy reaches 5.9) share.
 //
 // Sorted points share vertices in runs: only the first lane of a run of
 // equal keys in a wave probes the LDS table and later counts the whole run,

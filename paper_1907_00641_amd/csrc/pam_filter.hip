@@ -324,10 +324,10 @@ __host__ __device__ constexpr int seg_cap(int T) { return T >= 512 ? PAM_SEG_CAP
 #endif
 __host__ __device__ constexpr int splat_threads(int d) { return tile_points(d) * PAM_SPLAT_SPREAD; }
 
-// Splat modes: x as given (with the fused eq. 8 term), or, for the normalised backward pass, x = g / z with the weight
-// column taking b * gamma, or the augmented channels of the embedding
-// gradient: d*C lattice channels, channel a*C + c taking f_a x_c (f the
-// build's features).
+// Splat modes: x as given (with the fused eq. 8 term), or, for the normalised
+// backward pass, x = g / z with the weight column taking b * gamma, or the
+// augmented channels of the embedding gradient: d*C lattice channels, channel
+// a*C + c taking f_a x_c (f the build's features).
 constexpr int kSplatPlain = kSplatModePlain;
 constexpr int kSplatNormBwd = kSplatModeNormBwd;
 constexpr int kSplatAug = kSplatModeAug;
@@ -462,18 +462,20 @@ __device__ __forceinline__ float run_sum(float x, uint64_t heads)
 // The lanes of a quad
 // (of a pair with 8 channels) load BL consecutive entries (weight and point)
 // straight from the tile record, the next batch while the current one is
-// summed, and broadcast them with DPP moves, so that entries take no LDS.  A
-// segment's sum goes to the lattice through a per-wave LDS transpose, so
-// that each atomic instruction covers whole rows.
+// summed, and broadcast them with DPP moves, so that entries take no LDS.
+// Segment sums go to the lattice through a per-wave LDS transpose, a row's
+// neighbouring segments as one (flush_runs), so that each atomic instruction
+// covers whole rows.
 //
 // LDS (64 KB of rows for 512 points and 32 channels, 16 KB of transpose
-// scratch) leaves two blocks of 1024 threads per CU: one loads its rows
-// while the other sums.  Bound by the latency of its chain (record and row
-// numbers, rows of x, sums, flush) over two blocks per CU: 128^3 points,
-// d = 5, 32 channels 133 us per launch (150 us gathering the rows through
-// the caches), of which 121 remain without the sums and 92 without the rows.
-// A persistent variant with the next item's loads under way (spilled, 342
-// us), 512 threads (194 us) and windows of 256 points (142 us) were slower.
+// scratch) and at most 64 registers leave two blocks of 1024 threads per CU:
+// one loads its rows while the other sums.  Bound by the latency of its chain
+// (record and row numbers, rows of x, sums, flush) over two blocks per CU:
+// 128^3 points, d = 5, 32 channels 123 us per launch (150 us gathering the
+// rows through the caches).  While it took 133, with entries of 8 bytes, 121
+// remained without the sums and 92 without the rows; a persistent variant
+// with the next item's loads under way (spilled, 342 us), 512 threads (194
+// us) and windows of 256 points (142 us) were slower.
 // ---------------------------------------------------------------------------
 
 #ifndef PAM_SPLAT_THREADS
@@ -2220,7 +2222,7 @@ hipError_t launch_splat(int d, const FilterArgs &a, const uint8_t *tiles, const 
             // few tiles: their segments are dealt to several blocks each, up
             // to two rounds of blocks on the chip (40x36x28 points, d = 12:
             // 158 tiles of thousands of short segments, 280 us per launch
-            // with one block each)
+            // with one block each, 57 dealt)
             const unsigned passes = (unsigned)((a.c + SCH - 1) / SCH);
             const unsigned deal = std::max(1u, std::min(8u, 2 * kCus / (grid.x * passes)));
             const dim3 g(grid.x, passes, deal), b(splat_rows_threads<D, SCH>());
@@ -2295,7 +2297,7 @@ hipError_t launch_slice_bwd(int d, const FilterArgs &a, const uint8_t *tiles, co
     const dim3 grid(tiles_for(d, a.n)), block(tile_threads(d));
     if (hA && a.normalize)
         return hipErrorInvalidValue;
-    if (a.src_n != a.n || a.tgt_0 != 0) {  // asymmetric filter (raw mode)
+    if (a.src_n != a.n || a.tgt_0 != 0) {  // asymmetric filter (raw mode): passes of 32 channels whatever C
         if (hA) {
             PAM_DISPATCH_D(d, PAM_DISPATCH_VEC(a, hipLaunchKernelGGL((k_slice_bwd<D, VEC, false, true, kCH, true>), grid,
                                                                      block, 0, s, a, tiles, val, grad, A, At, hA,
